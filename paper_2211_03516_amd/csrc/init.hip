@@ -86,16 +86,15 @@ __global__ __launch_bounds__(kErrThreads) void k_dose_error(const float* __restr
   }
 }
 
-__global__ void k_dose_error_final(const double* __restrict__ part, int nblocks, int64_t n, double* __restrict__ out) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double l1 = 0.0, tsum = 0.0, wrong = 0.0;
-    for (int b = 0; b < nblocks; ++b) {
-      l1 += part[3 * b];
-      tsum += part[3 * b + 1];
-      wrong += part[3 * b + 2];
-    }
-    out[0] = tsum > 0.0 ? l1 / tsum : 0.0;
-    out[1] = wrong / (double)n;
+// The block sums in a fixed order by one workgroup (a single thread walking
+// the 1024 x 3 sums took 122 us of waiting for loads, this 5 us).
+__global__ __launch_bounds__(kSumThreads) void k_dose_error_final(const double* __restrict__ part, int nblocks,
+                                                                  int64_t n, double* __restrict__ out) {
+  double s[3];
+  block_sum_rows<3>(part, nblocks, s);
+  if (threadIdx.x == 0) {
+    out[0] = s[1] > 0.0 ? s[0] / s[1] : 0.0;
+    out[1] = s[2] / (double)n;
   }
 }
 
@@ -131,16 +130,15 @@ __global__ __launch_bounds__(kEqThreads) void k_eq_stats(const float* __restrict
   }
 }
 
-// stats[0] mean, stats[1] population std, stats[2] clip = mean + 3 std
-__global__ void k_eq_final(const double* __restrict__ part, int nblocks, int64_t n, double* __restrict__ stats) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    double s1 = 0.0, s2 = 0.0;
-    for (int b = 0; b < nblocks; ++b) {
-      s1 += part[2 * b];
-      s2 += part[2 * b + 1];
-    }
-    const double mean = s1 / (double)n;
-    const double var = fmax(s2 / (double)n - mean * mean, 0.0);
+// stats[0] mean, stats[1] population std, stats[2] clip = mean + 3 std (one
+// workgroup: 84 us on one thread, 5 us so)
+__global__ __launch_bounds__(kSumThreads) void k_eq_final(const double* __restrict__ part, int nblocks, int64_t n,
+                                                          double* __restrict__ stats) {
+  double s[2];
+  block_sum_rows<2>(part, nblocks, s);
+  if (threadIdx.x == 0) {
+    const double mean = s[0] / (double)n;
+    const double var = fmax(s[1] / (double)n - mean * mean, 0.0);
     const double sd = sqrt(var);
     stats[0] = mean;
     stats[1] = sd;
@@ -194,7 +192,7 @@ vam_status vam_dose_error(const float* dose, const float* target, int64_t n, dou
   VAM_HIP_TRY(hipMallocAsync((void**)&part, (3 * blocks + 2) * sizeof(double), stream), "allocating partials");
   hipLaunchKernelGGL(k_dose_error, dim3(blocks), dim3(kErrThreads), 0, stream, dose, target, n, (float)threshold,
                      (float)sharpness, part);
-  hipLaunchKernelGGL(k_dose_error_final, dim3(1), dim3(64), 0, stream, part, blocks, n, part + 3 * blocks);
+  hipLaunchKernelGGL(k_dose_error_final, dim3(1), dim3(kSumThreads), 0, stream, part, blocks, n, part + 3 * blocks);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess)
     e = hipMemcpyAsync(out2, part + 3 * blocks, 2 * sizeof(double), hipMemcpyDeviceToHost, stream);
@@ -213,7 +211,7 @@ vam_status vam_equalize_u8(const float* proj, int64_t n, uint8_t* out, double* s
   VAM_HIP_TRY(hipMallocAsync((void**)&part, (2 * blocks + 3) * sizeof(double), stream), "allocating partials");
   double* st = part + 2 * blocks;
   hipLaunchKernelGGL(k_eq_stats, dim3(blocks), dim3(kEqThreads), 0, stream, proj, n, part);
-  hipLaunchKernelGGL(k_eq_final, dim3(1), dim3(64), 0, stream, part, blocks, n, st);
+  hipLaunchKernelGGL(k_eq_final, dim3(1), dim3(kSumThreads), 0, stream, part, blocks, n, st);
   hipLaunchKernelGGL(k_eq_map, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, proj, n, st, out);
   hipError_t e = hipGetLastError();
   if (e == hipSuccess && stats3) e = hipMemcpyAsync(stats3, st, 3 * sizeof(double), hipMemcpyDeviceToHost, stream);

@@ -166,6 +166,47 @@ __device__ inline double fx_scale(unsigned max_bits, double coef) {
   return ldexp(1.0, 61 - e);
 }
 
+// Largest of the block's values (blockDim.x a multiple of 64, at most 1024),
+// valid on thread 0.
+__device__ inline unsigned block_max(unsigned m) {
+  __shared__ unsigned wave_max[16];
+  for (int off = 32; off > 0; off >>= 1) m = max(m, (unsigned)__shfl_xor((int)m, off));
+  if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (unsigned w = 1; w < (blockDim.x + 63) / 64; ++w) m = max(m, wave_max[w]);
+  return m;
+}
+
+// *out = max(*out, m) from many blocks.  Atomics on one address are served
+// one after the other (about 7 ns each), so a block whose value is already
+// reached leaves after a plain read: *out only grows during the kernel.
+__device__ inline void raise_max(unsigned* out, unsigned m) {
+  if (m > *(volatile unsigned*)out) atomicMax(out, m);
+}
+
+// Sums of N columns of `part` ([nparts][N], FP64) by one block of kSumThreads
+// threads: thread t adds rows t, t + kSumThreads, ... in order, then a tree
+// of fixed shape adds the threads' sums; s[] is valid on thread 0.
+constexpr int kSumThreads = 256;
+template <int N>
+__device__ inline void block_sum_rows(const double* __restrict__ part, int nparts, double (&s)[N]) {
+  __shared__ double wave_sum[N][kSumThreads / 64];
+  for (int k = 0; k < N; ++k) s[k] = 0.0;
+  for (int i = threadIdx.x; i < nparts; i += kSumThreads)
+    for (int k = 0; k < N; ++k) s[k] += part[(int64_t)i * N + k];
+  for (int k = 0; k < N; ++k) {
+    for (int off = 32; off > 0; off >>= 1) s[k] += __shfl_down(s[k], off, 64);
+    if ((threadIdx.x & 63) == 0) wave_sum[k][threadIdx.x >> 6] = s[k];
+  }
+  __syncthreads();
+  if (threadIdx.x == 0)
+    for (int k = 0; k < N; ++k) {
+      s[k] = 0.0;
+      for (int w = 0; w < kSumThreads / 64; ++w) s[k] += wave_sum[k][w];
+    }
+}
+
 vam_status fail(vam_status s, const char* fmt, ...);
 void clear_error();
 bool valid_handle(const vam_geometry* h);

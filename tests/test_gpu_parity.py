@@ -1006,3 +1006,38 @@ def test_c4_deposit_two_angles(c4_case, dt):
         say("c4 %s deposit angle %d: rel-L2 %.3e, max element error beyond u|ref| %.3e of max"
             % (dt, a, e2, em))
         assert e2 <= (1e-5 if dt == "f32" else 2 * u) and em <= 1e-5
+
+
+# --------------------------------------- largest values, any alignment ----
+
+@pytest.mark.parametrize("dt", ["f32", "bf16", "f16"])
+@pytest.mark.parametrize("size", [1, 5, 15])
+def test_largest_projection_value_is_found_at_any_alignment(dt, size):
+    """The deposit's scale comes from the call's largest |value|, read 16 bytes
+    at a time between the buffer's first and last 16-byte boundary.  Planes of
+    an odd number of pixels start at every alignment of their type; a NaN in
+    any of the first or last places has to reach the whole dose, and a bright
+    value there gives the dose of the oracle (1e-5, the projections as
+    stored)."""
+    tdt = {"f32": torch.float32, "bf16": torch.bfloat16, "f16": torch.float16}[dt]
+    n, na = 16, 12
+    p = dict(c2_small(n, n_pupil=4, n_angles=na), nu=size, nv=size)
+    g = gpu_geom(p)
+    og = oracle.Geometry(p)
+    rng = synth.SplitMix64(41)
+    y = torch.from_numpy(rng.uniform(na * size * size).reshape(na, size, size)).to(tdt)
+    per = size * size
+    for a0 in (0, 1, 2, 3, 5):
+        total = (na - a0) * per
+        ends = sorted({i for i in range(total) if i < 8 or i >= total - 8})
+        for i in ends:
+            bad = y.to(DEV)
+            bad[a0:].view(-1)[i] = float("nan")
+            assert torch.isnan(g.back(bad[a0:], angle_begin=a0)).all(), (a0, i)
+        for i in (0, total - 1):
+            bright = y.clone()
+            bright[a0:].view(-1)[i] = 3e4
+            check(g.back(bright.to(DEV)[a0:], angle_begin=a0).cpu().numpy(),
+                  oracle.adjoint(og, bright[a0:].double().numpy(), a0=a0, na=na - a0),
+                  what="%s, %d^2 pixels, from angle %d, bright %d" % (dt, size, a0, i))
+    g.close()
