@@ -636,7 +636,9 @@ __device__ inline float coord(float k, float d, float p, float h) {
 // (low half) and voxel x + 1 (high half), so that a sample reads its 8
 // corners as 4 words instead of 8.  Widening a BF16 or FP16 value to FP32 is
 // exact, so both layouts give the same sums.
-enum { kVolF32 = 0, kVolBF16Pairs = 1, kVolF16Pairs = 2 };
+// (Named: kernel signatures are spelled with it, and host and device number
+// unnamed types differently.)
+enum VolFormat { kVolF32 = 0, kVolBF16Pairs = 1, kVolF16Pairs = 2 };
 
 // The x-lerp of the corner pair at word o: v_x + fx (v_{x+1} - v_x), FP32.
 // FP16 halves feed the mixed-precision FMA directly (v_fma_mix_f32 widens
@@ -831,6 +833,148 @@ __global__ __launch_bounds__(256) void k_forward_box(MarchParams P, BoxParams Bp
   }
 }
 
+// ------------------------------------- forward, several angles at once ---
+//
+// Angles that are whole quarter turns apart (find_turns) share every sample's
+// position, cell and offsets; only the values under the cell differ.  One
+// workgroup takes a box at all NQ = 2 or 4 of them: the LDS holds, per cell of
+// the representative's footprint, the NQ volumes turned into its frame
+// (interleaved, staged from a copy that k_pad_turned makes), a corner is one
+// LDS read of NQ values, and the position work and the segment records are
+// paid once.  The arithmetic per angle is march_forward's, so the projections
+// are the same bits as one angle at a time.
+//
+// What bounds it: LDS reads.  A wave's read of 64 unrelated cells takes 7.6
+// clocks for 4 bytes a lane, 7.7 for 8 and 12.8 for 16 (measured; 16 bytes: 20
+// words a clock against 8.4), so wide cells move 2.4 times the words.
+
+// LDS words of a cell of NQ values, and the words as one vector.
+template <int FMT, int NQ>
+constexpr int kCellWords = FMT == kVolF32 ? NQ : NQ / 2;
+template <int WORDS>
+struct CellVec;
+template <>
+struct CellVec<1> {
+  using T = uint32_t;
+};
+template <>
+struct CellVec<2> {
+  using T = uint2;
+};
+template <>
+struct CellVec<4> {
+  using T = uint4;
+};
+
+// v_x + fx (v_{x+1} - v_x) of member q, from the words of the cells x and x + 1
+// (the arithmetic of lerp_x).
+template <int FMT, int WORDS>
+__device__ inline float lerp_member(const uint32_t (&a)[WORDS], const uint32_t (&b)[WORDS], int q, float fx) {
+  if constexpr (FMT == kVolF32) {
+    const float lo = __uint_as_float(a[q]), hi = __uint_as_float(b[q]);
+    return fmaf(fx, hi - lo, lo);
+  } else if constexpr (FMT == kVolBF16Pairs) {
+    const uint32_t wa = a[q / 2], wb = b[q / 2];
+    const float lo = __uint_as_float(q & 1 ? wa & 0xffff0000u : wa << 16);
+    const float hi = __uint_as_float(q & 1 ? wb & 0xffff0000u : wb << 16);
+    return fmaf(fx, hi - lo, lo);
+  } else {
+    const uint32_t wa = a[q / 2], wb = b[q / 2];
+    float d;
+    if (q & 1)
+      asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(wb), "v"(wa));
+    else
+      asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(wb), "v"(wa));
+    const float lo = (float)__builtin_bit_cast(_Float16, (unsigned short)(q & 1 ? wa >> 16 : wa & 0xffffu));
+    return fmaf(fx, d, lo);
+  }
+}
+
+// march_forward_cached for NQ members: S[q] is member q's Horner sum.
+template <int SY, int SZ, bool CLAMP, int FMT, int NQ>
+__device__ inline void march_forward_turned(const typename CellVec<kCellWords<FMT, NQ>>::T* sv, const SegPos& g,
+                                            float hx, float hy, float hz, float r_hi, float r_lo, float (&S)[NQ]) {
+  constexpr int WORDS = kCellWords<FMT, NQ>;
+  constexpr int off[8] = {0, 1, SY, SY + 1, SZ, SZ + 1, SZ + SY, SZ + SY + 1};
+  uint32_t w[8][WORDS] = {};
+  unsigned cur = 0xffffffffu;
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) S[q] = 0.0f;
+  for (float kf = g.k1; kf >= g.k0; kf -= 1.0f) {
+    const float x = coord<CLAMP>(kf, g.dx, g.px, hx);
+    const float y = coord<CLAMP>(kf, g.dy, g.py, hy);
+    const float z = coord<CLAMP>(kf, g.dz, g.pz, hz);
+    const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y), fz = __builtin_amdgcn_fractf(z);
+    const unsigned o = __umul24((unsigned)z, SZ) + __umul24((unsigned)y, SY) + (unsigned)x;
+    if (o != cur) {
+      cur = o;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const auto v = sv[o + off[j]];
+        __builtin_memcpy(w[j], &v, sizeof(v));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const float c00 = lerp_member<FMT, WORDS>(w[0], w[1], q, fx);
+      const float c01 = lerp_member<FMT, WORDS>(w[2], w[3], q, fx);
+      const float c10 = lerp_member<FMT, WORDS>(w[4], w[5], q, fx);
+      const float c11 = lerp_member<FMT, WORDS>(w[6], w[7], q, fx);
+      const float c0 = fmaf(fy, c01 - c00, c00);
+      const float c1 = fmaf(fy, c11 - c10, c10);
+      const float val = fmaf(fz, c1 - c0, c0);
+      S[q] = fmaf(S[q], r_hi, fmaf(S[q], r_lo, val));
+    }
+  }
+}
+
+// P.a0 + a is the representative's angle; member q of work item a goes to row
+// a + q row_stride of pfx.
+template <int FMT, int NQ, int NT, int WAVES>
+__global__ __launch_bounds__(NT, WAVES) void k_forward_turned(
+    MarchParams P, BoxParams Bp, const typename CellVec<kCellWords<FMT, NQ>>::T* __restrict__ vol,
+    unsigned long long* __restrict__ pfx, int64_t row_stride, const unsigned* __restrict__ vmax, double fx_coef) {
+  constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY, NC = SZ * Fixed<kBox>::WZ;
+  using Vec = typename CellVec<kCellWords<FMT, NQ>>::T;
+  __shared__ Vec sv[NC];
+  int b, a;
+  if (!work_item(Bp.nboxes, Bp.na, Bp.xcd, b, a)) return;
+  const unsigned vm = *vmax;
+  if (vm >= 0x7f800000u) return;  // a non-finite value: k_fx_store writes NaN
+  const double2 cs = P.cs[P.a0 + a];
+  const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
+  for (int i = threadIdx.x; i < NC; i += NT) {
+    const int z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
+    Vec v = {};
+    if (x < f.WX && y < f.WY && z < f.WZ)
+      v = vol[((int64_t)(f.Z0 + z) * Bp.py + (f.Y0 + y)) * Bp.px + (f.X0 + x)];
+    sv[i] = v;
+  }
+  __syncthreads();
+  const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
+  const float c = (float)cs.x, s = (float)cs.y, sc = P.step * c, ss = P.step * s;
+  const int s_end = Bp.box_begin[b + 1];
+  const double scale = fx_scale(vm, fx_coef);
+  unsigned long long* row = pfx + (int64_t)a * Bp.npix;
+  for (int si = Bp.box_begin[b] + (int)threadIdx.x; si < s_end; si += NT) {
+    const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
+    const SegPos g = seg_pos(pw, dn, __float_as_int(dn.w), f, c, s, sc, ss, P.step);
+    float S[NQ];
+    if (seg_inside(g, hx, hy, hz))
+      march_forward_turned<SY, SZ, false, FMT, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
+    else
+      march_forward_turned<SY, SZ, true, FMT, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
+    // the slot rank * n_rays + pupil * npix + pixel, modulo npix, is the pixel
+    unsigned long long* at = row + (unsigned)Bp.seg.idx[si] % (unsigned)Bp.npix;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const float v = pw.w * S[q];
+      if (v != 0.0f)
+        atomicAdd(at + q * row_stride * Bp.npix, (unsigned long long)__double2ll_rn((double)v * scale));
+    }
+  }
+}
+
 // Clears the fixed-point projections of a call and the volume maximum.
 __global__ void k_fx_clear(unsigned long long* __restrict__ p, int64_t n, unsigned* __restrict__ vmax) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -859,22 +1003,6 @@ __device__ inline unsigned abs_bits(uint32_t w) {
 constexpr unsigned kMaxBlocks = 512;
 static inline dim3 max_grid(int64_t n) {
   return dim3((unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 4095) / 4096, kMaxBlocks)));
-}
-
-// One atomic per block that still raises the maximum (one per wave: 8192 on
-// one address, 57 us at 68^3 and 110 us at 260^3; so 5 and 24 us).
-template <int FMT>
-__global__ __launch_bounds__(1024) void k_absmax(const uint32_t* __restrict__ v, int64_t n, unsigned* __restrict__ vmax) {
-  unsigned m = 0u;
-  const uint4* v4 = (const uint4*)v;  // the working volume's own allocation: aligned
-  const int64_t step = (int64_t)gridDim.x * blockDim.x, t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t i = t; i < n / 4; i += step) {
-    const uint4 w = v4[i];
-    m = max(max(m, max(abs_bits<FMT>(w.x), abs_bits<FMT>(w.y))), max(abs_bits<FMT>(w.z), abs_bits<FMT>(w.w)));
-  }
-  if (t < n % 4) m = max(m, abs_bits<FMT>(v[n - 1 - t]));
-  m = block_max(m);
-  if (threadIdx.x == 0) raise_max(vmax, m);
 }
 
 template <typename PT>
@@ -986,30 +1114,152 @@ static void launch_forward_box_edge(int edge, dim3 grid, hipStream_t s, const Ma
   }
 }
 
-// Caller volume -> interior of the padded working volume as 16-bit pairs:
-// word (z, y, x) holds voxel x (low half) and voxel x + 1 (high half) of the
-// padded grid, stored as given (zero in the padding).
-__global__ void k_pad_pairs(const uint16_t* __restrict__ vol, uint32_t* __restrict__ vp, int nx, int ny, int nz,
-                            int px, int py, int pz) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)px * py * pz) return;
-  const int x = (int)(i % px), y = (int)((i / px) % py), z = (int)(i / ((int64_t)px * py));
-  const int ix = x - kPad, iy = y - kPad, iz = z - kPad;
-  uint32_t lo = 0u, hi = 0u;
-  if (iy >= 0 && iy < ny && iz >= 0 && iz < nz) {
-    const int64_t row = ((int64_t)iz * ny + iy) * nx;
-    if (ix >= 0 && ix < nx) lo = vol[row + ix];
-    if (ix + 1 >= 0 && ix + 1 < nx) hi = vol[row + ix + 1];
+// Caller volume -> padded working volume of the box forward, NQ copies
+// interleaved, copy j turned by turns.q[j] quarter turns into the frame of its
+// group's representative angle (zero in the padding).  A cell holds NQ values:
+// FP32 words, or 16-bit values; alone (NQ = 1) a 16-bit value is stored as a
+// pair word with its x neighbour.  Also raises *vmax to the largest |value|
+// (FP32 bits) unless vmax is NULL.
+//
+// One workgroup per 32 x 32 tile of a slice (and every gridDim.z-th slice):
+// copies turned by an odd number of quarter turns read the volume along the
+// tile's y, so every read and write is along a row; the tile turns in LDS.
+struct Turns {
+  int q[4];
+};
+
+__device__ inline uint32_t raw_bits(float v) { return __float_as_uint(v); }
+__device__ inline uint32_t raw_bits(uint16_t v) { return v; }
+
+template <int FMT, int NQ>
+using PadCell = std::conditional_t<FMT == kVolF32 || NQ == 1, uint32_t, uint16_t>;
+
+template <int FMT, int NQ>
+__global__ __launch_bounds__(256) void k_pad_turned(
+    const std::conditional_t<FMT == kVolF32, float, uint16_t>* __restrict__ vol, PadCell<FMT, NQ>* __restrict__ out,
+    int nx, int ny, int nz, int px, int py, int pz, Turns turns, unsigned* __restrict__ vmax) {
+  constexpr int T = 32, TX = FMT != kVolF32 && NQ == 1 ? T + 1 : T;  // pairs: one more column
+  __shared__ uint32_t tile[NQ][T][T + 3];
+  const int X0 = blockIdx.x * T, Y0 = blockIdx.y * T;
+  unsigned m = 0u;
+  for (int z = blockIdx.z; z < pz; z += gridDim.z) {
+    const int iz = z - kPad;
+    for (int j = 0; j < NQ; ++j) {
+      const int turn = turns.q[j];
+      for (int i = threadIdx.x; i < T * TX; i += 256) {
+        const int lx = turn & 1 ? i / T : i % TX, ly = turn & 1 ? i % T : i / TX;
+        const int X = X0 + lx, Y = Y0 + ly;
+        const int x = turn == 0 ? X : turn == 1 ? Y : turn == 2 ? px - 1 - X : px - 1 - Y;
+        const int y = turn == 0 ? Y : turn == 1 ? py - 1 - X : turn == 2 ? py - 1 - Y : X;
+        const int ix = x - kPad, iy = y - kPad;
+        uint32_t v = 0u;
+        if (X < px && Y < py && ix >= 0 && ix < nx && iy >= 0 && iy < ny && iz >= 0 && iz < nz)
+          v = raw_bits(vol[((int64_t)iz * ny + iy) * nx + ix]);
+        tile[j][ly][lx] = v;
+        if (j == 0) m = max(m, abs_bits<FMT>(v));
+      }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < T * T; i += 256) {
+      const int lx = i % T, ly = i / T, X = X0 + lx, Y = Y0 + ly;
+      if (X >= px || Y >= py) continue;
+      const int64_t o = ((int64_t)z * py + Y) * px + X;
+      if constexpr (NQ == 1) {
+        out[o] = FMT == kVolF32 ? tile[0][ly][lx] : tile[0][ly][lx] | (tile[0][ly][lx + (TX > T)] << 16);
+      } else {
+        PadCell<FMT, NQ> v[NQ];
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) v[j] = (PadCell<FMT, NQ>)tile[j][ly][lx];
+        __builtin_memcpy(__builtin_assume_aligned(out + o * NQ, sizeof(v)), v, sizeof(v));
+      }
+    }
+    __syncthreads();
   }
-  vp[i] = lo | (hi << 16);
+  if (vmax) {
+    m = block_max(m);
+    if (threadIdx.x == 0) raise_max(vmax, m);
+  }
+}
+
+template <int NQ>
+static void pad_turned(const vam_geometry* h, const void* vol, int fmt, void* out, const Turns& t, unsigned* vmax,
+                       hipStream_t s) {
+  const vam_geometry_desc& D = h->desc;
+  const int tx = (h->px + 31) / 32, ty = (h->py + 31) / 32;
+  const dim3 grid(tx, ty, std::min(h->pz, std::max(1, 2048 / (tx * ty))));
+  switch (fmt) {
+    case kVolBF16Pairs:
+      hipLaunchKernelGGL((k_pad_turned<kVolBF16Pairs, NQ>), grid, dim3(256), 0, s, (const uint16_t*)vol,
+                         (PadCell<kVolBF16Pairs, NQ>*)out, D.nx, D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
+      break;
+    case kVolF16Pairs:
+      hipLaunchKernelGGL((k_pad_turned<kVolF16Pairs, NQ>), grid, dim3(256), 0, s, (const uint16_t*)vol,
+                         (PadCell<kVolF16Pairs, NQ>*)out, D.nx, D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
+      break;
+    default:
+      hipLaunchKernelGGL((k_pad_turned<kVolF32, NQ>), grid, dim3(256), 0, s, (const float*)vol, (uint32_t*)out, D.nx,
+                         D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
+  }
+}
+
+// A launch of the forward or of the deposit over part of a call's angles: nq
+// members per work item, n work items; the first item's representative angle
+// and its first member's row in the call; rows between members.
+struct TurnPart {
+  int nq, n, rep0, row0, row_stride;
+  Turns turns;
+};
+
+// The parts of the call's angles [a0, a0 + na): groups of members where the
+// call has them all for every representative (a whole turn; two quarters of
+// one that begin at a representative), the rest one angle at a time, in runs
+// of equal turn.  Every angle is computed in its representative's frame, so
+// how a turn is cut into calls does not change a bit.
+static std::vector<TurnPart> turn_parts(const vam_geometry* h, int a0, int na, bool groups) {
+  const int M = h->turn_members, Q = h->turn_stride, T = h->turn_quarters;
+  std::vector<TurnPart> parts;
+  int row = 0;
+  if (groups && M == 4 && na == 4 * Q) {
+    parts.push_back({4, Q, 0, 0, Q, {{0, 1, 2, 3}}});
+    row = na;
+  } else if (groups && M > 1 && na >= 2 * Q && a0 % Q == 0) {
+    const int m = a0 / Q;
+    parts.push_back({2, Q, 0, 0, Q, {{m * T, (m + 1) * T, 0, 0}}});
+    row = 2 * Q;
+  }
+  while (row < na) {
+    const int a = a0 + row, n = std::min(na - row, Q - a % Q);
+    parts.push_back({1, n, a % Q, row, 0, {{a / Q * T, 0, 0, 0}}});
+    row += n;
+  }
+  return parts;
 }
 
 // Default forward: every segment adds its partial to its pixel in 64-bit
 // fixed point (scale from the volume's largest |value|), then one pass
 // rounds the integers to the stored projections.  Variant 2 (below) writes
 // FP32 partial sums instead and adds them per pixel in a fixed order.
+template <int FMT, int NQ>
+static void launch_forward_turned(const vam_geometry* h, const MarchParams& P, const BoxParams& Bp,
+                                  unsigned long long* pfx, int64_t row_stride, double coef, hipStream_t s) {
+  using Vec = typename CellVec<kCellWords<FMT, NQ>>::T;
+  hipLaunchKernelGGL((k_forward_turned<FMT, NQ, 512, 4>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(512), 0, s, P, Bp,
+                     (const Vec*)h->vol_turn, pfx, row_stride, h->vol_absmax, coef);
+}
+
+template <int NQ>
+static void launch_forward_turned(const vam_geometry* h, int fmt, const MarchParams& P, const BoxParams& Bp,
+                                  unsigned long long* pfx, int64_t row_stride, double coef, hipStream_t s) {
+  switch (fmt) {
+    case kVolBF16Pairs: launch_forward_turned<kVolBF16Pairs, NQ>(h, P, Bp, pfx, row_stride, coef, s); break;
+    case kVolF16Pairs: launch_forward_turned<kVolF16Pairs, NQ>(h, P, Bp, pfx, row_stride, coef, s); break;
+    default: launch_forward_turned<kVolF32, NQ>(h, P, Bp, pfx, row_stride, coef, s);
+  }
+}
+
 template <typename PT>
-static vam_status forward_box_fx(vam_geometry* h, const MarchParams& P, PT* proj, int na, int fmt, hipStream_t s) {
+static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, int a0, int na, int fmt,
+                                 hipStream_t s) {
   const vam_geometry_desc& D = h->desc;
   const int64_t npix = (int64_t)D.n_u * D.n_v;
   if (!h->proj_fx) {
@@ -1017,41 +1267,64 @@ static vam_status forward_box_fx(vam_geometry* h, const MarchParams& P, PT* proj
                 "allocating the fixed-point projections");
   }
   if (!h->vol_absmax) VAM_HIP_TRY(dev_alloc((void**)&h->vol_absmax, sizeof(unsigned)), "allocating a maximum");
+  // the turned copies need the members' FP32 volumes side by side; without
+  // that memory the angles go one at a time, with the same bits
+  if (h->turn_members > 1 && !h->vol_turn && !h->vol_turn_failed &&
+      dev_alloc(&h->vol_turn, h->pad_voxels * h->turn_members * sizeof(float)) != hipSuccess) {
+    (void)hipGetLastError();  // handled here
+    h->vol_turn = nullptr;
+    h->vol_turn_failed = 1;
+  }
   unsigned long long* pfx = (unsigned long long*)h->proj_fx;
   const int64_t n = (int64_t)na * npix;
   hipLaunchKernelGGL(k_fx_clear, dim3((unsigned)std::max<int64_t>((n + 255) / 256, 1)), dim3(256), 0, s, pfx, n,
                      h->vol_absmax);
-  const uint32_t* vol = (const uint32_t*)h->vol_pad;
-  const dim3 mb = max_grid(h->pad_voxels);
-  switch (fmt) {
-    case kVolBF16Pairs:
-      hipLaunchKernelGGL(k_absmax<kVolBF16Pairs>, mb, dim3(1024), 0, s, vol, h->pad_voxels, h->vol_absmax);
-      break;
-    case kVolF16Pairs:
-      hipLaunchKernelGGL(k_absmax<kVolF16Pairs>, mb, dim3(1024), 0, s, vol, h->pad_voxels, h->vol_absmax);
-      break;
-    default: hipLaunchKernelGGL(k_absmax<kVolF32>, mb, dim3(1024), 0, s, vol, h->pad_voxels, h->vol_absmax);
-  }
   const double coef = D.step / D.n_pupil * (double)h->pix_samples_max;
-  if (h->n_boxes > 0) {
-    const BoxParams Bp = box_params(h, h->seg_fwd, na, h->xcd_forward);
-    // the loops are bound by their LDS reads (FP32) or VALU issue (16-bit
-    // pairs); keeping the cell's words in registers saves LDS reads for FP32
-    // and BF16, while FP16's mixed-precision FMA reads its word directly
-    const int mode = h->forward_lanes ? h->forward_lanes : (fmt == kVolF16Pairs ? kMarchOne : kMarchCached);
-    const FwdOut o{nullptr, 0, pfx, h->vol_absmax, coef, mode};
-    launch_forward_box_edge<true>(h->boxes.B, work_grid(h->n_boxes, na, Bp.xcd), s, P, Bp, fmt, vol, o);
+  // a chosen march mode or box edge takes one angle at a time
+  const bool groups = h->vol_turn && h->forward_lanes == 0 && h->boxes.B == kBox;
+  bool first = true;
+  for (const TurnPart& part : turn_parts(h, a0, na, groups)) {
+    unsigned* vmax = first ? h->vol_absmax : nullptr;
+    switch (part.nq) {
+      case 4: pad_turned<4>(h, volume, fmt, h->vol_turn, part.turns, vmax, s); break;
+      case 2: pad_turned<2>(h, volume, fmt, h->vol_turn, part.turns, vmax, s); break;
+      default: pad_turned<1>(h, volume, fmt, h->vol_pad, part.turns, vmax, s);
+    }
+    if (first) VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
+    first = false;
+    if (h->n_boxes == 0) continue;
+    const MarchParams P = march_params(h, part.rep0);
+    const BoxParams Bp = box_params(h, h->seg_fwd, part.n, h->xcd_forward);
+    unsigned long long* rows = pfx + part.row0 * npix;
+    if (part.nq == 4) {
+      launch_forward_turned<4>(h, fmt, P, Bp, rows, part.row_stride, coef, s);
+    } else if (part.nq == 2) {
+      launch_forward_turned<2>(h, fmt, P, Bp, rows, part.row_stride, coef, s);
+    } else {
+      // the loops are bound by their LDS reads (FP32) or VALU issue (16-bit
+      // pairs); keeping the cell's words in registers saves LDS reads for FP32
+      // and BF16, while FP16's mixed-precision FMA reads its word directly
+      const int mode = h->forward_lanes ? h->forward_lanes : (fmt == kVolF16Pairs ? kMarchOne : kMarchCached);
+      const FwdOut o{nullptr, 0, rows, h->vol_absmax, coef, mode};
+      launch_forward_box_edge<true>(h->boxes.B, work_grid(h->n_boxes, part.n, Bp.xcd), s, P, Bp, fmt,
+                                    (const uint32_t*)h->vol_pad, o);
+    }
   }
   hipLaunchKernelGGL(k_fx_store<PT>, dim3((unsigned)std::max<int64_t>((n + 255) / 256, 1)), dim3(256), 0, s, pfx,
                      proj, n, h->vol_absmax, coef);
   VAM_HIP_TRY(hipGetLastError(), "launching the fixed-point forward projector");
+  VAM_HIP_TRY(hipEventRecord(h->ev[1], s), "recording an event");
   return VAM_OK;
 }
 
 template <typename PT>
-static vam_status forward_box_t(vam_geometry* h, const MarchParams& P0, PT* proj, int na, int fmt, hipStream_t s) {
-  if (h->forward_variant != 2) return forward_box_fx(h, P0, proj, na, fmt, s);
+static vam_status forward_box_t(vam_geometry* h, const void* volume, PT* proj, int a0, int na, int fmt, hipStream_t s) {
+  if (h->forward_variant != 2) return forward_box_fx(h, volume, proj, a0, na, fmt, s);
   const vam_geometry_desc& D = h->desc;
+  pad_turned<1>(h, volume, fmt, h->vol_pad, Turns{}, nullptr, s);
+  VAM_HIP_TRY(hipGetLastError(), "launching the volume copy");
+  const MarchParams P0 = march_params(h, a0);
+  VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
   const int64_t slots = (int64_t)std::max(h->max_seg_per_ray, 1) * h->n_rays;
   if (!h->seg_part) {
     // partial sums for a chunk of angles, at most 8 GiB (fewer launch tails
@@ -1084,27 +1357,20 @@ static vam_status forward_box_t(vam_geometry* h, const MarchParams& P0, PT* proj
                        h->ray_nseg, proj + (int64_t)c0 * npix, npix, D.n_pupil, h->n_rays, slots, nc);
     VAM_HIP_TRY(hipGetLastError(), "launching the box-tiled forward projector");
   }
+  VAM_HIP_TRY(hipEventRecord(h->ev[1], s), "recording an event");
   return VAM_OK;
 }
 
-// The padded working volume for the box forward: FP32 values (from an FP32
-// caller volume) or 16-bit pairs (from a BF16 or FP16 one), in h->vol_pad.
-void pad_box_volume(vam_geometry* h, const void* vol, vam_dtype vol_t, hipStream_t s) {
-  const vam_geometry_desc& D = h->desc;
-  hipLaunchKernelGGL(k_pad_pairs, dim3((unsigned)((h->pad_voxels + 255) / 256)), dim3(256), 0, s,
-                     (const uint16_t*)vol, (uint32_t*)h->vol_pad, D.nx, D.ny, D.nz, h->px, h->py, h->pz);
-}
-
-vam_status launch_box_forward(vam_geometry* h, const MarchParams& P, void* proj, vam_dtype proj_t, vam_dtype vol_t,
+vam_status launch_box_forward(vam_geometry* h, const void* vol, vam_dtype vol_t, void* proj, vam_dtype proj_t, int a0,
                               int na, hipStream_t s) {
   if (!h->boxes_ready)
     return fail(VAM_ERR_INVALID_ARG, "the box decomposition is not available (a rebuild failed); "
                                      "set the box edge again or create a new geometry");
   const int fmt = vol_t == VAM_BF16 ? kVolBF16Pairs : vol_t == VAM_F16 ? kVolF16Pairs : kVolF32;
   switch (proj_t) {
-    case VAM_F32: return forward_box_t(h, P, (float*)proj, na, fmt, s);
-    case VAM_BF16: return forward_box_t(h, P, (uint16_t*)proj, na, fmt, s);
-    case VAM_F16: return forward_box_t(h, P, (__half*)proj, na, fmt, s);
+    case VAM_F32: return forward_box_t(h, vol, (float*)proj, a0, na, fmt, s);
+    case VAM_BF16: return forward_box_t(h, vol, (uint16_t*)proj, a0, na, fmt, s);
+    case VAM_F16: return forward_box_t(h, vol, (__half*)proj, a0, na, fmt, s);
   }
   return fail(VAM_ERR_INVALID_ARG, "unknown projection dtype");
 }

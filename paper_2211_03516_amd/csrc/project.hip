@@ -332,11 +332,14 @@ vam_status launch_forward(vam_geometry* h, const void* vol, vam_dtype vol_t, voi
   const vam_geometry_desc& D = h->desc;
   if (h->forward_variant == 1 && !v2_eligible(h))
     return fail(VAM_ERR_UNSUPPORTED, "the ray-driven forward needs a padded volume below 2^28 voxels");
+  if (h->forward_variant != 1) {
+    // pads the volume itself and records the events around its main kernels
+    vam_status st = launch_box_forward(h, vol, vol_t, proj, proj_t, a0, na, s);
+    if (st == VAM_OK) h->ev_valid[0] = 1;
+    return st;
+  }
   const unsigned vb = blocks_for(h->pad_voxels, 256);
-  // the box forward stages a BF16 / FP16 volume as 16-bit pairs
-  const bool pairs = h->forward_variant != 1 && vol_t != VAM_F32;
-  if (pairs) pad_box_volume(h, vol, vol_t, s);
-  else switch (vol_t) {
+  switch (vol_t) {
     case VAM_F32:
       hipLaunchKernelGGL(k_pad<float>, dim3(vb), dim3(256), 0, s, (const float*)vol, h->vol_pad,
                          D.nx, D.ny, D.nz, h->px, h->py, h->pz);
@@ -353,20 +356,15 @@ vam_status launch_forward(vam_geometry* h, const void* vol, vam_dtype vol_t, voi
   VAM_HIP_TRY(hipGetLastError(), "launching the volume copy");
   MarchParams P = march_params(h, a0);
   VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
-  if (h->forward_variant != 1) {
-    vam_status st = launch_box_forward(h, P, proj, proj_t, vol_t, na, s);
-    if (st != VAM_OK) return st;
-  } else {
-    dim3 grid((D.n_u + 63) / 64, (D.n_v + 3) / 4, na), block(64, 4);
-    switch (proj_t) {
-      case VAM_F32: hipLaunchKernelGGL(k_forward2<float>, grid, block, 0, s, P, h->vol_pad, (float*)proj); break;
-      case VAM_BF16:
-        hipLaunchKernelGGL(k_forward2<uint16_t>, grid, block, 0, s, P, h->vol_pad, (uint16_t*)proj);
-        break;
-      case VAM_F16: hipLaunchKernelGGL(k_forward2<__half>, grid, block, 0, s, P, h->vol_pad, (__half*)proj); break;
-    }
-    VAM_HIP_TRY(hipGetLastError(), "launching the forward projector");
+  dim3 grid((D.n_u + 63) / 64, (D.n_v + 3) / 4, na), block(64, 4);
+  switch (proj_t) {
+    case VAM_F32: hipLaunchKernelGGL(k_forward2<float>, grid, block, 0, s, P, h->vol_pad, (float*)proj); break;
+    case VAM_BF16:
+      hipLaunchKernelGGL(k_forward2<uint16_t>, grid, block, 0, s, P, h->vol_pad, (uint16_t*)proj);
+      break;
+    case VAM_F16: hipLaunchKernelGGL(k_forward2<__half>, grid, block, 0, s, P, h->vol_pad, (__half*)proj); break;
   }
+  VAM_HIP_TRY(hipGetLastError(), "launching the forward projector");
   VAM_HIP_TRY(hipEventRecord(h->ev[1], s), "recording an event");
   h->ev_valid[0] = 1;
   return VAM_OK;

@@ -289,6 +289,42 @@ static TraceParams make_params(const vam_geometry* h, const double* pupil_dev) {
   return P;
 }
 
+// Angles that are whole quarter turns apart.  Turning the volume by 90 degrees
+// moves voxel centres onto voxel centres (about the axis of a grid with
+// nx = ny; by 180 degrees about that of any grid), so a ray's samples have the
+// same fractional offsets and weights at all angles theta + k 90 degrees: the
+// box kernels compute them once for up to four angles.  Looks for the members
+// n_angles / 4 (or / 2) places apart, as in any full turn of equal steps, and
+// makes their (cos, sin) exact turns of the representative's, which they
+// are to 1e-12 (2e-10 voxel at the rim of a 512-voxel vial, far inside the FP32
+// positions' rounding).
+static void find_turns(vam_geometry* h, std::vector<double2>& cs) {
+  const int n = h->desc.n_angles;
+  h->turn_members = 1;
+  h->turn_quarters = 0;
+  h->turn_stride = n;
+  auto turned = [](double2 c, int quarters) {
+    return quarters == 1 ? make_double2(-c.y, c.x) : make_double2(-c.x, -c.y);
+  };
+  const int tries[3][2] = {{4, 1}, {2, 2}, {2, 1}};  // members, quarter turns apart
+  for (const auto& t : tries) {
+    const int members = t[0], quarters = t[1];
+    if (n % members != 0 || (quarters == 1 && h->desc.nx != h->desc.ny)) continue;
+    const int stride = n / members;
+    bool ok = true;
+    for (int a = stride; ok && a < n; ++a) {
+      const double2 want = turned(cs[a - stride], quarters);
+      ok = std::fabs(cs[a].x - want.x) <= 1e-12 && std::fabs(cs[a].y - want.y) <= 1e-12;
+    }
+    if (!ok) continue;
+    for (int a = stride; a < n; ++a) cs[a] = turned(cs[a - stride], quarters);
+    h->turn_members = members;
+    h->turn_quarters = quarters;
+    h->turn_stride = stride;
+    return;
+  }
+}
+
 static vam_status validate(const vam_geometry_desc* d) {
   if (!d) return fail(VAM_ERR_INVALID_ARG, "descriptor is NULL");
   auto bad = [](const char* what) { return fail(VAM_ERR_INVALID_ARG, "invalid descriptor: %s", what); };
@@ -335,7 +371,7 @@ static void free_handle(vam_geometry* h) {
     if (h->ev[i]) (void)hipEventDestroy(h->ev[i]);
   free_boxes(h);
   free_gather(h);
-  void* ptrs[] = {h->rays, h->ray64, h->angle_cs, h->vol_pad, h->dose_pad64,
+  void* ptrs[] = {h->rays, h->ray64, h->angle_cs, h->vol_pad, h->vol_turn, h->dose_pad64,
                   h->resid, h->grad, h->dose_tmp, h->loss_part, h->proj_fx, h->vol_absmax};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -396,6 +432,7 @@ vam_status vam_setup_geometry(const vam_geometry_desc* desc, hipStream_t stream,
   unsigned long long* count_dev = nullptr;
   std::vector<double2> cs(desc->n_angles);
   for (int a = 0; a < desc->n_angles; ++a) cs[a] = make_double2(cos(h->angles[a]), sin(h->angles[a]));
+  find_turns(h, cs);
 
 #define SETUP_TRY(expr, what)                        \
   do {                                               \

@@ -95,6 +95,13 @@ struct vam_geometry {
   double* ray64;                 // [n_rays][kRay64Fields]
   double2* angle_cs;             // [n_angles] (cos, sin)
   float* vol_pad;                // padded FP32 working volume (forward input)
+  // Angles that are whole quarter turns apart (set at setup, see find_turns):
+  // angle a = member a / turn_stride of representative a % turn_stride, each
+  // member turn_quarters quarter turns after the one before; turn_members is
+  // 1 when the angles have no such structure
+  int turn_members, turn_quarters, turn_stride;
+  void* vol_turn;                // padded volume, the members' turned copies interleaved, on first use
+  int vol_turn_failed;           // its allocation failed once: one angle at a time from then on
   double* dose_pad64;            // padded dose accumulator (+ kAccTail words), allocated on first use:
                                  // 64-bit integers (box deposit) or FP64 (ray-driven deposit)
   // optimisation buffers, allocated on first vam_optimize_step
@@ -229,10 +236,8 @@ MarchParams march_params(const vam_geometry* h, int a0);
 // rebuilds from scratch and leaves boxes_ready = 0 (and nothing allocated)
 // on failure
 vam_status build_boxes(vam_geometry* h, hipStream_t s);
-vam_status launch_box_forward(vam_geometry* h, const MarchParams& P, void* proj, vam_dtype proj_t, vam_dtype vol_t,
+vam_status launch_box_forward(vam_geometry* h, const void* vol, vam_dtype vol_t, void* proj, vam_dtype proj_t, int a0,
                               int na, hipStream_t s);
-// the box forward's padded working volume from a BF16 or FP16 volume
-void pad_box_volume(vam_geometry* h, const void* vol, vam_dtype vol_t, hipStream_t s);
 // acc: pad_voxels + kAccTail words, cleared (pad_voxels + 1 of them) by the
 // caller; the box deposit leaves the dose there as 64-bit integers at the
 // scale fx_scale(acc[pad_voxels] bits, deposit_coef(h, na))
