@@ -64,6 +64,16 @@ __device__ inline int box_of(const BoxGrid& G, double x, double y, double z) {
   return (bz * G.nby + by) * G.nbx + bx;
 }
 
+// Coordinates of a linear box number in one word (24 bits for x and y, whose
+// count follows the vial, 16 for z): the box kernels unpack them with shifts
+// instead of two divisions in every wave.
+static inline int64_t pack_box(const BoxGrid& G, int box) {
+  return (int64_t)(box % G.nbx) | (int64_t)(box / G.nbx % G.nby) << 24 | (int64_t)(box / (G.nbx * G.nby)) << 48;
+}
+__device__ inline int box_x(int64_t id) { return (int)(id & 0xffffff); }
+__device__ inline int box_y(int64_t id) { return (int)(id >> 24 & 0xffffff); }
+__device__ inline int box_z(int64_t id) { return (int)(id >> 48); }
+
 // Walk the z-clipped samples of a ray in the lab frame (FP64, sample k at
 // e + (k + 1/2) step d) and call emit(box, first k, count, rank) once per
 // maximal run of samples in one box; rank numbers the runs of a ray from 0
@@ -118,12 +128,12 @@ __global__ void k_seg_fill(BoxGrid G, const RayRec* rays, const double* ray64, i
 //   pw = (x_m - xc, y_m - yc, z_m - zb, weight), dn = (d_x, d_y, d_z, count),
 //   idx = pixel (deposit) or partial-sum slot rank * n_rays + ray (forward:
 //   lanes marching neighbouring rays write neighbouring slots).
-__global__ void k_seg_pack(BoxGrid G, const int* box_id, const int* box_begin, const int4* segs,
+__global__ void k_seg_pack(BoxGrid G, const int64_t* box_id, const int* box_begin, const int4* segs,
                            const double* ray64, int n_rays, double step, double alpha, int npix,
                            int forward, float4* pw, float4* dn, int* idx) {
   const int b = blockIdx.x;
-  const int box = box_id[b];
-  const int bx = box % G.nbx, by = (box / G.nbx) % G.nby, bz = box / (G.nbx * G.nby);
+  const int64_t box = box_id[b];
+  const int bx = box_x(box), by = box_y(box), bz = box_z(box);
   const double xc = G.x0 + (bx + 0.5) * G.B, yc = G.y0 + (by + 0.5) * G.B, zb = G.z0 + (double)bz * G.B;
   for (int i = box_begin[b] + threadIdx.x; i < box_begin[b + 1]; i += blockDim.x) {
     const int4 sg = segs[i];
@@ -163,12 +173,12 @@ __global__ void k_lab_count(const RayRec* rays, const double* ray64, int64_t n_r
 // cube: at most 2 sqrt 2 wide in x and y) always fits in such a block, so
 // at any angle the box adds at most that many samples into one LDS cell.
 // One workgroup per box.
-__global__ void k_box_supp(BoxGrid G, const int* box_id, const unsigned* count, int ncx, int ncz, int* supp) {
+__global__ void k_box_supp(BoxGrid G, const int64_t* box_id, const unsigned* count, int ncx, int ncz, int* supp) {
   __shared__ unsigned s_max;
   if (threadIdx.x == 0) s_max = 0u;
   __syncthreads();
-  const int box = box_id[blockIdx.x];
-  const int bx = box % G.nbx, by = (box / G.nbx) % G.nby, bz = box / (G.nbx * G.nby);
+  const int64_t box = box_id[blockIdx.x];
+  const int bx = box_x(box), by = box_y(box), bz = box_z(box);
   const int x0 = bx * G.B, y0 = by * G.B, z0 = bz * G.B;
   const int x1 = min(x0 + G.B, ncx), y1 = min(y0 + G.B, ncx), z1 = min(z0 + G.B, ncz);
   // window anchors (lowest cell) from 3 (x, y) or 2 (z) cells before the box
@@ -353,12 +363,13 @@ static vam_status build_boxes_into(vam_geometry* h, hipStream_t s) {
     release();
     return hip_check(e, "counting box segments");
   }
-  std::vector<int> hoff(nb_all), begin, ids;
+  std::vector<int> hoff(nb_all), begin;
+  std::vector<int64_t> ids;
   int64_t total = 0;
   for (int b = 0; b < nb_all; ++b) {
     hoff[b] = (int)std::min<int64_t>(total, 0x7fffffff);
     if (hc[b] > 0) {
-      ids.push_back(b);
+      ids.push_back(pack_box(G, b));
       begin.push_back((int)std::min<int64_t>(total, 0x7fffffff));
     }
     total += hc[b];
@@ -376,13 +387,13 @@ static vam_status build_boxes_into(vam_geometry* h, hipStream_t s) {
   }
   e = dev_alloc((void**)&segs, std::max<int64_t>(total, 1) * sizeof(int4));
   if (e == hipSuccess) e = dev_alloc((void**)&h->box_begin, begin.size() * sizeof(int));
-  if (e == hipSuccess) e = dev_alloc((void**)&h->box_id, std::max<size_t>(ids.size(), 1) * sizeof(int));
+  if (e == hipSuccess) e = dev_alloc((void**)&h->box_id, std::max<size_t>(ids.size(), 1) * sizeof(int64_t));
   if (e == hipSuccess) e = dev_alloc((void**)&h->box_supp, std::max<size_t>(ids.size(), 1) * sizeof(int));
   if (e == hipSuccess) e = hipMemcpyAsync(off, hoff.data(), nb_all * sizeof(int), hipMemcpyHostToDevice, s);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h->box_begin, begin.data(), begin.size() * sizeof(int), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && !ids.empty())
-    e = hipMemcpyAsync(h->box_id, ids.data(), ids.size() * sizeof(int), hipMemcpyHostToDevice, s);
+    e = hipMemcpyAsync(h->box_id, ids.data(), ids.size() * sizeof(int64_t), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = hipMemsetAsync(count, 0, nb_all * sizeof(int), s);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(k_seg_fill, dim3(blocks), dim3(threads), 0, s, G, h->rays, h->ray64, h->n_rays, D.step,
@@ -463,12 +474,15 @@ struct BoxParams {
   int xcd;             // work order (see work_item)
   SegTable seg;
   const int* box_begin;
-  const int* box_id;
+  const int64_t* box_id;
   const int* box_supp; // fixed-point deposit: per-box n_supp
   int wxy_max, wz_max;
   int npix;            // n_u * n_v
   int px, py, pz;
   double w_coef;       // step / n_pupil: no sample weight exceeds it times |P|
+  // one-angle forward: angle a is member a / turn_stride of representative
+  // a % turn_stride; member0's turned volume comes first, the others follow
+  int turn_stride, member0;
 };
 
 static BoxParams box_params(const vam_geometry* h, const SegTable& t, int na, int xcd) {
@@ -487,6 +501,8 @@ static BoxParams box_params(const vam_geometry* h, const SegTable& t, int na, in
   Bp.py = h->py;
   Bp.pz = h->pz;
   Bp.w_coef = h->desc.step / h->desc.n_pupil;
+  Bp.turn_stride = h->desc.n_angles;
+  Bp.member0 = 0;
   return Bp;
 }
 
@@ -499,25 +515,25 @@ static BoxParams box_params(const vam_geometry* h, const SegTable& t, int na, in
 //            are reused across A angles while at most A workgroups of one box
 //            flush into the same dose cells at a time.
 __device__ inline bool work_item(int nboxes, int na, int xcd, int& b, int& a) {
+  // the grid has fewer than 2^31 workgroups, so 32 bits hold every number here
+  const unsigned L = blockIdx.x, nb = nboxes;
   if (!xcd) {
-    const int64_t L = blockIdx.x;
-    if (L >= (int64_t)nboxes * na) return false;
-    a = (int)(L / nboxes);
-    b = (int)(L - (int64_t)a * nboxes);
+    if (L >= nb * (unsigned)na) return false;
+    a = (int)(L / nb);
+    b = (int)(L - a * nb);
     return true;
   }
-  const int A = xcd == 1 ? na : xcd;
-  const int nblk = (na + A - 1) / A;
-  const int64_t W = (int64_t)nblk * nboxes * A;
-  const int64_t per = (W + kXcds - 1) / kXcds;
-  const int64_t L = blockIdx.x;
-  const int64_t i = L / kXcds;
-  const int64_t w = (L % kXcds) * per + i;
+  const unsigned A = xcd == 1 ? na : xcd;
+  const unsigned nblk = (na + A - 1) / A;
+  const unsigned W = nblk * nb * A;
+  const unsigned per = (W + kXcds - 1) / kXcds;
+  const unsigned i = L / kXcds;
+  const unsigned w = (L % kXcds) * per + i;
   if (i >= per || w >= W) return false;
-  const int64_t blk = w / ((int64_t)nboxes * A);
-  const int64_t rem = w - blk * nboxes * A;
+  const unsigned blk = w / (nb * A);
+  const unsigned rem = w - blk * (nb * A);
   b = (int)(rem / A);
-  a = (int)(blk * A + (rem - (int64_t)b * A));
+  a = (int)(blk * A + (rem - b * A));
   return a < na;
 }
 
@@ -535,19 +551,12 @@ struct Foot {
   float cx, cy, zoff;  // box centre (x, y) and bottom face (z) in footprint cells
 };
 
-__device__ inline Foot footprint(const BoxParams& Bp, int box, double c, double s, double cx, double cy) {
+__device__ inline Foot footprint(const BoxParams& Bp, int64_t box, double c, double s, double cx, double cy) {
   const BoxGrid& G = Bp.G;
-  const int bx = box % G.nbx, by = (box / G.nbx) % G.nby, bz = box / (G.nbx * G.nby);
-  const double xa = G.x0 + bx * G.B, ya = G.y0 + by * G.B;
-  double gxmin = 1e300, gxmax = -1e300, gymin = 1e300, gymax = -1e300;
-  for (int q = 0; q < 4; ++q) {
-    const double x = xa + (q & 1) * G.B, y = ya + (q >> 1) * G.B;
-    const double gx = c * x + s * y + cx, gy = -s * x + c * y + cy;
-    gxmin = fmin(gxmin, gx);
-    gxmax = fmax(gxmax, gx);
-    gymin = fmin(gymin, gy);
-    gymax = fmax(gymax, gy);
-  }
+  const int bz = box_z(box);
+  const double xc = G.x0 + (box_x(box) + 0.5) * G.B, yc = G.y0 + (box_y(box) + 0.5) * G.B;
+  const double gx = c * xc + s * yc + cx, gy = -s * xc + c * yc + cy;  // the turned centre
+  const double half = 0.5 * G.B * (fabs(c) + fabs(s));
   // [lo, hi) clamped inside the padded grid, at least 2 and at most wmax
   // cells wide; a box outside the grid maps onto the padding at its edge
   auto range = [](double gmin, double gmax, int n, int wmax, int& lo, int& w) {
@@ -556,19 +565,23 @@ __device__ inline Foot footprint(const BoxParams& Bp, int box, double c, double 
     w = max(hi, lo + 2) - lo;
   };
   Foot f;
-  range(gxmin, gxmax, Bp.px, Bp.wxy_max, f.X0, f.WX);
-  range(gymin, gymax, Bp.py, Bp.wxy_max, f.Y0, f.WY);
+  range(gx - half, gx + half, Bp.px, Bp.wxy_max, f.X0, f.WX);
+  range(gy - half, gy + half, Bp.py, Bp.wxy_max, f.Y0, f.WY);
   // z does not turn and the boxes sit on whole cells: the box's samples have
   // z in [bz B, (bz + 1) B) up to the FP32 rounding of their positions, so
   // the footprint starts at bz B and ends one cell above the last corner
   f.Z0 = min(max(bz * G.B, 0), Bp.pz - 2);
   const int zhi = min(min((bz + 1) * G.B + 2, Bp.pz), f.Z0 + Bp.wz_max);
   f.WZ = max(zhi, f.Z0 + 2) - f.Z0;
-  const double xc = xa + 0.5 * G.B, yc = ya + 0.5 * G.B;
-  f.cx = (float)(c * xc + s * yc + cx - f.X0);
-  f.cy = (float)(-s * xc + c * yc + cy - f.Y0);
+  f.cx = (float)(gx - f.X0);
+  f.cy = (float)(gy - f.Y0);
   f.zoff = (float)(bz * G.B - f.Z0);
   return f;
+}
+
+// Number of the footprint's first cell in the padded grid.
+__device__ inline int64_t tile_base(const BoxParams& Bp, const Foot& f) {
+  return ((int64_t)f.Z0 * Bp.py + f.Y0) * Bp.px + f.X0;
 }
 
 // Middle sample and step of a segment in footprint cells at angle (c, s);
@@ -775,14 +788,27 @@ __global__ __launch_bounds__(256) void k_forward_box(MarchParams P, BoxParams Bp
   __shared__ uint32_t sv[NC];
   int b, a;
   if (!work_item(Bp.nboxes, Bp.na, Bp.xcd, b, a)) return;
-  const double2 cs = P.cs[P.a0 + a];
+  const int member = (P.a0 + a) / Bp.turn_stride;
+  const double2 cs = P.cs[P.a0 + a - member * Bp.turn_stride];
+  vol += (int64_t)(member - Bp.member0) * Bp.px * Bp.py * Bp.pz;
   const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
-  for (int i = threadIdx.x; i < NC; i += blockDim.x) {
-    const int z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
-    uint32_t v = 0u;
-    if (x < f.WX && y < f.WY && z < f.WZ)
-      v = vol[((int64_t)(f.Z0 + z) * Bp.py + (f.Y0 + y)) * Bp.px + (f.X0 + x)];
-    sv[i] = v;
+  {
+    // the tile's loads in two batches, each in flight before it is waited for
+    // (offsets inside a tile, at most 18 slices, fit 32 bits)
+    const uint32_t* tile = vol + tile_base(Bp, f);
+    constexpr int NT = 256, PER = (NC + NT - 1) / NT, HALF = (PER + 1) / 2;
+    for (int k0 = 0; k0 < PER; k0 += HALF) {
+      uint32_t v[HALF];
+#pragma unroll
+      for (int k = 0; k < HALF; ++k) {
+        const int i = (k0 + k) * NT + threadIdx.x, z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
+        v[k] = 0u;
+        if (x < f.WX && y < f.WY && z < f.WZ) v[k] = tile[(unsigned)((z * Bp.py + y) * Bp.px + x)];
+      }
+#pragma unroll
+      for (int k = 0; k < HALF; ++k)
+        if ((k0 + k) * NT + (int)threadIdx.x < NC) sv[(k0 + k) * NT + threadIdx.x] = v[k];
+    }
   }
   __syncthreads();
   const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
@@ -844,59 +870,34 @@ __global__ __launch_bounds__(256) void k_forward_box(MarchParams P, BoxParams Bp
 // paid once.  The arithmetic per angle is march_forward's, so the projections
 // are the same bits as one angle at a time.
 //
-// What bounds it: LDS reads.  A wave's read of 64 unrelated cells takes 7.6
-// clocks for 4 bytes a lane, 7.7 for 8 and 12.8 for 16 (measured; 16 bytes: 20
-// words a clock against 8.4), so wide cells move 2.4 times the words.
+// The cells hold FP32 whatever the caller's type (widening is exact): 16-bit
+// cells halve the LDS bytes but their widening costs more VALU issue than the
+// bytes do (256^3, 360 angles: 71.1 ms with FP32 cells, 91.2 with FP16 cells
+// read by mixed-precision FMAs; BF16 at 512^3 338 against 300 ms).
+//
+// Bounds: a wave's step takes 84 VALU instructions for its 4 x 64 samples (about
+// 60 % of the time at 256^3) and up to eight 16-byte reads.  A read of 64
+// unrelated cells takes 7.6 clocks for 4 bytes a lane, 7.7 for 8 and 12.8 for
+// 16 (measured: 20 words a clock against 8.4), so wide cells move 2.4 times the
+// words.  256^3, 360 angles: 71 ms against 123 one angle at a time.
 
-// LDS words of a cell of NQ values, and the words as one vector.
-template <int FMT, int NQ>
-constexpr int kCellWords = FMT == kVolF32 ? NQ : NQ / 2;
-template <int WORDS>
+template <int NQ>
 struct CellVec;
 template <>
-struct CellVec<1> {
-  using T = uint32_t;
-};
-template <>
 struct CellVec<2> {
-  using T = uint2;
+  using T = float2;
 };
 template <>
 struct CellVec<4> {
-  using T = uint4;
+  using T = float4;
 };
 
-// v_x + fx (v_{x+1} - v_x) of member q, from the words of the cells x and x + 1
-// (the arithmetic of lerp_x).
-template <int FMT, int WORDS>
-__device__ inline float lerp_member(const uint32_t (&a)[WORDS], const uint32_t (&b)[WORDS], int q, float fx) {
-  if constexpr (FMT == kVolF32) {
-    const float lo = __uint_as_float(a[q]), hi = __uint_as_float(b[q]);
-    return fmaf(fx, hi - lo, lo);
-  } else if constexpr (FMT == kVolBF16Pairs) {
-    const uint32_t wa = a[q / 2], wb = b[q / 2];
-    const float lo = __uint_as_float(q & 1 ? wa & 0xffff0000u : wa << 16);
-    const float hi = __uint_as_float(q & 1 ? wb & 0xffff0000u : wb << 16);
-    return fmaf(fx, hi - lo, lo);
-  } else {
-    const uint32_t wa = a[q / 2], wb = b[q / 2];
-    float d;
-    if (q & 1)
-      asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[1,0,1] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(wb), "v"(wa));
-    else
-      asm("v_fma_mix_f32 %0, %1, 1.0, -%2 op_sel:[0,0,0] op_sel_hi:[1,0,1]" : "=v"(d) : "v"(wb), "v"(wa));
-    const float lo = (float)__builtin_bit_cast(_Float16, (unsigned short)(q & 1 ? wa >> 16 : wa & 0xffffu));
-    return fmaf(fx, d, lo);
-  }
-}
-
 // march_forward_cached for NQ members: S[q] is member q's Horner sum.
-template <int SY, int SZ, bool CLAMP, int FMT, int NQ>
-__device__ inline void march_forward_turned(const typename CellVec<kCellWords<FMT, NQ>>::T* sv, const SegPos& g,
-                                            float hx, float hy, float hz, float r_hi, float r_lo, float (&S)[NQ]) {
-  constexpr int WORDS = kCellWords<FMT, NQ>;
+template <int SY, int SZ, bool CLAMP, int NQ>
+__device__ inline void march_forward_turned(const typename CellVec<NQ>::T* sv, const SegPos& g, float hx, float hy,
+                                            float hz, float r_hi, float r_lo, float (&S)[NQ]) {
   constexpr int off[8] = {0, 1, SY, SY + 1, SZ, SZ + 1, SZ + SY, SZ + SY + 1};
-  uint32_t w[8][WORDS] = {};
+  float w[8][NQ] = {};
   unsigned cur = 0xffffffffu;
 #pragma unroll
   for (int q = 0; q < NQ; ++q) S[q] = 0.0f;
@@ -916,10 +917,10 @@ __device__ inline void march_forward_turned(const typename CellVec<kCellWords<FM
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
-      const float c00 = lerp_member<FMT, WORDS>(w[0], w[1], q, fx);
-      const float c01 = lerp_member<FMT, WORDS>(w[2], w[3], q, fx);
-      const float c10 = lerp_member<FMT, WORDS>(w[4], w[5], q, fx);
-      const float c11 = lerp_member<FMT, WORDS>(w[6], w[7], q, fx);
+      const float c00 = fmaf(fx, w[1][q] - w[0][q], w[0][q]);
+      const float c01 = fmaf(fx, w[3][q] - w[2][q], w[2][q]);
+      const float c10 = fmaf(fx, w[5][q] - w[4][q], w[4][q]);
+      const float c11 = fmaf(fx, w[7][q] - w[6][q], w[6][q]);
       const float c0 = fmaf(fy, c01 - c00, c00);
       const float c1 = fmaf(fy, c11 - c10, c10);
       const float val = fmaf(fz, c1 - c0, c0);
@@ -928,49 +929,113 @@ __device__ inline void march_forward_turned(const typename CellVec<kCellWords<FM
   }
 }
 
-// P.a0 + a is the representative's angle; member q of work item a goes to row
-// a + q row_stride of pfx.
-template <int FMT, int NQ, int NT, int WAVES>
-__global__ __launch_bounds__(NT, WAVES) void k_forward_turned(
-    MarchParams P, BoxParams Bp, const typename CellVec<kCellWords<FMT, NQ>>::T* __restrict__ vol,
-    unsigned long long* __restrict__ pfx, int64_t row_stride, const unsigned* __restrict__ vmax, double fx_coef) {
-  constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY, NC = SZ * Fixed<kBox>::WZ;
-  using Vec = typename CellVec<kCellWords<FMT, NQ>>::T;
-  __shared__ Vec sv[NC];
+// Value of the lane whose number differs in bit BIT (0 or 1) of the quad.
+template <int BIT>
+__device__ inline unsigned long long quad_xor(unsigned long long v) {
+  constexpr int perm = BIT == 0 ? 0xB1 : 0x4E;  // lanes 1 0 3 2, or 2 3 0 1
+  const int lo = __builtin_amdgcn_mov_dpp((int)(uint32_t)v, perm, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(uint32_t)(v >> 32), perm, 0xf, 0xf, true);
+  return (unsigned long long)(uint32_t)lo | (unsigned long long)(uint32_t)hi << 32;
+}
+
+// v[j] of lane i <-> v[i] of lane j within groups of NQ = 2 or 4 lanes (all
+// lanes of the wave must be active).
+template <int NQ>
+__device__ inline void transpose_lanes(unsigned long long (&v)[NQ]) {
+  const bool b0 = threadIdx.x & 1, b1 = threadIdx.x & 2;
+#pragma unroll
+  for (int p = 0; p < NQ; p += 2) {
+    const unsigned long long got = quad_xor<0>(b0 ? v[p] : v[p + 1]);
+    v[p] = b0 ? got : v[p];
+    v[p + 1] = b0 ? v[p + 1] : got;
+  }
+  if constexpr (NQ == 4) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const unsigned long long got = quad_xor<1>(b1 ? v[p] : v[p + 2]);
+      v[p] = b1 ? got : v[p];
+      v[p + 2] = b1 ? v[p + 2] : got;
+    }
+  }
+}
+
+// Lane j's value within groups of NQ lanes.
+template <int NQ>
+__device__ inline unsigned lane_of(unsigned v, int j) {
+  if constexpr (NQ == 2)
+    return j ? __builtin_amdgcn_mov_dpp(v, 0xF5, 0xf, 0xf, true) : __builtin_amdgcn_mov_dpp(v, 0xA0, 0xf, 0xf, true);
+  return j == 0   ? __builtin_amdgcn_mov_dpp(v, 0x00, 0xf, 0xf, true)
+         : j == 1 ? __builtin_amdgcn_mov_dpp(v, 0x55, 0xf, 0xf, true)
+         : j == 2 ? __builtin_amdgcn_mov_dpp(v, 0xAA, 0xf, 0xf, true)
+                  : __builtin_amdgcn_mov_dpp(v, 0xFF, 0xf, 0xf, true);
+}
+
+// P.a0 + a is the representative's angle; the sums of work item a go to
+// pfx[a][pixel][member].  A pixel's members lie side by side, and NQ lanes
+// exchange their segments' sums first, so that the NQ lanes add to one
+// pixel's members at a time: one request of 8 NQ bytes instead of NQ of 8.
+template <int NQ, int NT>
+__global__ __launch_bounds__(NT) void k_forward_turned(
+    MarchParams P, BoxParams Bp, const typename CellVec<NQ>::T* __restrict__ vol,
+    unsigned long long* __restrict__ pfx, const unsigned* __restrict__ vmax, double fx_coef) {
+  // slice pitch two cells longer than a slice: 69.7 against 71.0 ms at 256^3
+  constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY + 2, NC = SY * SY * Fixed<kBox>::WZ;
+  using Vec = typename CellVec<NQ>::T;
+  __shared__ Vec sv[SZ * Fixed<kBox>::WZ];
   int b, a;
   if (!work_item(Bp.nboxes, Bp.na, Bp.xcd, b, a)) return;
   const unsigned vm = *vmax;
   if (vm >= 0x7f800000u) return;  // a non-finite value: k_fx_store writes NaN
   const double2 cs = P.cs[P.a0 + a];
   const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
-  for (int i = threadIdx.x; i < NC; i += NT) {
-    const int z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
-    Vec v = {};
-    if (x < f.WX && y < f.WY && z < f.WZ)
-      v = vol[((int64_t)(f.Z0 + z) * Bp.py + (f.Y0 + y)) * Bp.px + (f.X0 + x)];
-    sv[i] = v;
+  {
+    // every load of the tile in flight before the first is waited for
+    const Vec* tile = vol + tile_base(Bp, f);
+    constexpr int PER = (NC + NT - 1) / NT;
+    Vec v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      const int i = k * NT + threadIdx.x, z = i / (SY * SY), rem = i - z * (SY * SY), y = rem / SY, x = rem - y * SY;
+      v[k] = Vec{};
+      if (x < f.WX && y < f.WY && z < f.WZ) v[k] = tile[(unsigned)((z * Bp.py + y) * Bp.px + x)];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if ((k + 1) * NT <= NC || k * NT + (int)threadIdx.x < NC) {
+        const int i = k * NT + threadIdx.x, z = i / (SY * SY);
+        sv[i + z * (SZ - SY * SY)] = v[k];
+      }
   }
   __syncthreads();
   const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
   const float c = (float)cs.x, s = (float)cs.y, sc = P.step * c, ss = P.step * s;
   const int s_end = Bp.box_begin[b + 1];
   const double scale = fx_scale(vm, fx_coef);
-  unsigned long long* row = pfx + (int64_t)a * Bp.npix;
-  for (int si = Bp.box_begin[b] + (int)threadIdx.x; si < s_end; si += NT) {
-    const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
-    const SegPos g = seg_pos(pw, dn, __float_as_int(dn.w), f, c, s, sc, ss, P.step);
-    float S[NQ];
-    if (seg_inside(g, hx, hy, hz))
-      march_forward_turned<SY, SZ, false, FMT, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
-    else
-      march_forward_turned<SY, SZ, true, FMT, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
-    // the slot rank * n_rays + pupil * npix + pixel, modulo npix, is the pixel
-    unsigned long long* at = row + (unsigned)Bp.seg.idx[si] % (unsigned)Bp.npix;
+  unsigned long long* row = pfx + (int64_t)a * Bp.npix * NQ + (threadIdx.x & (NQ - 1));
+  // whole waves go round together: lanes without a segment add nothing
+  for (int s0 = Bp.box_begin[b] + (int)(threadIdx.x & ~63u); s0 < s_end; s0 += NT) {
+    const int si = s0 + (int)(threadIdx.x & 63u);
+    unsigned long long sum[NQ] = {};
+    unsigned pixel = 0u;
+    if (si < s_end) {
+      const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
+      const unsigned slot = (unsigned)Bp.seg.idx[si];  // loaded before the march, used after it
+      const SegPos g = seg_pos(pw, dn, __float_as_int(dn.w), f, c, s, sc, ss, P.step);
+      float S[NQ];
+      if (seg_inside(g, hx, hy, hz))
+        march_forward_turned<SY, SZ, false, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
+      else
+        march_forward_turned<SY, SZ, true, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
+      // the slot rank * n_rays + pupil * npix + pixel, modulo npix, is the pixel
+      pixel = slot % (unsigned)Bp.npix;
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const float v = pw.w * S[q];
-      if (v != 0.0f)
-        atomicAdd(at + q * row_stride * Bp.npix, (unsigned long long)__double2ll_rn((double)v * scale));
+      for (int q = 0; q < NQ; ++q) sum[q] = (unsigned long long)__double2ll_rn((double)(pw.w * S[q]) * scale);
+    }
+    transpose_lanes<NQ>(sum);
+#pragma unroll
+    for (int j = 0; j < NQ; ++j) {
+      const unsigned at = lane_of<NQ>(pixel, j);
+      if (sum[j] != 0) atomicAdd(row + (int64_t)at * NQ, sum[j]);
     }
   }
 }
@@ -1038,6 +1103,22 @@ __global__ void k_fx_store(const unsigned long long* __restrict__ pfx, PT* __res
   const bool finite = vm < 0x7f800000u;
   const float x = finite ? (float)((double)(long long)pfx[i] / fx_scale(vm, fx_coef)) : __uint_as_float(0x7fc00000u);
   store_proj(proj, i, x);
+}
+
+// The same for groups of NQ members: n (work item, pixel) pairs, the members of
+// a pixel side by side in pfx and member_stride values apart in proj.
+template <typename PT, int NQ>
+__global__ void k_fx_store_turned(const unsigned long long* __restrict__ pfx, PT* __restrict__ proj, int64_t n,
+                                  int64_t member_stride, const unsigned* __restrict__ vmax, double fx_coef) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const unsigned vm = *vmax;
+  const bool finite = vm < 0x7f800000u;
+  const double scale = fx_scale(vm, fx_coef);
+#pragma unroll
+  for (int q = 0; q < NQ; ++q)
+    store_proj(proj, i + q * member_stride,
+               finite ? (float)((double)(long long)pfx[i * NQ + q] / scale) : __uint_as_float(0x7fc00000u));
 }
 
 template <typename PT>
@@ -1116,9 +1197,9 @@ static void launch_forward_box_edge(int edge, dim3 grid, hipStream_t s, const Ma
 
 // Caller volume -> padded working volume of the box forward, NQ copies
 // interleaved, copy j turned by turns.q[j] quarter turns into the frame of its
-// group's representative angle (zero in the padding).  A cell holds NQ values:
-// FP32 words, or 16-bit values; alone (NQ = 1) a 16-bit value is stored as a
-// pair word with its x neighbour.  Also raises *vmax to the largest |value|
+// group's representative angle (zero in the padding).  A cell holds NQ FP32
+// words; alone (NQ = 1) a 16-bit value is stored as a pair word with its x
+// neighbour.  Also raises *vmax to the largest |value|
 // (FP32 bits) unless vmax is NULL.
 //
 // One workgroup per 32 x 32 tile of a slice (and every gridDim.z-th slice):
@@ -1128,15 +1209,18 @@ struct Turns {
   int q[4];
 };
 
-__device__ inline uint32_t raw_bits(float v) { return __float_as_uint(v); }
-__device__ inline uint32_t raw_bits(uint16_t v) { return v; }
+// A caller's value (VFMT) as stored in a cell (FMT: the same, or FP32 words).
+template <int VFMT, int FMT, typename VT>
+__device__ inline uint32_t cell_bits(VT v) {
+  if constexpr (VFMT == kVolF32) return __float_as_uint(v);
+  else if constexpr (VFMT == FMT) return v;
+  else if constexpr (VFMT == kVolBF16Pairs) return (uint32_t)v << 16;
+  else return __float_as_uint((float)__builtin_bit_cast(_Float16, v));
+}
 
-template <int FMT, int NQ>
-using PadCell = std::conditional_t<FMT == kVolF32 || NQ == 1, uint32_t, uint16_t>;
-
-template <int FMT, int NQ>
+template <int VFMT, int FMT, int NQ>
 __global__ __launch_bounds__(256) void k_pad_turned(
-    const std::conditional_t<FMT == kVolF32, float, uint16_t>* __restrict__ vol, PadCell<FMT, NQ>* __restrict__ out,
+    const std::conditional_t<VFMT == kVolF32, float, uint16_t>* __restrict__ vol, uint32_t* __restrict__ out,
     int nx, int ny, int nz, int px, int py, int pz, Turns turns, unsigned* __restrict__ vmax) {
   constexpr int T = 32, TX = FMT != kVolF32 && NQ == 1 ? T + 1 : T;  // pairs: one more column
   __shared__ uint32_t tile[NQ][T][T + 3];
@@ -1154,7 +1238,7 @@ __global__ __launch_bounds__(256) void k_pad_turned(
         const int ix = x - kPad, iy = y - kPad;
         uint32_t v = 0u;
         if (X < px && Y < py && ix >= 0 && ix < nx && iy >= 0 && iy < ny && iz >= 0 && iz < nz)
-          v = raw_bits(vol[((int64_t)iz * ny + iy) * nx + ix]);
+          v = cell_bits<VFMT, FMT>(vol[((int64_t)iz * ny + iy) * nx + ix]);
         tile[j][ly][lx] = v;
         if (j == 0) m = max(m, abs_bits<FMT>(v));
       }
@@ -1167,9 +1251,9 @@ __global__ __launch_bounds__(256) void k_pad_turned(
       if constexpr (NQ == 1) {
         out[o] = FMT == kVolF32 ? tile[0][ly][lx] : tile[0][ly][lx] | (tile[0][ly][lx + (TX > T)] << 16);
       } else {
-        PadCell<FMT, NQ> v[NQ];
+        uint32_t v[NQ];
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) v[j] = (PadCell<FMT, NQ>)tile[j][ly][lx];
+        for (int j = 0; j < NQ; ++j) v[j] = tile[j][ly][lx];
         __builtin_memcpy(__builtin_assume_aligned(out + o * NQ, sizeof(v)), v, sizeof(v));
       }
     }
@@ -1181,80 +1265,56 @@ __global__ __launch_bounds__(256) void k_pad_turned(
   }
 }
 
-template <int NQ>
-static void pad_turned(const vam_geometry* h, const void* vol, int fmt, void* out, const Turns& t, unsigned* vmax,
+template <int VFMT, int FMT, int NQ>
+static void pad_turned(const vam_geometry* h, const void* vol, void* out, const Turns& t, unsigned* vmax,
                        hipStream_t s) {
+  using VT = std::conditional_t<VFMT == kVolF32, float, uint16_t>;
   const vam_geometry_desc& D = h->desc;
   const int tx = (h->px + 31) / 32, ty = (h->py + 31) / 32;
   const dim3 grid(tx, ty, std::min(h->pz, std::max(1, 2048 / (tx * ty))));
+  hipLaunchKernelGGL((k_pad_turned<VFMT, FMT, NQ>), grid, dim3(256), 0, s, (const VT*)vol, (uint32_t*)out,
+                     D.nx, D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
+}
+
+// fmt: the caller's format.
+template <int NQ>
+static void pad_turned(const vam_geometry* h, const void* vol, int fmt, void* out, const Turns& t, unsigned* vmax,
+                       hipStream_t s) {
   switch (fmt) {
-    case kVolBF16Pairs:
-      hipLaunchKernelGGL((k_pad_turned<kVolBF16Pairs, NQ>), grid, dim3(256), 0, s, (const uint16_t*)vol,
-                         (PadCell<kVolBF16Pairs, NQ>*)out, D.nx, D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
-      break;
-    case kVolF16Pairs:
-      hipLaunchKernelGGL((k_pad_turned<kVolF16Pairs, NQ>), grid, dim3(256), 0, s, (const uint16_t*)vol,
-                         (PadCell<kVolF16Pairs, NQ>*)out, D.nx, D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
-      break;
-    default:
-      hipLaunchKernelGGL((k_pad_turned<kVolF32, NQ>), grid, dim3(256), 0, s, (const float*)vol, (uint32_t*)out, D.nx,
-                         D.ny, D.nz, h->px, h->py, h->pz, t, vmax);
+    case kVolBF16Pairs: pad_turned<kVolBF16Pairs, NQ == 1 ? kVolBF16Pairs : kVolF32, NQ>(h, vol, out, t, vmax, s); break;
+    case kVolF16Pairs: pad_turned<kVolF16Pairs, NQ == 1 ? kVolF16Pairs : kVolF32, NQ>(h, vol, out, t, vmax, s); break;
+    default: pad_turned<kVolF32, kVolF32, NQ>(h, vol, out, t, vmax, s);
   }
 }
 
-// A launch of the forward or of the deposit over part of a call's angles: nq
-// members per work item, n work items; the first item's representative angle
-// and its first member's row in the call; rows between members.
-struct TurnPart {
-  int nq, n, rep0, row0, row_stride;
-  Turns turns;
-};
-
-// The parts of the call's angles [a0, a0 + na): groups of members where the
-// call has them all for every representative (a whole turn; two quarters of
-// one that begin at a representative), the rest one angle at a time, in runs
-// of equal turn.  Every angle is computed in its representative's frame, so
-// how a turn is cut into calls does not change a bit.
-static std::vector<TurnPart> turn_parts(const vam_geometry* h, int a0, int na, bool groups) {
-  const int M = h->turn_members, Q = h->turn_stride, T = h->turn_quarters;
-  std::vector<TurnPart> parts;
-  int row = 0;
-  if (groups && M == 4 && na == 4 * Q) {
-    parts.push_back({4, Q, 0, 0, Q, {{0, 1, 2, 3}}});
-    row = na;
-  } else if (groups && M > 1 && na >= 2 * Q && a0 % Q == 0) {
-    const int m = a0 / Q;
-    parts.push_back({2, Q, 0, 0, Q, {{m * T, (m + 1) * T, 0, 0}}});
-    row = 2 * Q;
-  }
-  while (row < na) {
-    const int a = a0 + row, n = std::min(na - row, Q - a % Q);
-    parts.push_back({1, n, a % Q, row, 0, {{a / Q * T, 0, 0, 0}}});
-    row += n;
-  }
-  return parts;
+// How many members of each representative a call's angles [a0, a0 + na) are
+// taken together: 4 or 2 where the call is whole quarters of a turn (two of
+// them side by side, or two members half a turn apart), else 1.  Either way
+// every angle is computed in its representative's frame, so how a turn is cut
+// into calls does not change a bit.  (Three quarters, or a call that cuts
+// through a quarter, go one angle at a time in one launch: a pair launch and a
+// launch for the rest were 3 % slower at 179 of 180 angles of 128^3, each with
+// its own tail.)
+static int members_together(const vam_geometry* h, int a0, int na) {
+  const int M = h->turn_members, Q = h->turn_stride;
+  if (M == 1 || a0 % Q != 0) return 1;
+  return na == 4 * Q ? 4 : na == 2 * Q ? 2 : 1;
 }
 
 // Default forward: every segment adds its partial to its pixel in 64-bit
 // fixed point (scale from the volume's largest |value|), then one pass
 // rounds the integers to the stored projections.  Variant 2 (below) writes
 // FP32 partial sums instead and adds them per pixel in a fixed order.
-template <int FMT, int NQ>
-static void launch_forward_turned(const vam_geometry* h, const MarchParams& P, const BoxParams& Bp,
-                                  unsigned long long* pfx, int64_t row_stride, double coef, hipStream_t s) {
-  using Vec = typename CellVec<kCellWords<FMT, NQ>>::T;
-  hipLaunchKernelGGL((k_forward_turned<FMT, NQ, 512, 4>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(512), 0, s, P, Bp,
-                     (const Vec*)h->vol_turn, pfx, row_stride, h->vol_absmax, coef);
-}
-
+// Workgroup sizes: four angles take 81 KB of LDS, so two workgroups fit a CU
+// (256^3: 512 lanes 74.4 ms, 768 71.0, 1024 70.0; 128^3: 3.21, 3.19, 3.27);
+// two angles take 41 KB, four fit (256^3 telecentric, 90 angles: 512 lanes
+// 20.0 ms, 768 22.5, 1024 23.2).
 template <int NQ>
-static void launch_forward_turned(const vam_geometry* h, int fmt, const MarchParams& P, const BoxParams& Bp,
-                                  unsigned long long* pfx, int64_t row_stride, double coef, hipStream_t s) {
-  switch (fmt) {
-    case kVolBF16Pairs: launch_forward_turned<kVolBF16Pairs, NQ>(h, P, Bp, pfx, row_stride, coef, s); break;
-    case kVolF16Pairs: launch_forward_turned<kVolF16Pairs, NQ>(h, P, Bp, pfx, row_stride, coef, s); break;
-    default: launch_forward_turned<kVolF32, NQ>(h, P, Bp, pfx, row_stride, coef, s);
-  }
+static void launch_forward_turned(const vam_geometry* h, const MarchParams& P, const BoxParams& Bp,
+                                  unsigned long long* pfx, double coef, hipStream_t s) {
+  constexpr int NT = NQ == 4 ? 768 : 512;
+  hipLaunchKernelGGL((k_forward_turned<NQ, NT>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(NT), 0, s, P, Bp,
+                     (const typename CellVec<NQ>::T*)h->vol_turn, pfx, h->vol_absmax, coef);
 }
 
 template <typename PT>
@@ -1280,38 +1340,54 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
   hipLaunchKernelGGL(k_fx_clear, dim3((unsigned)std::max<int64_t>((n + 255) / 256, 1)), dim3(256), 0, s, pfx, n,
                      h->vol_absmax);
   const double coef = D.step / D.n_pupil * (double)h->pix_samples_max;
+  const int Q = h->turn_stride, T = h->turn_quarters, m0 = a0 / Q;
   // a chosen march mode or box edge takes one angle at a time
-  const bool groups = h->vol_turn && h->forward_lanes == 0 && h->boxes.B == kBox;
-  bool first = true;
-  for (const TurnPart& part : turn_parts(h, a0, na, groups)) {
-    unsigned* vmax = first ? h->vol_absmax : nullptr;
-    switch (part.nq) {
-      case 4: pad_turned<4>(h, volume, fmt, h->vol_turn, part.turns, vmax, s); break;
-      case 2: pad_turned<2>(h, volume, fmt, h->vol_turn, part.turns, vmax, s); break;
-      default: pad_turned<1>(h, volume, fmt, h->vol_pad, part.turns, vmax, s);
-    }
-    if (first) VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
-    first = false;
-    if (h->n_boxes == 0) continue;
-    const MarchParams P = march_params(h, part.rep0);
-    const BoxParams Bp = box_params(h, h->seg_fwd, part.n, h->xcd_forward);
-    unsigned long long* rows = pfx + part.row0 * npix;
-    if (part.nq == 4) {
-      launch_forward_turned<4>(h, fmt, P, Bp, rows, part.row_stride, coef, s);
-    } else if (part.nq == 2) {
-      launch_forward_turned<2>(h, fmt, P, Bp, rows, part.row_stride, coef, s);
+  const int nq = h->vol_turn && h->forward_lanes == 0 && h->boxes.B == kBox ? members_together(h, a0, na) : 1;
+  if (nq > 1) {
+    const Turns turns{{m0 * T, (m0 + 1) * T, (m0 + 2) * T, (m0 + 3) * T}};
+    const MarchParams P = march_params(h, 0);
+    const BoxParams Bp = box_params(h, h->seg_fwd, Q, h->xcd_forward);
+    if (nq == 4) pad_turned<4>(h, volume, fmt, h->vol_turn, turns, h->vol_absmax, s);
+    else pad_turned<2>(h, volume, fmt, h->vol_turn, turns, h->vol_absmax, s);
+    VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
+    const int64_t pairs = Q * npix;
+    const dim3 store_grid((unsigned)((pairs + 255) / 256));
+    if (nq == 4) {
+      if (h->n_boxes > 0) launch_forward_turned<4>(h, P, Bp, pfx, coef, s);
+      hipLaunchKernelGGL((k_fx_store_turned<PT, 4>), store_grid, dim3(256), 0, s, pfx, proj, pairs, pairs,
+                         h->vol_absmax, coef);
     } else {
+      if (h->n_boxes > 0) launch_forward_turned<2>(h, P, Bp, pfx, coef, s);
+      hipLaunchKernelGGL((k_fx_store_turned<PT, 2>), store_grid, dim3(256), 0, s, pfx, proj, pairs, pairs,
+                         h->vol_absmax, coef);
+    }
+  } else {
+    // one turned copy of the volume per member in the call, beside each other
+    // (in vol_turn) and one launch, or without that memory one after the other
+    const int m1 = (a0 + na - 1) / Q;
+    const bool together = m0 == m1 || h->vol_turn;
+    void* vol = m0 == m1 ? (void*)h->vol_pad : h->vol_turn;
+    for (int m = m0; m <= m1; ++m) {
+      pad_turned<1>(h, volume, fmt, together ? (uint32_t*)vol + (m - m0) * h->pad_voxels : (uint32_t*)h->vol_pad,
+                    Turns{{m * T, 0, 0, 0}}, m == m0 ? h->vol_absmax : nullptr, s);
+      if (together && m < m1) continue;
+      if (together || m == m0) VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
+      if (h->n_boxes == 0) continue;
+      const int first = together ? a0 : std::max(a0, m * Q), last = together ? a0 + na : std::min(a0 + na, (m + 1) * Q);
+      BoxParams Bp = box_params(h, h->seg_fwd, last - first, h->xcd_forward);
+      Bp.turn_stride = Q;
+      Bp.member0 = together ? m0 : m;
       // the loops are bound by their LDS reads (FP32) or VALU issue (16-bit
       // pairs); keeping the cell's words in registers saves LDS reads for FP32
       // and BF16, while FP16's mixed-precision FMA reads its word directly
       const int mode = h->forward_lanes ? h->forward_lanes : (fmt == kVolF16Pairs ? kMarchOne : kMarchCached);
-      const FwdOut o{nullptr, 0, rows, h->vol_absmax, coef, mode};
-      launch_forward_box_edge<true>(h->boxes.B, work_grid(h->n_boxes, part.n, Bp.xcd), s, P, Bp, fmt,
-                                    (const uint32_t*)h->vol_pad, o);
+      const FwdOut o{nullptr, 0, pfx + (first - a0) * npix, h->vol_absmax, coef, mode};
+      launch_forward_box_edge<true>(h->boxes.B, work_grid(h->n_boxes, Bp.na, Bp.xcd), s, march_params(h, first), Bp,
+                                    fmt, together ? (const uint32_t*)vol : (const uint32_t*)h->vol_pad, o);
     }
+    hipLaunchKernelGGL(k_fx_store<PT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pfx, proj, n,
+                       h->vol_absmax, coef);
   }
-  hipLaunchKernelGGL(k_fx_store<PT>, dim3((unsigned)std::max<int64_t>((n + 255) / 256, 1)), dim3(256), 0, s, pfx,
-                     proj, n, h->vol_absmax, coef);
   VAM_HIP_TRY(hipGetLastError(), "launching the fixed-point forward projector");
   VAM_HIP_TRY(hipEventRecord(h->ev[1], s), "recording an event");
   return VAM_OK;
@@ -1525,13 +1601,13 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
       march_deposit<SY, SZ, true>(acc, g, e, hx, hy, hz, P.r_hi, P.r_lo);
   }
   __syncthreads();
+  unsigned long long* tile = acc64 + tile_base(Bp, f);
   for (int i = threadIdx.x; i < NC; i += blockDim.x) {
     const int raw = acc[i];
     if (raw == 0) continue;
     const int z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
     if (x >= f.WX || y >= f.WY || z >= f.WZ) continue;
-    const int64_t gi = ((int64_t)(f.Z0 + z) * Bp.py + (f.Y0 + y)) * Bp.px + (f.X0 + x);
-    atomicAdd(acc64 + gi, (unsigned long long)__double2ll_rn((double)raw * toG));
+    atomicAdd(tile + (unsigned)((z * Bp.py + y) * Bp.px + x), (unsigned long long)__double2ll_rn((double)raw * toG));
   }
 }
 

@@ -136,7 +136,7 @@ struct vam_geometry {
   unsigned* vol_absmax;
   int64_t pix_samples_max;
   int* box_begin;                // [n_boxes + 1] segment offsets
-  int* box_id;                   // [n_boxes] linear box index (x fastest)
+  int64_t* box_id;               // [n_boxes] box coordinates (pack_box)
   int* box_supp;                 // [n_boxes] most samples of the box in any 4 x 4 x 3 block of lab unit cells
   int64_t supp_bound;            // most samples of all boxes in any such block: <= 8 x max box_supp
   int box_cells;                 // largest rotated-box footprint in cells (LDS)

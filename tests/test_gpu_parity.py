@@ -1041,3 +1041,59 @@ def test_largest_projection_value_is_found_at_any_alignment(dt, size):
                   oracle.adjoint(og, bright[a0:].double().numpy(), a0=a0, na=na - a0),
                   what="%s, %d^2 pixels, from angle %d, bright %d" % (dt, size, a0, i))
     g.close()
+
+
+# ------------------------------ angles that are quarter turns apart --------
+
+def _turn_cases():
+    half = [i * math.pi / 6 for i in range(6)]             # half a turn: partners 90 degrees apart
+    uneven = [0.1, 0.45, 1.3]
+    full = [a + k * math.pi / 2 for k in range(4) for a in uneven]
+    return [
+        ("four, one representative", 31, 31, 4, None),
+        ("four, odd sizes", 33, 33, 12, None),
+        ("two: 2 mod 4 angles", 40, 40, 10, None),
+        ("two: nx != ny", 29, 38, 8, None),
+        ("two, 90 degrees apart", 33, 33, 6, half),
+        ("four, uneven steps", 33, 33, 12, full),
+        ("alone: odd count", 33, 33, 7, None),
+        ("alone: 1e-6 off a quarter turn", 33, 33, 4, [0.0, math.pi / 2 + 1e-6, math.pi, 1.5 * math.pi]),
+    ]
+
+
+@pytest.mark.parametrize("what,nx,ny,na,angles", _turn_cases())
+def test_angles_a_quarter_turn_apart(what, nx, ny, na, angles):
+    """The forward takes angles that are whole quarter turns apart together.
+    Against the oracle (1e-5), and the same bits as one angle at a time (a
+    chosen march mode) and as the call cut into ranges that hold whole
+    quarters, parts of them, or cross from one to the next; every volume
+    type; and without the memory for the turned copies."""
+    p = c2_small(33, n_pupil=3, n_angles=na, nx=nx, ny=ny, nz=35, nu=37, nv=21)
+    if angles is not None:
+        p["angles"] = np.array(angles)
+    rng = synth.SplitMix64(43)
+    x = rng.uniform(35 * ny * nx).reshape(35, ny, nx) - 0.2
+    og = oracle.Geometry(p)
+    g = gpu_geom(p)
+    full = g.forward(to_dev(x))
+    poor = gpu_geom(p)
+    vam.debug_fail_allocations(3)          # projections, maximum, then the turned copies
+    try:
+        assert torch.equal(poor.forward(to_dev(x)), full)
+        assert torch.equal(poor.forward(to_dev(x), angle_begin=na // 3,
+                                        angle_count=na - na // 3), full[na // 3:])
+    finally:
+        vam.debug_fail_allocations(0)
+    poor.close()
+    for dt, tdt in (("f32", torch.float32), ("bf16", torch.bfloat16), ("f16", torch.float16)):
+        xs = torch.from_numpy(x).to(tdt)
+        xd = xs.to(DEV)
+        P = g.forward(xd)
+        check(P.cpu().numpy(), oracle.forward(og, xs.double().numpy()), what="%s, %s" % (what, dt))
+        g.set_forward_lanes(1)
+        assert torch.equal(g.forward(xd), P)
+        g.set_forward_lanes(0)
+        for a0, n in {(0, max(1, na // 2)), (na // 2, na - na // 2), (na // 4, max(1, na // 2)), (0, max(1, na - 1)),
+                      (na // 4, max(1, na // 4)), (na - 1, 1)}:
+            assert torch.equal(g.forward(xd, angle_begin=a0, angle_count=n), P[a0:a0 + n]), (a0, n)
+    g.close()
