@@ -272,19 +272,22 @@ vam_status vam_export_rays(vam_geometry_t h, double* out);
  *                   7, 8 = order 3, then each run of 1024 (7) or 2048 (8)
  *                   segments by decreasing length, 9 = by pupil sample,
  *                   then pixel column, then row, 10 = by class (u mod 3,
- *                   v mod 2), then ray, 11, 12, 13 = order 10, then each
- *                   run of 1024 (11, default), 512 (12) or 2048 (13)
- *                   segments by decreasing length, 14, 15, 16 = by ray,
+ *                   v mod 2), then ray, 11, 12, 13 = order 10, then the
+ *                   whole box (11, default) or each run of 512 (12) or
+ *                   2048 (13) segments by decreasing length, 14, 15, 16 = by ray,
  *                   then each run of 256 (14) or 1024 (15) segments, or the
  *                   whole box (16), by decreasing length in steps of two
  *                   samples; rebuilds the boxes.
- *   op 5, threads:  workgroup size of the box deposit, 256 (default) or 512.
+ *   op 5, threads:  workgroup size of the box deposit that takes one angle at
+ *                   a time, 256 (default) or 512 (512 also takes whole turns
+ *                   one angle at a time).
  *   op 7, order:    as op 4, for the forward projection (default 16).
  *   op 8, 9:        work order of the deposit (8) or forward (9) box
  *                   kernels: 0 = boxes fastest, 1 = XCD-aware with all
  *                   angles of a box on one XCD, A >= 2 = XCD-aware with the
- *                   angles of a box in blocks of A (up to 4096; default 8
- *                   for the deposit, 16 for the forward).
+ *                   angles of a box in blocks of A (up to 4096; default 4
+ *                   or 8 for the deposit, by kernel, 16 for the forward).
+ *                   Angles that the kernel takes together count as one.
  *   op 10, mode:    how the default (fixed-point) box forward marches a
  *                   segment: 1 = one lane; 2 = two lanes take alternate
  *                   samples, each summing with r^2 (their samples are half

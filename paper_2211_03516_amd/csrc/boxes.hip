@@ -76,42 +76,48 @@ __device__ inline int box_z(int64_t id) { return (int)(id >> 48); }
 
 // Walk the z-clipped samples of a ray in the lab frame (FP64, sample k at
 // e + (k + 1/2) step d) and call emit(box, first k, count, rank) once per
-// maximal run of samples in one box; rank numbers the runs of a ray from 0
-// in marching order.
-template <class F>
+// maximal run of samples in one box (SPLIT: in one box and one z cell); rank
+// numbers the runs of a ray from 0 in marching order.
+__device__ inline int z_cell(const BoxGrid& G, double z) { return min(max((int)floor(z - G.z0), 0), G.nbz * G.B - 1); }
+
+template <bool SPLIT, class F>
 __device__ inline void walk_segments(const BoxGrid& G, const RayRec& R, const double* o, double step,
                                      F emit) {
   if (R.n <= 0) return;
-  int cur = -1, start = 0, rank = 0;
+  int cur = -1, cell = 0, start = 0, rank = 0;
   for (int k = R.k0; k < R.k0 + R.n; ++k) {
     const double s = (k + 0.5) * step;
     const int b = box_of(G, o[0] + s * o[3], o[1] + s * o[4], o[2] + s * o[5]);
-    if (b != cur) {
+    const int c = SPLIT ? z_cell(G, o[2] + s * o[5]) : 0;
+    if (b != cur || c != cell) {
       if (cur >= 0) emit(cur, start, k - start, rank++);
       cur = b;
+      cell = c;
       start = k;
     }
   }
   if (cur >= 0) emit(cur, start, R.k0 + R.n - start, rank);
 }
 
+template <bool SPLIT>
 __global__ void k_seg_count(BoxGrid G, const RayRec* rays, const double* ray64, int64_t n_rays, double step,
                             int* box_count, int* ray_nseg) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_rays) return;
   int n = 0;
-  walk_segments(G, rays[r], ray64 + r * kRay64Fields, step, [&](int b, int, int, int) {
+  walk_segments<SPLIT>(G, rays[r], ray64 + r * kRay64Fields, step, [&](int b, int, int, int) {
     atomicAdd(box_count + b, 1);
     ++n;
   });
-  ray_nseg[r] = n;
+  if (ray_nseg) ray_nseg[r] = n;
 }
 
+template <bool SPLIT>
 __global__ void k_seg_fill(BoxGrid G, const RayRec* rays, const double* ray64, int64_t n_rays, double step,
                            const int* box_off, int* cursor, int4* segs) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= n_rays) return;
-  walk_segments(G, rays[r], ray64 + r * kRay64Fields, step, [&](int b, int k, int n, int rank) {
+  walk_segments<SPLIT>(G, rays[r], ray64 + r * kRay64Fields, step, [&](int b, int k, int n, int rank) {
     const int slot = box_off[b] + atomicAdd(cursor + b, 1);
     segs[slot] = make_int4((int)r, k, n, rank);
   });
@@ -125,9 +131,14 @@ __global__ void k_seg_fill(BoxGrid G, const RayRec* rays, const double* ray64, i
 // half the segment (the rounding of the direction grows with the distance
 // stepped); the weight is (T1 T2 / n_pupil) step exp(-alpha s) at the
 // segment's first sample, rounded once.
-//   pw = (x_m - xc, y_m - yc, z_m - zb, weight), dn = (d_x, d_y, d_z, count),
+//   pw = (x_m - xc, y_m - yc, z_m - zb, weight), dn = (d_x, d_y, d_z, count;
+//   deposit: plus 2^24 times the z cell of its samples in the box),
 //   idx = pixel (deposit) or partial-sum slot rank * n_rays + ray (forward:
 //   lanes marching neighbouring rays write neighbouring slots).
+constexpr int kCountBits = 24;  // a segment has fewer than 2^24 samples
+__device__ inline int seg_count(const float4& dn) { return __float_as_int(dn.w) & ((1 << kCountBits) - 1); }
+__device__ inline int seg_z_cell(const float4& dn) { return __float_as_int(dn.w) >> kCountBits; }
+
 __global__ void k_seg_pack(BoxGrid G, const int64_t* box_id, const int* box_begin, const int4* segs,
                            const double* ray64, int n_rays, double step, double alpha, int npix,
                            int forward, float4* pw, float4* dn, int* idx) {
@@ -142,7 +153,8 @@ __global__ void k_seg_pack(BoxGrid G, const int64_t* box_id, const int* box_begi
     const double sm = (sg.y + (sg.z - 1) / 2 + 0.5) * step;
     pw[i] = make_float4((float)(o[0] + sm * o[3] - xc), (float)(o[1] + sm * o[4] - yc),
                         (float)(o[2] + sm * o[5] - zb), (float)(o[8] * step * exp(-alpha * s)));
-    dn[i] = make_float4((float)o[3], (float)o[4], (float)o[5], __int_as_float(sg.z));
+    const int iz = forward ? 0 : min(max(z_cell(G, o[2] + s * o[5]) - bz * G.B, 0), G.B - 1);
+    dn[i] = make_float4((float)o[3], (float)o[4], (float)o[5], __int_as_float(sg.z | iz << kCountBits));
     idx[i] = forward ? sg.w * n_rays + sg.x : sg.x % npix;
   }
 }
@@ -232,7 +244,7 @@ static vam_status support_bound(vam_geometry* h, const BoxGrid& G, hipStream_t s
 // ------------------------------------------------------ decomposition ------
 
 static void free_table(SegTable& t) {
-  void* ptrs[] = {t.pw, t.dn, t.idx};
+  void* ptrs[] = {t.pw, t.dn, t.idx, t.box_begin};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
   t = SegTable{};
@@ -241,10 +253,9 @@ static void free_table(SegTable& t) {
 void free_boxes(vam_geometry* h) {
   free_table(h->seg_dep);
   free_table(h->seg_fwd);
-  void* ptrs[] = {h->box_begin, h->box_id, h->box_supp, h->ray_nseg, h->seg_part};
+  void* ptrs[] = {h->box_id, h->box_supp, h->ray_nseg, h->seg_part};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
-  h->box_begin = nullptr;
   h->box_id = nullptr;
   h->box_supp = nullptr;
   h->ray_nseg = nullptr;
@@ -282,8 +293,10 @@ static vam_status alloc_table(SegTable& t, int64_t n) {
 //     lanes march rays one pixel apart in z, which does not turn;
 //  10: by class (u mod 3, v mod 2), then ray (lanes three pixels apart
 //     along a row, rows two apart);
-//  11, 12, 13: order 10, then each run of 1024 (11), 512 (12) or 2048
-//     (13) consecutive segments by decreasing length;
+//  11, 12, 13: order 10, then the whole box (11) or each run of 512 (12) or
+//     2048 (13) consecutive segments by decreasing length (the plane-by-plane
+//     deposit at 256^3: runs of 512 / 1024 / 1536 / 4096 segments 129 / 118 /
+//     116 / 113 ms, the whole box 111);
 //  14, 15, 16: by ray, then each run of 256 (14) or 1024 (15) segments, or
 //     the whole box (16), by decreasing length in steps of two samples
 //     (ties keep the ray order).
@@ -306,8 +319,8 @@ static void sort_segments(std::vector<int4>& hs, const std::vector<int>& begin, 
     return r;
   };
   const int korder = (order == 7 || order == 8) ? 3 : (order >= 11 && order <= 13) ? 10 : order >= 14 ? 0 : order;
-  const int run = (order == 7 || order == 11 || order == 15) ? 1024 : (order == 8 || order == 13) ? 2048
-                : order == 12 ? 512 : order == 14 ? 256 : order == 16 ? 0x7fffffff : 0;
+  const int run = (order == 7 || order == 15) ? 1024 : (order == 8 || order == 13) ? 2048
+                : order == 12 ? 512 : order == 14 ? 256 : (order == 11 || order == 16) ? 0x7fffffff : 0;
   for (size_t i = 0; i + 1 < begin.size(); ++i) {
     std::sort(hs.begin() + begin[i], hs.begin() + begin[i + 1],
               [&](const int4& x, const int4& y) { return key(x, korder) < key(y, korder); });
@@ -315,6 +328,120 @@ static void sort_segments(std::vector<int4>& hs, const std::vector<int>& begin, 
       std::stable_sort(hs.begin() + g, hs.begin() + std::min<int64_t>(g + run, begin[i + 1]),
                        [](const int4& x, const int4& y) { return (x.z >> 1) > (y.z >> 1); });
   }
+}
+
+// One table of segments, in the order `order` inside each box, packed into
+// compact records: the forward's runs of samples in a box, or (SPLIT) the
+// deposit's, which also end where the z cell changes (z does not turn, so
+// a segment then has one z cell at every angle).  ids: the boxes that hold
+// segments (the same for both); host: the sorted segments, for the caller.
+// Synchronises the stream.
+template <bool SPLIT>
+static vam_status build_table(vam_geometry* h, const BoxGrid& G, int order, SegTable& t, std::vector<int64_t>& ids,
+                              std::vector<int4>& host, hipStream_t s) {
+  const vam_geometry_desc& D = h->desc;
+  const int nb_all = G.nbx * G.nby * G.nbz;
+  int* ray_nseg = SPLIT ? nullptr : h->ray_nseg;
+  // staging: box counts, offsets and cursors, then the unsorted segments
+  int* count = nullptr;
+  int4* segs = nullptr;
+  auto release = [&]() {
+    if (count) (void)hipFree(count);
+    if (segs) (void)hipFree(segs);
+    count = nullptr;
+    segs = nullptr;
+  };
+  hipError_t e = dev_alloc((void**)&count, 2 * (int64_t)nb_all * sizeof(int));
+  if (e != hipSuccess) return hip_check(e, "allocating box counts");
+  int* off = count + nb_all;
+  e = hipMemsetAsync(count, 0, nb_all * sizeof(int), s);
+  const int threads = 256;
+  const unsigned blocks = (unsigned)((h->n_rays + threads - 1) / threads);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_seg_count<SPLIT>, dim3(blocks), dim3(threads), 0, s, G, h->rays, h->ray64, h->n_rays, D.step,
+                       count, ray_nseg);
+    e = hipGetLastError();
+  }
+  std::vector<int> hc(nb_all), ns(SPLIT ? 0 : h->n_rays);
+  if (e == hipSuccess) e = hipMemcpyAsync(hc.data(), count, nb_all * sizeof(int), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess && !SPLIT)
+    e = hipMemcpyAsync(ns.data(), ray_nseg, h->n_rays * sizeof(int), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    release();
+    return hip_check(e, "counting box segments");
+  }
+  std::vector<int> hoff(nb_all), begin;
+  ids.clear();
+  int64_t total = 0;
+  for (int b = 0; b < nb_all; ++b) {
+    hoff[b] = (int)std::min<int64_t>(total, 0x7fffffff);
+    if (hc[b] > 0) {
+      ids.push_back(pack_box(G, b));
+      begin.push_back((int)std::min<int64_t>(total, 0x7fffffff));
+    }
+    total += hc[b];
+  }
+  begin.push_back((int)std::min<int64_t>(total, 0x7fffffff));
+  if (total >= 0x7fffffffLL) {
+    release();
+    return fail(VAM_ERR_UNSUPPORTED, "more than 2^31 ray segments");
+  }
+  if (!SPLIT) {
+    // forward partial-sum slots rank * n_rays + ray must be 32-bit offsets
+    h->max_seg_per_ray = ns.empty() ? 0 : *std::max_element(ns.begin(), ns.end());
+    if ((int64_t)h->max_seg_per_ray * h->n_rays >= 0x7fffffffLL) {
+      release();
+      return fail(VAM_ERR_UNSUPPORTED, "more than 2^31 forward partial-sum slots per angle");
+    }
+  }
+  e = dev_alloc((void**)&segs, std::max<int64_t>(total, 1) * sizeof(int4));
+  if (e == hipSuccess) e = dev_alloc((void**)&t.box_begin, begin.size() * sizeof(int));
+  if (e == hipSuccess) e = hipMemcpyAsync(off, hoff.data(), nb_all * sizeof(int), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(t.box_begin, begin.data(), begin.size() * sizeof(int), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) e = hipMemsetAsync(count, 0, nb_all * sizeof(int), s);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_seg_fill<SPLIT>, dim3(blocks), dim3(threads), 0, s, G, h->rays, h->ray64, h->n_rays, D.step,
+                       off, count, segs);
+    e = hipGetLastError();
+  }
+  host.resize(std::max<int64_t>(total, 1));
+  if (e == hipSuccess) e = hipMemcpyAsync(host.data(), segs, total * sizeof(int4), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    release();
+    return hip_check(e, "filling box segments");
+  }
+  h->n_boxes = (int)ids.size();
+  if (!h->box_id) {
+    e = dev_alloc((void**)&h->box_id, std::max<size_t>(ids.size(), 1) * sizeof(int64_t));
+    if (e == hipSuccess && !ids.empty())
+      e = hipMemcpyAsync(h->box_id, ids.data(), ids.size() * sizeof(int64_t), hipMemcpyHostToDevice, s);
+    if (e != hipSuccess) {
+      release();
+      return hip_check(e, "listing the boxes");
+    }
+  }
+  vam_status st = alloc_table(t, total);
+  if (st != VAM_OK) {
+    release();
+    return st;
+  }
+  // (the sort also makes the order independent of the scheduling of the fill
+  // kernel)
+  sort_segments(host, begin, order, D.n_u, D.n_v, D.n_pupil);
+  e = hipMemcpyAsync(segs, host.data(), total * sizeof(int4), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess && h->n_boxes > 0) {
+    hipLaunchKernelGGL(k_seg_pack, dim3((unsigned)h->n_boxes), dim3(256), 0, s, G, h->box_id, t.box_begin, segs,
+                       h->ray64, (int)h->n_rays, D.step, D.alpha, D.n_u * D.n_v, SPLIT ? 0 : 1, t.pw, t.dn, t.idx);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  release();
+  if (e != hipSuccess) return hip_check(e, "packing box segments");
+  host.resize(total);
+  return VAM_OK;
 }
 
 // Build the decomposition into the handle (everything it allocates is
@@ -332,123 +459,25 @@ static vam_status build_boxes_into(vam_geometry* h, hipStream_t s) {
   G.nby = G.nbx;
   G.nbz = (int)std::ceil((double)h->pz / G.B);
   h->boxes = G;
-  const int nb_all = G.nbx * G.nby * G.nbz;
-
   VAM_HIP_TRY(dev_alloc((void**)&h->ray_nseg, h->n_rays * sizeof(int)), "allocating segment counts");
-  // staging: box counts, offsets and cursors, then the unsorted segments
-  int* count = nullptr;
-  int4* segs = nullptr;
-  auto release = [&]() {
-    if (count) (void)hipFree(count);
-    if (segs) (void)hipFree(segs);
-    count = nullptr;
-    segs = nullptr;
-  };
-  hipError_t e = dev_alloc((void**)&count, 2 * (int64_t)nb_all * sizeof(int));
-  if (e != hipSuccess) return hip_check(e, "allocating box counts");
-  int* off = count + nb_all;
-  e = hipMemsetAsync(count, 0, nb_all * sizeof(int), s);
-  const int threads = 256;
-  const unsigned blocks = (unsigned)((h->n_rays + threads - 1) / threads);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_seg_count, dim3(blocks), dim3(threads), 0, s, G, h->rays, h->ray64, h->n_rays, D.step,
-                       count, h->ray_nseg);
-    e = hipGetLastError();
-  }
-  std::vector<int> hc(nb_all), ns(h->n_rays);
-  if (e == hipSuccess) e = hipMemcpyAsync(hc.data(), count, nb_all * sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipMemcpyAsync(ns.data(), h->ray_nseg, h->n_rays * sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    release();
-    return hip_check(e, "counting box segments");
-  }
-  std::vector<int> hoff(nb_all), begin;
   std::vector<int64_t> ids;
-  int64_t total = 0;
-  for (int b = 0; b < nb_all; ++b) {
-    hoff[b] = (int)std::min<int64_t>(total, 0x7fffffff);
-    if (hc[b] > 0) {
-      ids.push_back(pack_box(G, b));
-      begin.push_back((int)std::min<int64_t>(total, 0x7fffffff));
-    }
-    total += hc[b];
-  }
-  begin.push_back((int)std::min<int64_t>(total, 0x7fffffff));
-  if (total >= 0x7fffffffLL) {
-    release();
-    return fail(VAM_ERR_UNSUPPORTED, "more than 2^31 ray segments");
-  }
-  // forward partial-sum slots rank * n_rays + ray must be 32-bit offsets
-  h->max_seg_per_ray = ns.empty() ? 0 : *std::max_element(ns.begin(), ns.end());
-  if ((int64_t)h->max_seg_per_ray * h->n_rays >= 0x7fffffffLL) {
-    release();
-    return fail(VAM_ERR_UNSUPPORTED, "more than 2^31 forward partial-sum slots per angle");
-  }
-  e = dev_alloc((void**)&segs, std::max<int64_t>(total, 1) * sizeof(int4));
-  if (e == hipSuccess) e = dev_alloc((void**)&h->box_begin, begin.size() * sizeof(int));
-  if (e == hipSuccess) e = dev_alloc((void**)&h->box_id, std::max<size_t>(ids.size(), 1) * sizeof(int64_t));
-  if (e == hipSuccess) e = dev_alloc((void**)&h->box_supp, std::max<size_t>(ids.size(), 1) * sizeof(int));
-  if (e == hipSuccess) e = hipMemcpyAsync(off, hoff.data(), nb_all * sizeof(int), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(h->box_begin, begin.data(), begin.size() * sizeof(int), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess && !ids.empty())
-    e = hipMemcpyAsync(h->box_id, ids.data(), ids.size() * sizeof(int64_t), hipMemcpyHostToDevice, s);
-  if (e == hipSuccess) e = hipMemsetAsync(count, 0, nb_all * sizeof(int), s);
-  if (e == hipSuccess) {
-    hipLaunchKernelGGL(k_seg_fill, dim3(blocks), dim3(threads), 0, s, G, h->rays, h->ray64, h->n_rays, D.step,
-                       off, count, segs);
-    e = hipGetLastError();
-  }
-  std::vector<int4> hs(std::max<int64_t>(total, 1));
-  if (e == hipSuccess) e = hipMemcpyAsync(hs.data(), segs, total * sizeof(int4), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
-  if (e != hipSuccess) {
-    release();
-    return hip_check(e, "filling box segments");
-  }
-  h->n_boxes = (int)ids.size();
-  h->n_segments = total;
+  std::vector<int4> hs;
+  vam_status st = build_table<false>(h, G, h->seg_order_fwd, h->seg_fwd, ids, hs, s);
+  if (st != VAM_OK) return st;
+  h->n_segments = (int64_t)hs.size();
   {
     // the most samples of one pixel over all its rays (bounds the
     // fixed-point forward's sums)
     const int npix = D.n_u * D.n_v;
     std::vector<int64_t> per(npix, 0);
-    for (int64_t i = 0; i < total; ++i) per[hs[i].x % npix] += hs[i].z;
+    for (const int4& sg : hs) per[sg.x % npix] += sg.z;
     h->pix_samples_max = per.empty() ? 0 : *std::max_element(per.begin(), per.end());
   }
-  {
-    vam_status st = support_bound(h, G, s);
-    if (st != VAM_OK) {
-      release();
-      return st;
-    }
-  }
-  // both orders, each packed into compact records (the sort also makes the
-  // order independent of the scheduling of the fill kernel)
-  const int npix = D.n_u * D.n_v;
-  for (int fwd = 0; fwd < 2; ++fwd) {
-    SegTable& t = fwd ? h->seg_fwd : h->seg_dep;
-    vam_status st = alloc_table(t, total);
-    if (st != VAM_OK) {
-      release();
-      return st;
-    }
-    sort_segments(hs, begin, fwd ? h->seg_order_fwd : h->seg_order, D.n_u, D.n_v, D.n_pupil);
-    e = hipMemcpyAsync(segs, hs.data(), total * sizeof(int4), hipMemcpyHostToDevice, s);
-    if (e == hipSuccess && h->n_boxes > 0) {
-      hipLaunchKernelGGL(k_seg_pack, dim3((unsigned)h->n_boxes), dim3(256), 0, s, G, h->box_id, h->box_begin, segs,
-                         h->ray64, (int)h->n_rays, D.step, D.alpha, npix, fwd, t.pw, t.dn, t.idx);
-      e = hipGetLastError();
-    }
-    // the host copy is re-sorted next: wait for the upload
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) {
-      release();
-      return hip_check(e, "packing box segments");
-    }
-  }
-  release();
+  st = build_table<true>(h, G, h->seg_order, h->seg_dep, ids, hs, s);
+  if (st != VAM_OK) return st;
+  VAM_HIP_TRY(dev_alloc((void**)&h->box_supp, std::max(h->n_boxes, 1) * sizeof(int)), "allocating support bounds");
+  st = support_bound(h, G, s);
+  if (st != VAM_OK) return st;
   int wxy, wz;
   footprint_bound(G.B, h->px, h->py, h->pz, wxy, wz);
   h->box_cells = wxy * wxy * wz;
@@ -492,7 +521,7 @@ static BoxParams box_params(const vam_geometry* h, const SegTable& t, int na, in
   Bp.na = na;
   Bp.xcd = xcd;
   Bp.seg = t;
-  Bp.box_begin = h->box_begin;
+  Bp.box_begin = t.box_begin;
   Bp.box_id = h->box_id;
   Bp.box_supp = h->box_supp;
   footprint_bound(h->boxes.B, h->px, h->py, h->pz, Bp.wxy_max, Bp.wz_max);
@@ -1492,6 +1521,9 @@ __device__ inline float load_p<__half>(const __half* p, int64_t i) {
   return __half2float(p[i]);
 }
 
+// v clamped to [0, 1] (free as an instruction modifier).
+__device__ inline float unit(float v) { return __builtin_amdgcn_fmed3f(v, 0.0f, 1.0f); }
+
 // Round to the nearest integer, halves upwards (one v_cvt_rpi_i32_f32).
 __device__ inline int round_to_int(float v) {
   int r;
@@ -1512,27 +1544,26 @@ __device__ inline void flush8(int* acc, unsigned cur, const float* w) {
   atomicAdd(p + SZ + SY + 1, round_to_int(w[7]));
 }
 
+// zc: the segment's z cell in the footprint (one for all its samples).
 template <int SY, int SZ, bool CLAMP>
-__device__ inline void march_deposit(int* acc, const SegPos& g, float e, float hx, float hy, float hz,
-                                     float r_hi, float r_lo) {
-  auto cell_bytes = [](float x, float y, float z) {
-    return __umul24((unsigned)z, SZ * 4) + __umul24((unsigned)y, SY * 4) + (unsigned)x * 4;
-  };
+__device__ inline void march_deposit(int* acc, const SegPos& g, int zc, float e, float hx, float hy, float r_hi,
+                                     float r_lo) {
+  auto cell_bytes = [](float x, float y) { return __umul24((unsigned)y, SY * 4) + (unsigned)x * 4; };
+  acc += zc * SZ;
+  const float pz = g.pz - (float)zc;
   float w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   // byte offset of the cell whose corners w holds, starting at the first
   // sample's (w is zero until its first add)
-  unsigned cur = cell_bytes(coord<CLAMP>(g.k0, g.dx, g.px, hx), coord<CLAMP>(g.k0, g.dy, g.py, hy),
-                            coord<CLAMP>(g.k0, g.dz, g.pz, hz));
+  unsigned cur = cell_bytes(coord<CLAMP>(g.k0, g.dx, g.px, hx), coord<CLAMP>(g.k0, g.dy, g.py, hy));
   // exact: a segment has fewer than 2^24 samples
   for (float kf = g.k0; kf <= g.k1; kf += 1.0f) {
     const float x = coord<CLAMP>(kf, g.dx, g.px, hx);
     const float y = coord<CLAMP>(kf, g.dy, g.py, hy);
-    const float z = coord<CLAMP>(kf, g.dz, g.pz, hz);
-    const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y), fz = __builtin_amdgcn_fractf(z);
+    const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y), fz = unit(fmaf(kf, g.dz, pz));
     const float z1 = e * fz, z0 = e - z1;
     const float y01 = z0 * fy, y00 = z0 - y01;
     const float y11 = z1 * fy, y10 = z1 - y11;
-    const unsigned ob = cell_bytes(x, y, z);
+    const unsigned ob = cell_bytes(x, y);
     const bool fl = ob != cur;
     if (fl) flush8<SY, SZ>(acc, cur, w);
     const float keep = fl ? 0.0f : 1.0f;
@@ -1593,12 +1624,13 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
     const float pv = load_p(proj, pbase + Bp.seg.idx[si]);
     if (pv == 0.0f) continue;
     const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
-    const SegPos g = seg_pos(pw, dn, __float_as_int(dn.w), f, c, s, sc, ss, P.step);
+    const SegPos g = seg_pos(pw, dn, seg_count(dn), f, c, s, sc, ss, P.step);
     const float e = pw.w * pv * S;  // sample weights in the fixed-point units
+    const int zc = min(max(seg_z_cell(dn) + (int)f.zoff, 0), f.WZ - 2);
     if (seg_inside(g, hx, hy, hz))
-      march_deposit<SY, SZ, false>(acc, g, e, hx, hy, hz, P.r_hi, P.r_lo);
+      march_deposit<SY, SZ, false>(acc, g, zc, e, hx, hy, P.r_hi, P.r_lo);
     else
-      march_deposit<SY, SZ, true>(acc, g, e, hx, hy, hz, P.r_hi, P.r_lo);
+      march_deposit<SY, SZ, true>(acc, g, zc, e, hx, hy, P.r_hi, P.r_lo);
   }
   __syncthreads();
   unsigned long long* tile = acc64 + tile_base(Bp, f);
@@ -1608,6 +1640,252 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
     const int z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
     if (x >= f.WX || y >= f.WY || z >= f.WZ) continue;
     atomicAdd(tile + (unsigned)((z * Bp.py + y) * Bp.px + x), (unsigned long long)__double2ll_rn((double)raw * toG));
+  }
+}
+
+// ------------------------------------------------ deposit, plane by plane --
+//
+// The deposit of four angles that are whole quarter turns apart (find_turns).
+//
+// What bounds a deposit that adds a run's 8 corners whenever a lane's cell
+// changes (k_back_box): the LDS adds.  A wave's ds_add_u32 takes 4.3 clocks
+// however few of its lanes are active, 7.8 with 64 unrelated ones; at 256^3
+// each step of a wave issues 8 of them with 37 active lanes, 41 clocks of the
+// 43 that a step takes.  So here the lanes add together and less often:
+//
+//  * A lane walks its segment along the axis (x or y) that it advances along
+//    fastest, plane by plane.  All samples between planes j and j + 1 go
+//    into registers: sums for the columns of plane j (started by the samples
+//    before it) and of plane j + 1.  Then the whole wave adds plane j to LDS
+//    and moves on.  A corner that several cells share is added once, and a
+//    step covers 1 / |advance| >= 2 samples at the usual half-voxel spacing.
+//  * The other axis and the direction are mirrored so that both coordinates
+//    grow.  Between two planes the cross coordinate grows by less than one
+//    cell, so a plane receives at most four columns, from the cell of its
+//    first sample on.  Columns are kept as sums of clamp(u - i) over the
+//    samples (u from the base column): the tent weights are their
+//    differences, exactly zero in columns that no sample reached, which are
+//    not added (so no add leaves the footprint).
+//  * z does not turn: the deposit's segments end where their z cell changes,
+//    so a segment has two z corners throughout.
+//  * The four angles share all of it: the sums are free of the projection
+//    value, and the members' sums of a corner leave as two 64-bit adds
+//    (ds_add_u64: 12.8 clocks for 64 lanes, 6.4 a member), each the exact
+//    integer hi 2^32 + lo of two members' 32-bit sums, whose bound is
+//    k_back_box's: a corner gets at most one add per sample of its support.
+//
+// 256^3, 360 angles: 110.9 ms against 181.0 corner by corner (91.7 against
+// 118.0 on projections dark outside a part's shadow); 128^3, 180 angles, 8
+// pupil points 4.50 against 6.49; one pupil point 4.40 against 4.55 (there the
+// adds into the voxels bind, the same for both).  Without its LDS adds and
+// their conversions it takes 82 ms, without the adds into the voxels 105: the
+// adds and the vector work both bind, and neither hides the other fully.
+// Two members, or one, per workgroup measured (128^3: 90 angles in pairs 3.01
+// against 3.30 corner by corner, but 23.4 against 21.0 at 256^3 telecentric
+// on dark-edged projections, and one angle 2.30 against 1.79): per member the
+// vector work then grows past what the adds save, so those go corner by corner.
+
+// Largest value of the wave.
+__device__ inline float wave_max(float m) {
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+  return m;
+}
+
+constexpr int kTurns = 4;  // members of a work item
+
+// Adds a corner's sums t f[q] of the members, rounded, at element `at`.
+template <int PLANE>
+__device__ inline void add_members(unsigned long long* acc, int at, float t, const float (&f)[kTurns]) {
+#pragma unroll
+  for (int p = 0; p < kTurns; p += 2) {
+    const int lo = round_to_int(t * f[p]), hi = round_to_int(t * f[p + 1]) + (lo >> 31);
+    atomicAdd(acc + p / 2 * PLANE + at, (unsigned long long)(uint32_t)lo | (unsigned long long)(uint32_t)hi << 32);
+  }
+}
+
+// One segment.  m, c: main and cross coordinate of its middle sample, dm >= dc
+// >= 0 their steps; element(m, c) = base + m sm + c sc is the footprint's
+// corner in the lower z slice of the segment's cell.
+template <int SZ, int PLANE, bool CLAMP>
+__device__ inline void march_planes(unsigned long long* acc, float k0, float k1, float pm, float dm, float hm, float pc, float dc,
+                                    float hc, float pz, float dz, int base, int sm, int sc, float e,
+                                    const float (&f)[kTurns], float r_hi, float r_lo) {
+  float A[2][4] = {}, B[2][3] = {};  // [z][column sums] of the planes jf and jf + 1
+  float kf = k0;
+  float m = coord<CLAMP>(kf, dm, pm, hm);
+  float jf = floorf(m);
+  float bB = floorf(coord<CLAMP>(kf, dc, pc, hc)), bA = bB;
+  bool last = false;
+  for (;;) {
+    const float end = jf + 1.0f;
+    while (kf <= k1 && !(m >= end)) {
+      const float c = coord<CLAMP>(kf, dc, pc, hc);
+      const float fz = unit(fmaf(kf, dz, pz)), fm = unit(m - jf);
+      const float a1 = unit(c - bA), a2 = unit(c - (bA + 1.0f)), a3 = unit(c - (bA + 2.0f));
+      const float b1 = unit(c - bB), b2 = unit(c - (bB + 1.0f));
+      const float e1 = e * fz, ez[2] = {e - e1, e1};
+#pragma unroll
+      for (int z = 0; z < 2; ++z) {
+        const float wb = ez[z] * fm, wa = ez[z] - wb;
+        A[z][0] += wa;
+        A[z][1] = fmaf(wa, a1, A[z][1]);
+        A[z][2] = fmaf(wa, a2, A[z][2]);
+        A[z][3] = fmaf(wa, a3, A[z][3]);
+        B[z][0] += wb;
+        B[z][1] = fmaf(wb, b1, B[z][1]);
+        B[z][2] = fmaf(wb, b2, B[z][2]);
+      }
+      e = fmaf(e, r_hi, e * r_lo);
+      kf += 1.0f;
+      m = coord<CLAMP>(kf, dm, pm, hm);
+    }
+    int at = base + (int)jf * sm + (int)bA * sc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float t0 = i < 3 ? A[0][i] - A[0][i + 1] : A[0][3], t1 = i < 3 ? A[1][i] - A[1][i + 1] : A[1][3];
+      if (fabsf(t0) + fabsf(t1) != 0.0f) {
+        add_members<PLANE>(acc, at, t0, f);
+        add_members<PLANE>(acc, at + SZ, t1, f);
+      }
+      at += sc;
+    }
+    if (last) break;
+    last = !(kf <= k1);
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        A[z][i] = B[z][i];
+        B[z][i] = 0.0f;
+      }
+      A[z][3] = 0.0f;
+    }
+    jf = end;
+    bA = bB;
+    bB = floorf(coord<CLAMP>(kf, dc, pc, hc));
+  }
+}
+
+// Work item (b, a): the box at the members of representative angle a: rows a,
+// a + member_rows, ... of proj, member q turned by q quarter turns.  acc64, pmax, dep_coef: as for k_back_box.
+template <typename PT, int NT>
+__global__ __launch_bounds__(NT) void k_back_planes(MarchParams P, BoxParams Bp, const PT* __restrict__ proj,
+                                                    int64_t member_rows,
+                                                    unsigned long long* __restrict__ acc64,
+                                                    const unsigned* __restrict__ pmax, double dep_coef) {
+  constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY + 1, PLANE = SZ * Fixed<kBox>::WZ;
+  constexpr int NQ = kTurns, NC = PLANE * (NQ / 2);
+  __shared__ unsigned long long acc[NC];
+  __shared__ unsigned s_pvmax[NQ];
+  int b, a;
+  if (!work_item(Bp.nboxes, Bp.na, Bp.xcd, b, a)) return;
+  const unsigned pm_bits = *pmax;
+  if (pm_bits >= 0x7f800000u) return;  // a non-finite projection value: the dose is NaN
+  const double G = fx_scale(pm_bits, dep_coef);
+  const double2 cs = P.cs[a];
+  const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
+  for (int i = threadIdx.x; i < NC; i += NT) acc[i] = 0;
+  if (threadIdx.x < NQ) s_pvmax[threadIdx.x] = 0u;
+  __syncthreads();
+  const PT* rows[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) rows[q] = proj + (a + q * member_rows) * Bp.npix;
+  const int s_begin = Bp.box_begin[b], s_end = Bp.box_begin[b + 1];
+  // the box's largest |projection value| of each member sets its scale
+  {
+    float mx[NQ] = {};
+    for (int si = s_begin + (int)threadIdx.x; si < s_end; si += NT) {
+      const int pix = Bp.seg.idx[si];
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) mx[q] = fmaxf(mx[q], fabsf(load_p(rows[q], pix)));
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const float w = wave_max(mx[q]);
+      if ((threadIdx.x & 63) == 0) atomicMax(&s_pvmax[q], __float_as_uint(w));  // non-negative floats order as their bits
+    }
+  }
+  __syncthreads();
+  const int nb = Bp.box_supp[b];
+  float S[NQ];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const double bound = (double)nb * Bp.w_coef * (double)__uint_as_float(s_pvmax[q]);
+    // capped below FP32's largest value (a smaller S only rounds coarser)
+    S[q] = bound > 0.0 ? (float)fmin((2147483648.0 - nb - 4096.0) * (1.0 - 1.0 / 4096.0) / bound, 3.0e38) : 1.0f;
+  }
+  const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
+  const float c = (float)cs.x, s = (float)cs.y, sc = P.step * c, ss = P.step * s;
+  // (the next round's pixel is loaded a round ahead: its projection values
+  // wait for it)
+  int next = s_begin + (int)threadIdx.x < s_end ? Bp.seg.idx[s_begin + (int)threadIdx.x] : 0;
+  for (int si = s_begin + (int)threadIdx.x; si < s_end; si += NT) {
+    const int pix = next;
+    if (si + NT < s_end) next = Bp.seg.idx[si + NT];
+    float v[NQ];
+    bool lit = false;
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const float pv = load_p(rows[q], pix);
+      lit |= pv != 0.0f;
+      v[q] = pv * S[q];  // sample weights in the fixed-point units
+    }
+    if (!lit) continue;
+    const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
+    const SegPos g = seg_pos(pw, dn, seg_count(dn), f, c, s, sc, ss, P.step);
+    // main axis, and both axes mirrored to grow along the segment
+    const bool x_main = fabsf(g.dx) > fabsf(g.dy);
+    float m = x_main ? g.px : g.py, dm = x_main ? g.dx : g.dy, u = x_main ? g.py : g.px, du = x_main ? g.dy : g.dx;
+    const int wm = x_main ? f.WX : f.WY, wu = x_main ? f.WY : f.WX;
+    int sm = x_main ? 1 : SY, su = x_main ? SY : 1;
+    const int iz = min(max(seg_z_cell(dn) + (int)f.zoff, 0), f.WZ - 2);
+    int base = iz * SZ;
+    if (dm < 0.0f) {
+      m = (float)(wm - 1) - m;
+      dm = -dm;
+      base += (wm - 1) * sm;
+      sm = -sm;
+    }
+    if (du < 0.0f) {
+      u = (float)(wu - 1) - u;
+      du = -du;
+      base += (wu - 1) * su;
+      su = -su;
+    }
+    const float z = g.pz - (float)iz;
+    if (seg_inside(g, hx, hy, hz))
+      march_planes<SZ, PLANE, false>(acc, g.k0, g.k1, m, dm, 0.0f, u, du, 0.0f, z, g.dz, base, sm, su, pw.w, v,
+                                         P.r_hi, P.r_lo);
+    else
+      march_planes<SZ, PLANE, true>(acc, g.k0, g.k1, m, dm, (float)wm - 1.001f, u, du, (float)wu - 1.001f, z, g.dz,
+                                        base, sm, su, pw.w, v, P.r_hi, P.r_lo);
+  }
+  __syncthreads();
+  // each touched cell to its voxel, members turned back; an odd number of
+  // quarter turns is read along y, which is the volume's x then
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const double toG = G / (double)S[q];
+    // volume voxel of footprint cell (x, y, z): tile[z pz + y py + x px]
+    const int64_t X = f.X0, Y = f.Y0;
+    int64_t first;
+    int px, py;
+    if (q == 0) { first = Y * Bp.px + X; px = 1; py = Bp.px; }
+    else if (q == 1) { first = (Bp.py - 1 - X) * Bp.px + Y; px = -Bp.px; py = 1; }
+    else if (q == 2) { first = (Bp.py - 1 - Y) * Bp.px + (Bp.px - 1 - X); px = -1; py = -Bp.px; }
+    else { first = X * Bp.px + (Bp.px - 1 - Y); px = Bp.px; py = -1; }
+    unsigned long long* tile = acc64 + (int64_t)f.Z0 * Bp.py * Bp.px + first;
+    for (int i = threadIdx.x; i < SY * SY * Fixed<kBox>::WZ; i += NT) {
+      const int z = i / (SY * SY), rem = i - z * (SY * SY), hi = rem / SY, lo = rem - hi * SY;
+      const int x = q & 1 ? hi : lo, y = q & 1 ? lo : hi;
+      const unsigned long long w = acc[q / 2 * PLANE + z * SZ + y * SY + x];
+      int raw = (int)(uint32_t)w;
+      if (q & 1) raw = (int)(((long long)w - (long long)raw) >> 32);
+      if (raw == 0) continue;
+      if (x >= f.WX || y >= f.WY || z >= f.WZ) continue;
+      atomicAdd(tile + ((int64_t)z * Bp.py * Bp.px + y * py + x * px),
+                (unsigned long long)__double2ll_rn((double)raw * toG));
+    }
   }
 }
 
@@ -1648,10 +1926,15 @@ double deposit_coef(const vam_geometry* h, int na) {
   return (double)na * (double)std::max<int64_t>(h->supp_bound, 1) * h->desc.step / h->desc.n_pupil;
 }
 
+// Work order of the deposit where none was chosen: angles in blocks of 8, or of
+// 4 representatives (256^3: blocks of 4 / 8 / 16 representatives 117.9 / 120.1 /
+// 120.3 ms; one angle at a time, 45 of 360: blocks of 4 / 8 25.3 / 25.0).
+static int deposit_order(const vam_geometry* h, int blocks) { return h->xcd_deposit >= 0 ? h->xcd_deposit : blocks; }
+
 template <int B, typename PT>
 static void launch_back_box(vam_geometry* h, const MarchParams& P, const PT* proj, int na, double* acc,
                             hipStream_t s) {
-  const BoxParams Bp = box_params(h, h->seg_dep, na, h->xcd_deposit);
+  const BoxParams Bp = box_params(h, h->seg_dep, na, deposit_order(h, 8));
   const dim3 grid = work_grid(h->n_boxes, na, Bp.xcd);
   unsigned long long* a64 = (unsigned long long*)acc;
   const unsigned* pm = (const unsigned*)(acc + h->pad_voxels);
@@ -1668,6 +1951,19 @@ static void launch_back_box_t(vam_geometry* h, const MarchParams& P, const PT* p
   // the largest |projection value| first (its slot was cleared with acc)
   const int64_t n = (int64_t)na * h->desc.n_u * h->desc.n_v;
   hipLaunchKernelGGL(k_proj_absmax<PT>, max_grid(n), dim3(1024), 0, s, proj, n, (unsigned*)(acc + h->pad_voxels));
+  // plane by plane for whole turns of quarter-turn angles where no plane
+  // between two samples is skipped (and at the default edge and workgroup
+  // size); else corner by corner
+  if (h->boxes.B == kBox && h->desc.step <= 0.99 && h->deposit_threads == 256 && members_together(h, P.a0, na) == 4) {
+    // two workgroups fit a CU's LDS: 24 waves at 77 registers (256^3: 512 lanes
+    // 141 ms, 768 120; 1024 need 64 registers to fit twice, 170 in one)
+    constexpr int NT = 768;
+    const BoxParams Bp = box_params(h, h->seg_dep, h->turn_stride, deposit_order(h, 4));
+    hipLaunchKernelGGL((k_back_planes<PT, NT>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(NT), 0, s, P, Bp, proj,
+                       (int64_t)h->turn_stride, (unsigned long long*)acc, (const unsigned*)(acc + h->pad_voxels),
+                       deposit_coef(h, na));
+    return;
+  }
   switch (h->boxes.B) {
     case 8: launch_back_box<8, PT>(h, P, proj, na, acc, s); break;
     case 12: launch_back_box<12, PT>(h, P, proj, na, acc, s); break;

@@ -402,10 +402,10 @@ vam_status vam_setup_geometry(const vam_geometry_desc* desc, hipStream_t stream,
   h->magic = kMagic;
   h->desc = *desc;
   h->adjoint_variant = 0;
-  h->seg_order = 11;  // pixel classes (u mod 3, v mod 2), length-sorted runs (fastest measured)
+  h->seg_order = 11;  // pixel classes (u mod 3, v mod 2), then by length (fastest measured)
   h->seg_order_fwd = 16;  // ray order, then the box by length in steps of two samples (fastest measured)
   h->deposit_threads = 256;
-  h->xcd_deposit = 8;  // XCD-aware deposit order, angles in blocks of 8 (fastest measured)
+  h->xcd_deposit = -1;  // XCD-aware deposit order, block size by kernel (deposit_order)
   h->xcd_forward = 16;  // the same for the forward, in blocks of 16: its segment records come from the XCD's L2
   h->forward_lanes = 0;  // by volume format: cached cell words for FP32 and BF16, one lane for FP16 (fastest measured)
   h->angles.resize(desc->n_angles);

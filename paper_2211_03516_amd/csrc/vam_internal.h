@@ -51,13 +51,14 @@ struct BoxGrid {
 // per segment, grouped by box): pw = first sample's lab position relative to
 // its box (x, y from the box centre, z from its bottom face) and that
 // sample's weight (T1 T2 / n_pupil) step exp(-alpha s); dn = lab direction
-// and the sample count (int bits); idx = pixel (deposit order) or
+// and the sample count (int bits; deposit: with the z cell above them); idx = pixel (deposit order) or
 // partial-sum slot rank * n_rays + ray (forward order).  36 bytes per
 // segment.
 struct SegTable {
   float4* pw = nullptr;
   float4* dn = nullptr;
   int* idx = nullptr;
+  int* box_begin = nullptr;  // [n_boxes + 1] offsets of the boxes' segments
 };
 
 // Per-launch constants of the marching kernels.
@@ -118,7 +119,7 @@ struct vam_geometry {
   int seg_order;                 // deposit order of segments inside a box (see sort_segments)
   int seg_order_fwd;             // forward order of segments inside a box
   int deposit_threads;           // workgroup size of the box deposit (256 or 512)
-  int xcd_forward, xcd_deposit;  // work order of the box kernels (see work_item)
+  int xcd_forward, xcd_deposit;  // work order of the box kernels (see work_item; deposit: -1 = by kernel)
   vam::BoxGrid boxes;
   int boxes_ready;               // 1 once the decomposition is complete; 0 after a failed rebuild
   int n_boxes;                   // boxes holding at least one segment
@@ -135,7 +136,6 @@ struct vam_geometry {
   int64_t* proj_fx;
   unsigned* vol_absmax;
   int64_t pix_samples_max;
-  int* box_begin;                // [n_boxes + 1] segment offsets
   int64_t* box_id;               // [n_boxes] box coordinates (pack_box)
   int* box_supp;                 // [n_boxes] most samples of the box in any 4 x 4 x 3 block of lab unit cells
   int64_t supp_bound;            // most samples of all boxes in any such block: <= 8 x max box_supp

@@ -1097,3 +1097,46 @@ def test_angles_a_quarter_turn_apart(what, nx, ny, na, angles):
                       (na // 4, max(1, na // 4)), (na - 1, 1)}:
             assert torch.equal(g.forward(xd, angle_begin=a0, angle_count=n), P[a0:a0 + n]), (a0, n)
     g.close()
+
+
+@pytest.mark.parametrize("what,na,kw", [
+    ("one representative", 4, {}),
+    ("default step", 12, {}),
+    ("steps of 0.1", 8, {"step": 0.1}),
+    ("the largest step taken plane by plane", 8, {"step": 0.99}),
+    ("corner by corner above it", 8, {"step": 1.0}),
+    ("vial wider than the grid", 8, {"r_outer": 25.0, "r_inner": 22.0}),
+    ("steep rays", 8, {"projector": 0, "focus": 0.0, "pupil": 0.9, "r_outer": 16.0, "r_inner": 16.0}),
+    ("chief rays on the lattice", 4, {"projector": 0, "focus": 0.0, "pupil": 0.0, "r_outer": 16.0, "r_inner": 16.0}),
+])
+def test_deposit_of_whole_turns(what, na, kw):
+    """The deposit takes four angles a quarter turn apart together, plane by
+    plane along each segment's faster axis.  Against the oracle (1e-5) with
+    dense, signed and mostly dark projections in every storage type, through
+    both entry points, accumulating, and the same bits on every call; and
+    against one angle at a time (a chosen workgroup size), whose sums differ
+    in FP32 roundings of the weights only."""
+    n = 35
+    p = c2_small(n, n_pupil=3, n_angles=na, nx=n, ny=n, nz=29, nu=37, nv=21, **kw)
+    og = oracle.Geometry(p)
+    g = gpu_geom(p)
+    rng = synth.SplitMix64(47)
+    y = rng.uniform(na * 21 * 37).reshape(na, 21, 37)
+    dark = y * (rng.uniform(na * 21 * 37).reshape(na, 21, 37) < 0.2)
+    for name, yy in (("dense", y), ("signed", y - 0.5), ("dark", dark)):
+        for dt, tdt in (("f32", torch.float32), ("bf16", torch.bfloat16), ("f16", torch.float16)):
+            ys = torch.from_numpy(yy).to(tdt)
+            D = g.back(ys.to(DEV))
+            ref = oracle.adjoint(og, ys.double().numpy())
+            check(D.cpu().numpy(), ref, what="%s, %s, %s" % (what, name, dt))
+            assert torch.equal(D, g.back(ys.to(DEV)))
+    yd = to_dev(y - 0.5)
+    D = g.back(yd)
+    g.set_deposit_threads(512)
+    one = g.back(yd)
+    g.set_deposit_threads(256)
+    check(one.cpu().numpy(), D.double().cpu().numpy(), tol=2e-6, what="%s, one angle at a time" % what)
+    acc = torch.ones_like(D)
+    g.back(yd, out=acc, accumulate=True)
+    check(acc.cpu().numpy(), (D.double() + 1.0).cpu().numpy(), tol=1e-6, what="%s, accumulated" % what)
+    g.close()
