@@ -18,7 +18,10 @@
 // global memory to LDS.
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
+#include <new>
+#include <thread>
 #include <type_traits>
 
 #include "vam_internal.h"
@@ -268,6 +271,7 @@ void free_boxes(vam_geometry* h) {
 }
 
 static vam_status alloc_table(SegTable& t, int64_t n) {
+  t.n = n;
   const int64_t m = std::max<int64_t>(n, 1);
   VAM_HIP_TRY(dev_alloc((void**)&t.pw, m * sizeof(float4)), "allocating segment records");
   VAM_HIP_TRY(dev_alloc((void**)&t.dn, m * sizeof(float4)), "allocating segment records");
@@ -300,8 +304,13 @@ static vam_status alloc_table(SegTable& t, int64_t n) {
 //  14, 15, 16: by ray, then each run of 256 (14) or 1024 (15) segments, or
 //     the whole box (16), by decreasing length in steps of two samples
 //     (ties keep the ray order).
-static void sort_segments(std::vector<int4>& hs, const std::vector<int>& begin, int order, int nu, int nv,
-                          int np) {
+//
+// Segments of one ray in one box (the deposit's, cut at z cells) follow in
+// marching order, so that the order never depends on the fill kernel's
+// scheduling.  Boxes are sorted by up to 16 threads, with each key formed
+// once (256^3, two tables: 4.0 s a geometry on one thread, now 0.47).  False if host memory ran
+// out.
+static bool sort_segments(std::vector<int4>& hs, const std::vector<int>& begin, int order, int nu, int nv, int np) {
   auto key = [&](const int4& s, int ord) -> int64_t {
     const int r = s.x;
     const int u = r % nu, v = (r / nu) % nv;
@@ -321,13 +330,47 @@ static void sort_segments(std::vector<int4>& hs, const std::vector<int>& begin, 
   const int korder = (order == 7 || order == 8) ? 3 : (order >= 11 && order <= 13) ? 10 : order >= 14 ? 0 : order;
   const int run = (order == 7 || order == 15) ? 1024 : (order == 8 || order == 13) ? 2048
                 : order == 12 ? 512 : order == 14 ? 256 : (order == 11 || order == 16) ? 0x7fffffff : 0;
-  for (size_t i = 0; i + 1 < begin.size(); ++i) {
-    std::sort(hs.begin() + begin[i], hs.begin() + begin[i + 1],
-              [&](const int4& x, const int4& y) { return key(x, korder) < key(y, korder); });
-    for (int64_t g = begin[i]; run && g < begin[i + 1]; g += run)
-      std::stable_sort(hs.begin() + g, hs.begin() + std::min<int64_t>(g + run, begin[i + 1]),
-                       [](const int4& x, const int4& y) { return (x.z >> 1) > (y.z >> 1); });
+  struct Item {
+    int64_t key;
+    int4 seg;
+  };
+  auto by_key = [](const Item& x, const Item& y) { return x.key != y.key ? x.key < y.key : x.seg.y < y.seg.y; };
+  auto by_length = [&](const Item& x, const Item& y) {
+    const int lx = x.seg.z >> 1, ly = y.seg.z >> 1;
+    return lx != ly ? lx > ly : by_key(x, y);
+  };
+  const size_t n_boxes = begin.size() - 1;
+  std::atomic<size_t> next{0};
+  std::atomic<bool> ok{true};
+  auto work = [&]() {
+    try {
+      std::vector<Item> items;
+      for (size_t i = next++; ok && i < n_boxes; i = next++) {
+        items.resize(begin[i + 1] - begin[i]);
+        for (size_t k = 0; k < items.size(); ++k) items[k] = {key(hs[begin[i] + k], korder), hs[begin[i] + k]};
+        if (run == 0x7fffffff) {
+          std::sort(items.begin(), items.end(), by_length);
+        } else {
+          std::sort(items.begin(), items.end(), by_key);
+          for (size_t g = 0; run && g < items.size(); g += run)
+            std::sort(items.begin() + g, items.begin() + std::min(g + run, items.size()), by_length);
+        }
+        for (size_t k = 0; k < items.size(); ++k) hs[begin[i] + k] = items[k].seg;
+      }
+    } catch (const std::bad_alloc&) {
+      ok = false;
+    }
+  };
+  // a thread that cannot be started leaves its boxes to the others
+  std::vector<std::thread> threads;
+  const unsigned n_threads = std::min({16u, std::thread::hardware_concurrency(), (unsigned)(n_boxes / 8 + 1)});
+  try {
+    for (unsigned t = 1; t < n_threads; ++t) threads.emplace_back(work);
+  } catch (const std::exception&) {
   }
+  work();
+  for (std::thread& t : threads) t.join();
+  return ok;
 }
 
 // One table of segments, in the order `order` inside each box, packed into
@@ -430,7 +473,10 @@ static vam_status build_table(vam_geometry* h, const BoxGrid& G, int order, SegT
   }
   // (the sort also makes the order independent of the scheduling of the fill
   // kernel)
-  sort_segments(host, begin, order, D.n_u, D.n_v, D.n_pupil);
+  if (!sort_segments(host, begin, order, D.n_u, D.n_v, D.n_pupil)) {
+    release();
+    return fail(VAM_ERR_OUT_OF_MEMORY, "sorting the box segments: out of host memory");
+  }
   e = hipMemcpyAsync(segs, host.data(), total * sizeof(int4), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && h->n_boxes > 0) {
     hipLaunchKernelGGL(k_seg_pack, dim3((unsigned)h->n_boxes), dim3(256), 0, s, G, h->box_id, t.box_begin, segs,
@@ -1952,9 +1998,14 @@ static void launch_back_box_t(vam_geometry* h, const MarchParams& P, const PT* p
   const int64_t n = (int64_t)na * h->desc.n_u * h->desc.n_v;
   hipLaunchKernelGGL(k_proj_absmax<PT>, max_grid(n), dim3(1024), 0, s, proj, n, (unsigned*)(acc + h->pad_voxels));
   // plane by plane for whole turns of quarter-turn angles where no plane
-  // between two samples is skipped (and at the default edge and workgroup
-  // size); else corner by corner
-  if (h->boxes.B == kBox && h->desc.step <= 0.99 && h->deposit_threads == 256 && members_together(h, P.a0, na) == 4) {
+  // between two samples is skipped and the boxes hold enough segments to fill
+  // its workgroups (and at the default edge and workgroup size); else corner
+  // by corner.  128^3, 180 angles, planes / corners: 1 pupil point (150 segments
+  // a box) 4.39 / 4.36 ms, 2 points 4.96 / 5.12, 4 points (650) 5.05 / 5.27; on
+  // dark-edged projections 2.98 / 2.72, 3.35 / 3.31, 3.90 / 3.63, with a thin
+  // lens 1.93 / 1.90, 2.13 / 2.10, 2.48 / 2.65; 64^3, 1 point 0.64 / 0.60.
+  if (h->boxes.B == kBox && h->desc.step <= 0.99 && h->deposit_threads == 256 &&
+      h->seg_dep.n >= 500 * (int64_t)h->n_boxes && members_together(h, P.a0, na) == 4) {
     // two workgroups fit a CU's LDS: 24 waves at 77 registers (256^3: 512 lanes
     // 141 ms, 768 120; 1024 need 64 registers to fit twice, 170 in one)
     constexpr int NT = 768;

@@ -59,6 +59,7 @@ struct SegTable {
   float4* dn = nullptr;
   int* idx = nullptr;
   int* box_begin = nullptr;  // [n_boxes + 1] offsets of the boxes' segments
+  int64_t n = 0;
 };
 
 // Per-launch constants of the marching kernels.

@@ -1117,7 +1117,7 @@ def test_deposit_of_whole_turns(what, na, kw):
     against one angle at a time (a chosen workgroup size), whose sums differ
     in FP32 roundings of the weights only."""
     n = 35
-    p = c2_small(n, n_pupil=3, n_angles=na, nx=n, ny=n, nz=29, nu=37, nv=21, **kw)
+    p = c2_small(n, n_pupil=12, n_angles=na, nx=n, ny=n, nz=29, nu=37, nv=21, **kw)  # over 500 segments a box
     og = oracle.Geometry(p)
     g = gpu_geom(p)
     rng = synth.SplitMix64(47)
