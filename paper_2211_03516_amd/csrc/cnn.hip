@@ -5,17 +5,14 @@
 //   forward          z[p][co]     = sum_kc col(a)[p][kc]   W[co][kc]
 //   data gradient    da[p][ci]    = sum_kc col(g)[p][kc]   Wflip[ci][kc]
 //   weight gradient  dW^T[kc][co] = sum_p  col(a)[p][kc]   g[p][co]
-// Every GEMM gathers its col tiles straight from the NHWC activations (or
-// gradients) while staging them in LDS: no im2col matrix is written to
-// memory.  The weight gradient stages both operands transposed (pixels
-// along k).
 // with p a pixel of the batch, kc = (tap, channel) and Wflip the kernel
 // turned by 180 degrees with input and output channels swapped (the
 // transposed convolution as a convolution).  Activations are NHWC BF16 with
-// channels padded to a multiple of 8; K of every GEMM is padded to the
-// 32-element k-tile with zeros.  The weight-gradient GEMM splits its pixel
-// sum over workgroups into FP32 partials that a second kernel adds in a
-// fixed order, so training is deterministic.
+// channels padded to a multiple of 8.  No im2col matrix is written to memory:
+// a workgroup stages an image tile with its one-pixel border in LDS once and
+// reads it at the nine shifts.  The weight gradient's workgroups each add
+// up their tiles, and a second kernel adds their FP32 sums in a fixed order,
+// so training is deterministic.
 
 #include <algorithm>
 #include <cmath>
@@ -33,8 +30,9 @@ typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 constexpr uint64_t kCnnMagic = 0x56414d434e4e3031ull;  // "VAMCNN01"
-constexpr int BM = 128, BN = 64, BK = 32, LDK = BK + 8;
-constexpr int kMaxSplits = 256;
+constexpr int kMaxChannels = 64;
+constexpr int BK = 32;          // rows of packed weights are padded to multiples of this
+constexpr int kMaxSplits = 256;  // workgroups of a weight gradient: one a CU
 
 __device__ inline uint16_t f2bf(float f) {  // round to nearest even
   uint32_t u = __float_as_uint(f);
@@ -44,173 +42,315 @@ __device__ inline uint16_t f2bf(float f) {  // round to nearest even
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ inline bool bf_positive(uint16_t h) { return h != 0 && !(h & 0x8000u); }
 
-enum Epi { EPI_RELU_BF16 = 0, EPI_BIAS_F32 = 1, EPI_MASK_BF16 = 2, EPI_PART_F32 = 3 };
+enum Epi { EPI_RELU_BF16 = 0, EPI_OUT_F32 = 1, EPI_MASK_BF16 = 2 };
 
-struct GemmArgs {
-  const uint16_t* B;   // !CONVT: [N][ldb] (B^T rows: the packed weights)
-  int M, N, K;         // K per split (multiple of BK)
-  int ldb;
-  void* C;
-  int ldc;
-  int64_t split_stride;      // EPI_PART_F32: elements between split partials
-  const float* bias;         // EPI_RELU_BF16, EPI_BIAS_F32
-  const uint16_t* mask;      // EPI_MASK_BF16: [M][ldm]
-  int ldm;
-  const uint16_t* X;         // !CONVT: A = col(X), X NHWC [M pixels][cp]; CONVT: A = col(X)^T
-  int H, W, cp;              // image size, padded channels of X
-  const uint16_t* G;         // CONVT: B = G^T, G NHWC [pixels][cpg]
-  int cpg;
-  int ones_row;              // CONVT: A row of ones (the bias gradient's column sums)
+struct ConvArgs {
+  const uint16_t* X;       // NHWC [pixels][CP]
+  int H, W;                // image size
+  int tiles_x, tiles_y, tiles;  // 16 x 16 tiles of an image, and of the batch
+  const uint16_t* B;       // packed weights [rows][ldb]
+  int rows, ldb;           // output channels (padded), row length
+  void* C;                 // BF16 [pixels][rows], or FP32 [pixels] (EPI_OUT_F32)
+  const float* bias;       // EPI_RELU_BF16, EPI_OUT_F32
+  const uint16_t* mask;    // EPI_MASK_BF16: BF16 [pixels][rows]
+  const float* x;          // EPI_OUT_F32: network input [n][2][H][W], or NULL for z itself
+  float s1;
 };
 
-// Transposed staging (CONVT) of 8 rows x 2 pixels: fetch_t loads the
-// 8-channel chunk `c` of pixels k0 + pp and k0 + pp + 1 of `src` (channels
-// per pixel `cp`) shifted by (dy, dx), zero where `ok` is false or the
-// shifted pixel leaves the image; store_t writes element j of both as one
-// 32-bit word at tile[(8 rc + j) LDK + pp].
-__device__ inline void fetch_t(uint4 (&v)[2], const uint16_t* src, int64_t k0, int pp, int cp, int c, int dy, int dx,
-                               bool ok, int H, int W) {
+constexpr int kTile = 16, kTileP = kTile + 2;  // tile edge, with its border
+
+// Element offset, in a staged tile of `pitch` elements a pixel, of the k-th
+// entry of a pixel's im2col row of CP channels a tap.
+template <int CP, int PITCH>
+constexpr int col_offset(int k) {
+  const int tap = k / CP, c = k % CP;
+  return (tap / 3 * kTileP + tap % 3) * PITCH + c;
+}
+
+// out = epilogue(sum_k W[co][k] col(X)[p][k]) for 16 x 16 pixel tiles, eight
+// waves per workgroup, NB blocks of 32 output channels.
+//
+// What bounds it: at 64 channels a layer moves 2 x 33 MB a batch of 16 x 128^2
+// (13 us at the rate of a large copy) and needs 16 us of matrix work at the
+// rate of a large product, so both have to overlap and neither may be repeated.
+//  * A workgroup keeps its waves' share of the packed weights in registers (a
+//    wave has one block of 32 channels: 144 registers at 64 channels) and goes
+//    over tiles, so the weights are read once per workgroup.
+//  * A tile with its border is staged once (18 x 18 pixels) and read at nine
+//    shifts: every LDS address is one base plus a constant.  Pixels lie an odd
+//    number of 16-byte units apart, so 16 lanes read 16 different bank groups.
+//  * The next tile's loads are issued before the current tile's products and
+//    written to the other LDS buffer after them: one barrier a tile.
+//  * Weights are the MFMA's first operand and pixels its second, so a lane
+//    holds four neighbouring channels of one pixel: 8-byte stores.
+// The products of an output are added in ascending k, 16 at a time, from
+// zero: the same bits as any other tiling of that order.
+template <int CP, int NB, int EPI>
+__global__ __launch_bounds__(512) void k_conv(ConvArgs g) {
+  constexpr int U = CP / 8, PITCH = (U | 1) * 8, PIX = kTileP * kTileP;
+  constexpr int KS = (9 * CP + 15) / 16, CHUNKS = PIX * U, PER = (CHUNKS + 511) / 512;
+  constexpr int MB = NB == 2 ? 2 : 1;  // 32-pixel blocks (two tile rows) of a wave
+  __shared__ __attribute__((aligned(16))) uint16_t tile[2][PIX * PITCH];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
+  const int nb = NB == 2 ? wave & 1 : 0, mg = NB == 2 ? wave >> 1 : wave;
+  bf16x8 w[KS];
+  {
+    const int co = nb * 32 + (lane & 31);
 #pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    v[e] = make_uint4(0, 0, 0, 0);
-    const int p = (int)k0 + pp + e;  // pixel indices fit 31 bits (checked at creation)
-    if (ok) {
-      const int x = p % W, y = (p / W) % H;
-      if (y + dy >= 0 && y + dy < H && x + dx >= 0 && x + dx < W)
-        v[e] = *(const uint4*)(src + ((int64_t)p + dy * W + dx) * cp + c);
+    for (int s = 0; s < KS; ++s) {
+      w[s] = bf16x8{};
+      if (co < g.rows) w[s] = *(const bf16x8*)(g.B + (int64_t)co * g.ldb + 16 * s + 8 * half);
     }
   }
-}
-
-__device__ inline void store_t(uint16_t* tile, int rc, int pp, const uint4 (&v)[2]) {
-  const uint32_t w0[4] = {v[0].x, v[0].y, v[0].z, v[0].w}, w1[4] = {v[1].x, v[1].y, v[1].z, v[1].w};
+  // lane's pixel in block b: tile row 2 (mg MB + b) + (lane / 16) % 2, column lane % 16.
+  // The upper half of the wave takes the second 8 of a step's 16 entries:
+  // the next channels, the next tap, or the next row of taps.
+  const int row0 = 2 * mg * MB + ((lane >> 4) & 1), col = lane & 15;
+  const int base = (row0 * kTileP + col) * PITCH;
+  const int at_chan = base + half * 8, at_tap = base + half * (PITCH - (CP - 8)),
+            at_row = base + half * ((kTileP - 2) * PITCH - (CP - 8));
+  constexpr int BATCH = (PER + 1) / 2;
+  uint4 r[BATCH];
+  auto origin = [&](int t, int& img, int& y0, int& x0) {
+    img = t / (g.tiles_x * g.tiles_y);
+    const int rest = t - img * (g.tiles_x * g.tiles_y), ty = rest / g.tiles_x;
+    y0 = ty * kTile;
+    x0 = (rest - ty * g.tiles_x) * kTile;
+  };
+  auto fetch = [&](int t, int batch) {
+    int img, y0, x0;
+    origin(t, img, y0, x0);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    *(uint32_t*)(tile + (8 * rc + 2 * q) * LDK + pp) = (w0[q] & 0xffffu) | (w1[q] << 16);
-    *(uint32_t*)(tile + (8 * rc + 2 * q + 1) * LDK + pp) = (w0[q] >> 16) | (w1[q] & 0xffff0000u);
-  }
-}
-
-// C = epilogue(sum_k A(m, k) B(k, n)), 128 x 64 output tile per workgroup,
-// four waves of 32 rows x 64 columns (two 32 x 32 MFMA blocks each).  In
-// the !CONVT GEMMs the next k-tile's global loads are issued into registers
-// before the current tile's MFMAs and written to LDS after them (10 %
-// faster); the CONVT GEMM stages each tile just before its MFMAs (its
-// prefetching form needs more registers and ran 37 % slower).
-//  !CONVT: A(m, k) = X[pixel m shifted by tap][c], k = tap cp + c (tap =
-//   3 (dy + 1) + dx + 1), zero outside the image and for k >= 9 cp: the
-//   im2col matrix, gathered 8 channels (16 bytes) at a time; B(k, n) =
-//   B[n][k] (packed weights, ldb per row).
-//  CONVT: A(m, k) = the same with m = tap cp + c and k the pixel, and
-//   B(k, n) = G[pixel k][n] (the weight gradient's operands); row ones_row
-//   of A is all ones, so that row of C is the column sums of G (the bias
-//   gradient).
-template <int EPI, bool CONVT>
-__global__ __launch_bounds__(256) void k_gemm(GemmArgs g) {
-  __shared__ __attribute__((aligned(16))) uint16_t As[BM * LDK];
-  __shared__ __attribute__((aligned(16))) uint16_t Bs[BN * LDK];
-  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
-  const int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
-  const int64_t kbase = (int64_t)blockIdx.z * g.K;
-  f32x16 acc0, acc1;
-  for (int r = 0; r < 16; ++r) {
-    acc0[r] = 0.0f;
-    acc1[r] = 0.0f;
-  }
-  auto mma = [&]() {
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 16) {
-      const int kk = ks + 8 * (lane >> 5);
-      const bf16x8 a = *(const bf16x8*)(As + (wave * 32 + (lane & 31)) * LDK + kk);
-      const bf16x8 b0 = *(const bf16x8*)(Bs + (lane & 31) * LDK + kk);
-      const bf16x8 b1 = *(const bf16x8*)(Bs + (32 + (lane & 31)) * LDK + kk);
-      acc0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b0, acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b1, acc1, 0, 0, 0);
+    for (int k = 0; k < BATCH; ++k) {
+      const int i = (batch * BATCH + k) * 512 + threadIdx.x, px = i / U, ch = i - px * U;
+      const int y = y0 + px / kTileP - 1, x = x0 + px % kTileP - 1;
+      r[k] = make_uint4(0, 0, 0, 0);
+      if (i < CHUNKS && y >= 0 && y < g.H && x >= 0 && x < g.W)
+        r[k] = *(const uint4*)(g.X + (((int64_t)img * g.H + y) * g.W + x) * CP + ch * 8);
     }
   };
-  if constexpr (CONVT) {
-    // each tile staged right before its MFMAs: work item (rc, pp) moves an
-    // 8-row chunk of two pixels of A (and, t < 128, of B)
-    const int rc = t >> 4, pp = (t & 15) * 2, kc = m0 + 8 * rc, co = n0 + 8 * rc;
-    for (int kt = 0; kt < g.K; kt += BK) {
-      const int64_t k0 = kbase + kt;
-      uint4 v[2];
-      if (kc == g.ones_row) {
-        // rows ones_row .. + 7: ones, then zeros (bf16 1.0 = 0x3f80)
-        *(uint32_t*)(As + (8 * rc) * LDK + pp) = 0x3f803f80u;
+  auto stage = [&](uint16_t* to, int batch) {
 #pragma unroll
-        for (int j = 1; j < 8; ++j) *(uint32_t*)(As + (8 * rc + j) * LDK + pp) = 0u;
-      } else {
-        const int tap = kc / g.cp, c = kc - tap * g.cp;
-        fetch_t(v, g.X, k0, pp, g.cp, c, tap / 3 - 1, tap % 3 - 1, kc < g.M && tap < 9, g.H, g.W);
-        store_t(As, rc, pp, v);
-      }
-      if (t < 128) {
-        fetch_t(v, g.G, k0, pp, g.cpg, co, 0, 0, co < g.cpg, g.H, g.W);
-        store_t(Bs, rc, pp, v);
-      }
-      __syncthreads();
-      mma();
-      __syncthreads();
+    for (int k = 0; k < BATCH; ++k) {
+      const int i = (batch * BATCH + k) * 512 + threadIdx.x, px = i / U, ch = i - px * U;
+      if (i < CHUNKS) *(uint4*)(to + px * PITCH + ch * 8) = r[k];
     }
-  } else {
-    // the next tile's global loads are issued before the current tile's
-    // MFMAs and written to LDS after them
-    int cy[2], cx[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const int p = m0 + (t >> 2) + 64 * i;
-      cx[i] = p % g.W;
-      cy[i] = (p / g.W) % g.H;
-    }
-    uint4 ra[2], rb;
-    auto fetch = [&](int64_t k0) {
-      const int kc = (int)k0 + (t & 3) * 8;
-      const int tap = kc / g.cp, c = kc - tap * g.cp;
-      const int dy = tap / 3 - 1, dx = tap % 3 - 1;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int p = m0 + (t >> 2) + 64 * i;
-        const int yy = cy[i] + dy, xx = cx[i] + dx;
-        ra[i] = make_uint4(0, 0, 0, 0);
-        if (p < g.M && tap < 9 && yy >= 0 && yy < g.H && xx >= 0 && xx < g.W)
-          ra[i] = *(const uint4*)(g.X + ((int64_t)p + dy * g.W + dx) * g.cp + c);
-      }
-      const int row = t >> 2;
-      rb = make_uint4(0, 0, 0, 0);
-      if (n0 + row < g.N) rb = *(const uint4*)(g.B + (int64_t)(n0 + row) * g.ldb + k0 + (t & 3) * 8);
-    };
-    fetch(kbase);
-    for (int kt = 0; kt < g.K; kt += BK) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) *(uint4*)(As + ((t >> 2) + 64 * i) * LDK + (t & 3) * 8) = ra[i];
-      *(uint4*)(Bs + (t >> 2) * LDK + (t & 3) * 8) = rb;
-      __syncthreads();
-      if (kt + BK < g.K) fetch(kbase + kt + BK);
-      mma();
-      __syncthreads();
+  };
+  int t = blockIdx.x, cur = 0;
+  if (t < g.tiles) {
+    for (int batch = 0; batch < 2; ++batch) {
+      fetch(t, batch);
+      stage(tile[0], batch);
     }
   }
+  __syncthreads();
+  for (; t < g.tiles; t += gridDim.x, cur ^= 1) {
+    // the next tile's chunks in two batches, so that half the registers hold them
+    const bool more = t + (int)gridDim.x < g.tiles;
+    if (more) fetch(t + gridDim.x, 0);
+    const uint16_t* in = tile[cur];
+    f32x16 acc[MB];
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
+    for (int b = 0; b < MB; ++b)
+      for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      // accumulator layout: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
-      const int m = m0 + wave * 32 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
-      const int n = n0 + 32 * j + (lane & 31);
-      if (m >= g.M || n >= g.N) continue;
-      const float v = j ? acc1[r] : acc0[r];
-      const int64_t o = (int64_t)m * g.ldc + n;
-      if (EPI == EPI_RELU_BF16) {
-        ((uint16_t*)g.C)[o] = f2bf(fmaxf(v + g.bias[n], 0.0f));
-      } else if (EPI == EPI_BIAS_F32) {
-        ((float*)g.C)[o] = v + g.bias[n];
-      } else if (EPI == EPI_MASK_BF16) {
-        ((uint16_t*)g.C)[o] = bf_positive(g.mask[(int64_t)m * g.ldm + n]) ? f2bf(v) : (uint16_t)0;
-      } else {
-        ((float*)g.C)[(int64_t)blockIdx.z * g.split_stride + o] = v;
+    for (int s = 0; s < KS; ++s) {
+      if (s == KS / 2 && more) {
+        stage(tile[cur ^ 1], 0);
+        fetch(t + gridDim.x, 1);
+      }
+      constexpr int last = 9 * CP;
+      const int lo = 16 * s, hi = lo + 8;
+      const int o = col_offset<CP, PITCH>(lo);
+      // past the last tap (weights zero) the upper half rereads the lower's
+      const int at = hi >= last ? base : lo / CP == hi / CP ? at_chan : hi / CP % 3 != 0 ? at_tap : at_row;
+#pragma unroll
+      for (int b = 0; b < MB; ++b) {
+        const bf16x8 a = *(const bf16x8*)(in + at + o + b * 2 * kTileP * PITCH);
+        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s], a, acc[b], 0, 0, 0);
       }
     }
+    int img, y0, x0;
+    origin(t, img, y0, x0);
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      const int y = y0 + row0 + 2 * b, x = x0 + col;
+      if (y >= g.H || x >= g.W) continue;
+      const int64_t p = ((int64_t)img * g.H + y) * g.W + x;
+      if (EPI == EPI_OUT_F32) {
+        // accumulator layout: register r of lane l holds row 8 (r / 4) +
+        // 4 (l / 32) + r % 4 (channel), column l % 32 (pixel)
+        if (half == 0) {
+          const float z = acc[b][0] + g.bias[0];
+          const int64_t hw = (int64_t)g.H * g.W;
+          ((float*)g.C)[p] = g.x ? g.x[p + (img + 1) * hw] + z / g.s1 : z;
+        }
+        continue;
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int co = nb * 32 + 8 * j + 4 * half;
+        if (co >= g.rows) continue;
+        uint16_t q[4];
+        if (EPI == EPI_RELU_BF16) {
+          const float4 bias = *(const float4*)(g.bias + co);
+          const float bv[4] = {bias.x, bias.y, bias.z, bias.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) q[i] = f2bf(fmaxf(acc[b][4 * j + i] + bv[i], 0.0f));
+        } else {
+          uint16_t m[4];
+          const uint2 mw = *(const uint2*)(g.mask + p * g.rows + co);
+          __builtin_memcpy(m, &mw, 8);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) q[i] = bf_positive(m[i]) ? f2bf(acc[b][4 * j + i]) : (uint16_t)0;
+        }
+        uint2 qw;
+        __builtin_memcpy(&qw, q, 8);
+        *(uint2*)((uint16_t*)g.C + p * g.rows + co) = qw;
+      }
+    }
+    if (more) stage(tile[cur ^ 1], 1);
+    __syncthreads();
+  }
+}
+
+struct WgradArgs {
+  const uint16_t* X;       // layer input, NHWC [pixels][cp]
+  const uint16_t* G;       // output gradient, NHWC [pixels][cpg]
+  int H, W, cp, cpg;
+  int tiles_x, tiles_y, tiles;  // 8 x 16 tiles of an image, and of the batch
+  float* part;             // [workgroup][9 cp rows, .., row bias_row][cpg]
+  int64_t stride;          // elements of a workgroup's sums
+  int bias_row;
+};
+
+// Sums of a workgroup's tiles: part[kc][co] = sum_p col(X)[p][kc] G[p][co], and
+// the column sums of G (the bias gradient) in row bias_row.  Nine waves, one
+// tap each; CIB x COB blocks of 32 x 32 (input x output channels) a wave.
+//
+// Both operands run along pixels, the outer dimension of NHWC: they are
+// read from row-major LDS tiles with the transposing ds_read_b64_tr_b16 (16
+// lanes fetch 4 pixels x 16 channels and each receives one channel's 4
+// pixels), 16 pixels of a tile row per MFMA step.  Pixels lie 64 or 192 bytes
+// apart, so the 4 pixels x 32 channels of 32 lanes cover all 64 banks.  A step's
+// four reads of 512 bytes for four MFMAs keep the LDS (113 bytes a clock for
+// 8-byte reads) as busy as the matrix cores; a tile's border is staged once
+// for all nine taps.  The next tile is loaded while this one is multiplied.
+template <int CIB, int COB>
+__global__ __launch_bounds__(576) void k_wgrad(WgradArgs g) {
+  constexpr int TH = 8, PIX = (TH + 2) * kTileP, PIXG = TH * kTile;
+  constexpr int PA = CIB == 1 ? 32 : 96, PG = COB == 1 ? 32 : 96;  // elements between pixels
+  constexpr int UA = 4 * CIB, UG = 4 * COB;                        // 8-channel chunks staged per pixel
+  constexpr int PERA = (PIX * UA + 575) / 576, PERG = (PIXG * UG + 575) / 576;
+  constexpr int BUF = PIX * PA + PIXG * PG;
+  __shared__ __attribute__((aligned(16))) uint16_t tile[2][BUF];
+  const int tap = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s4 lds_s4;
+  // transposing read: lane l supplies pixel 8 (l / 32) + (l / 4) % 4, channels
+  // 16 ((l / 16) % 2) + 4 (l % 4) .. + 3, and receives channel l % 32 of pixels
+  // 8 (l / 32) .. + 3 (the second read: 4 pixels on)
+  const int pix = 8 * (lane >> 5) + ((lane >> 2) & 3), chan = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const int at_a = ((tap / 3) * kTileP + tap % 3 + pix) * PA + chan, at_g = PIX * PA + pix * PG + chan;
+  auto operand = [&](uint16_t* at, int pitch) {
+    const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)at);
+    const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(at + 4 * pitch));
+    bf16x8 v;
+    __builtin_memcpy(&v, &lo, 8);
+    __builtin_memcpy((char*)&v + 8, &hi, 8);
+    return v;
+  };
+  uint4 ra[PERA], rg[PERG];
+  float bias[8] = {};  // 8 channels of the thread's chunk (576 is a multiple of UG)
+  auto fetch = [&](int t) {
+    const int img = t / (g.tiles_x * g.tiles_y), rest = t - img * (g.tiles_x * g.tiles_y), ty = rest / g.tiles_x;
+    const int y0 = ty * TH, x0 = (rest - ty * g.tiles_x) * kTile;
+#pragma unroll
+    for (int k = 0; k < PERA; ++k) {
+      const int i = k * 576 + threadIdx.x, px = i / UA, ch = i % UA;
+      const int y = y0 + px / kTileP - 1, x = x0 + px % kTileP - 1;
+      ra[k] = make_uint4(0, 0, 0, 0);
+      if (px < PIX && ch * 8 < g.cp && y >= 0 && y < g.H && x >= 0 && x < g.W)
+        ra[k] = *(const uint4*)(g.X + (((int64_t)img * g.H + y) * g.W + x) * g.cp + ch * 8);
+    }
+#pragma unroll
+    for (int k = 0; k < PERG; ++k) {
+      const int i = k * 576 + threadIdx.x, px = i / UG, ch = i % UG;
+      const int y = y0 + px / kTile, x = x0 + px % kTile;
+      rg[k] = make_uint4(0, 0, 0, 0);
+      if (px < PIXG && ch * 8 < g.cpg && y < g.H && x < g.W)
+        rg[k] = *(const uint4*)(g.G + (((int64_t)img * g.H + y) * g.W + x) * g.cpg + ch * 8);
+    }
+  };
+  auto stage = [&](uint16_t* to) {
+#pragma unroll
+    for (int k = 0; k < PERA; ++k) {
+      const int i = k * 576 + threadIdx.x, px = i / UA;
+      if (px < PIX) *(uint4*)(to + px * PA + i % UA * 8) = ra[k];
+    }
+#pragma unroll
+    for (int k = 0; k < PERG; ++k) {
+      const int i = k * 576 + threadIdx.x, px = i / UG;
+      if (px < PIXG) *(uint4*)(to + PIX * PA + px * PG + i % UG * 8) = rg[k];
+      const uint32_t w[4] = {rg[k].x, rg[k].y, rg[k].z, rg[k].w};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        bias[2 * q] += __uint_as_float(w[q] << 16);
+        bias[2 * q + 1] += __uint_as_float(w[q] & 0xffff0000u);
+      }
+    }
+  };
+  f32x16 acc[CIB][COB];
+#pragma unroll
+  for (int i = 0; i < CIB; ++i)
+    for (int j = 0; j < COB; ++j)
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  int t = blockIdx.x, cur = 0;
+  if (t < g.tiles) {
+    fetch(t);
+    stage(tile[0]);
+  }
+  __syncthreads();
+  for (; t < g.tiles; t += gridDim.x, cur ^= 1) {
+    const bool more = t + (int)gridDim.x < g.tiles;
+    if (more) fetch(t + gridDim.x);
+#pragma unroll
+    for (int y = 0; y < TH; ++y) {
+      bf16x8 a[CIB], b[COB];
+#pragma unroll
+      for (int i = 0; i < CIB; ++i) a[i] = operand(tile[cur] + at_a + y * kTileP * PA + 32 * i, PA);
+#pragma unroll
+      for (int j = 0; j < COB; ++j) b[j] = operand(tile[cur] + at_g + y * kTile * PG + 32 * j, PG);
+#pragma unroll
+      for (int i = 0; i < CIB; ++i)
+#pragma unroll
+        for (int j = 0; j < COB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+    if (more) stage(tile[cur ^ 1]);
+    __syncthreads();
+  }
+  float* part = g.part + (int64_t)blockIdx.x * g.stride;
+#pragma unroll
+  for (int i = 0; i < CIB; ++i)
+#pragma unroll
+    for (int j = 0; j < COB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        // accumulator layout: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+        const int c = 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), co = 32 * j + (lane & 31);
+        if (c < g.cp && co < g.cpg) part[(int64_t)(tap * g.cp + c) * g.cpg + co] = acc[i][j][r];
+      }
+  // column sums of G: the threads of a chunk added in thread order
+  float* sums = (float*)tile[0];
+  static_assert(sizeof(tile) >= 576 * 8 * sizeof(float), "bias sums fit the tile");
+#pragma unroll
+  for (int q = 0; q < 8; ++q) sums[threadIdx.x * 8 + q] = bias[q];
+  __syncthreads();
+  if ((int)threadIdx.x < g.cpg) {
+    float v = 0.0f;
+    for (int k = threadIdx.x / 8; k < 576; k += UG) v += sums[k * 8 + threadIdx.x % 8];
+    part[(int64_t)g.bias_row * g.cpg + threadIdx.x] = v;
   }
 }
 
@@ -227,18 +367,9 @@ __global__ void k_pack_input(const float* __restrict__ x, int64_t npix, int hw, 
   *(uint4*)(a0 + p * 8) = v;
 }
 
-// y = x1 + z / s1
-__global__ void k_output(const float* __restrict__ z, int ldz, const float* __restrict__ x, int64_t npix, int hw,
-                         float s1, float* __restrict__ y) {
-  const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= npix) return;
-  const int64_t img = p / hw, off = p - img * hw;
-  y[p] = x[img * 2 * hw + hw + off] + z[p * ldz] / s1;
-}
-
 // Residual r = z + s1 x1 - s1 t; g[p][0] = bf16(2 r / npix), other channels
 // 0; per-block sum of r^2 in FP64 (fixed-order tree).
-__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ z, int ldz, const float* __restrict__ x,
+__global__ __launch_bounds__(256) void k_loss(const float* __restrict__ z, const float* __restrict__ x,
                                               const float* __restrict__ tgt, int64_t npix, int hw, float s1,
                                               uint16_t* __restrict__ g, double* __restrict__ part) {
   __shared__ double sh[256];
@@ -246,7 +377,7 @@ __global__ __launch_bounds__(256) void k_loss(const float* __restrict__ z, int l
   double r2 = 0.0;
   if (p < npix) {
     const int64_t img = p / hw, off = p - img * hw;
-    const float r = z[p * ldz] + s1 * x[img * 2 * hw + hw + off] - s1 * tgt[p];
+    const float r = z[p] + s1 * x[img * 2 * hw + hw + off] - s1 * tgt[p];
     r2 = (double)r * r;
     uint4 v;
     v.x = f2bf(2.0f * r / (float)npix);
@@ -279,37 +410,46 @@ __global__ __launch_bounds__(256) void k_sum_in_order(const double* part, int n,
 }
 
 // grad W[co][tap][ci] = sum over splits of part[z][tap * cinp + ci][co]
-// and grad b[co] = sum over splits of part[z][kp][co] (the row of ones)
+// and grad b[co] = sum over splits of part[z][kp][co] (the bias row)
 // (part entry o = kc * ldc + co).  A workgroup takes 64 consecutive entries
-// o; its four waves add the splits z = w, w + 4, ... (w = wave) in order,
-// reading 64 consecutive floats per split, and the four sums are added in
-// wave order: a fixed order on every call.
-__global__ __launch_bounds__(256) void k_wgrad_reduce(const float* part, int splits, int64_t stride, int ldc, int cinp,
-                                                      int cin, int cout, int kp, float* grad, float* bgrad) {
-  __shared__ double sh[4][64];
+// o; its 16 waves add the splits z = w, w + 16, ... (w = wave) in order,
+// reading 64 consecutive floats per split, and the 16 sums are added in
+// wave order: a fixed order on every call.  (Four waves kept too few loads in
+// flight: 19 us for 256 splits of 577 x 64.)
+constexpr int kReduceWaves = 16;
+__global__ __launch_bounds__(kReduceWaves * 64) void k_wgrad_reduce(const float* __restrict__ part, int splits,
+                                                                    int64_t stride, int ldc, int cinp, int cin,
+                                                                    int cout, int kp, float* __restrict__ grad,
+                                                                    float* __restrict__ bgrad) {
+  __shared__ double sh[kReduceWaves][64];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int64_t o = (int64_t)blockIdx.x * 64 + l;
-  double s = 0.0;
-  if (o < stride)
-    for (int z = w; z < splits; z += 4) s += part[z * stride + o];
-  sh[w][l] = s;
-  __syncthreads();
-  if (w != 0 || o >= stride) return;
   const int kc = (int)(o / ldc), co = (int)(o - (int64_t)kc * ldc);
   const int tap = kc / cinp, ci = kc - tap * cinp;
-  const float v = (float)(((sh[0][l] + sh[1][l]) + sh[2][l]) + sh[3][l]);
-  if (co >= cout) return;  // padding
+  // padding rows and columns were never written
+  const bool used = o < stride && co < cout && (kc == kp || (tap < 9 && ci < cin));
+  double s = 0.0;
+  if (used)
+    for (int z = w; z < splits; z += kReduceWaves) s += part[z * stride + o];
+  sh[w][l] = s;
+  __syncthreads();
+  if (w != 0 || !used) return;
+  double v = sh[0][l];
+  for (int k = 1; k < kReduceWaves; ++k) v += sh[k][l];
   if (kc == kp)
-    bgrad[co] = v;
-  else if (tap < 9 && ci < cin)
-    grad[(co * 9 + tap) * cin + ci] = v;
+    bgrad[co] = (float)v;
+  else
+    grad[(co * 9 + tap) * cin + ci] = (float)v;
 }
 
 // Forward weights wb[co][kc] (kc = tap * cinp + ci) and, for the data
 // gradient, wf[ci][kc'] (kc' = tap' * coutp + co) = W[co][8 - tap'][ci].
-__global__ void k_pack_weights(const float* __restrict__ W, int cin, int cout, int cinp, int coutp, int kp, int kpb,
-                               uint16_t* __restrict__ wb, uint16_t* __restrict__ wf) {
+// And the layer's biases, zero beyond cout (read four at a time).
+__global__ void k_pack_weights(const float* __restrict__ W, const float* __restrict__ b, int cin, int cout, int cinp,
+                               int coutp, int kp, int kpb, uint16_t* __restrict__ wb, uint16_t* __restrict__ wf,
+                               float* __restrict__ bias) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < kMaxChannels) bias[i] = i < cout ? b[i] : 0.0f;
   if (i < coutp * kp) {
     const int co = i / kp, kc = i % kp, tap = kc / cinp, ci = kc % cinp;
     const float v = (co < cout && tap < 9 && ci < cin) ? W[(co * 9 + tap) * cin + ci] : 0.0f;
@@ -347,6 +487,7 @@ struct vam_cnn {
   std::vector<int64_t> woff, boff;
   int64_t nparam;
   float *master, *m1, *m2, *grad;
+  float* bias;                     // [layers][kMaxChannels], padded copies of the biases
   std::vector<uint16_t*> wb, wf;   // per layer (index l - 1)
   std::vector<uint16_t*> act;      // a_0 .. a_{L-1}
   float* z;
@@ -366,7 +507,7 @@ static inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 static bool valid(const vam_cnn* h) { return h && h->magic == kCnnMagic; }
 
 static void free_cnn(vam_cnn* h) {
-  std::vector<void*> ptrs = {h->master, h->m1, h->m2, h->grad, h->z, h->g[0], h->g[1],
+  std::vector<void*> ptrs = {h->master, h->m1, h->m2, h->grad, h->bias, h->z, h->g[0], h->g[1],
                              h->part, h->lpart, h->loss};
   for (auto p : h->wb) ptrs.push_back(p);
   for (auto p : h->wf) ptrs.push_back(p);
@@ -377,20 +518,64 @@ static void free_cnn(vam_cnn* h) {
   delete h;
 }
 
-template <int EPI, bool CONVT>
-static vam_status gemm(const GemmArgs& a, int splits, hipStream_t s) {
-  const dim3 grid((unsigned)((a.M + BM - 1) / BM), (unsigned)((a.N + BN - 1) / BN), (unsigned)splits);
-  hipLaunchKernelGGL((k_gemm<EPI, CONVT>), grid, dim3(256), 0, s, a);
-  VAM_HIP_TRY(hipGetLastError(), "launching a CNN GEMM");
+template <int CP, int EPI>
+static void launch_conv(const ConvArgs& a, hipStream_t s) {
+  // one workgroup a CU (eight waves with the weights in registers fill it), two
+  // where fewer channels leave room
+  const dim3 grid((unsigned)std::min(a.tiles, CP > 32 ? 256 : 512));
+  if constexpr (EPI != EPI_OUT_F32) {
+    if (a.rows > 32) {
+      hipLaunchKernelGGL((k_conv<CP, 2, EPI>), grid, dim3(512), 0, s, a);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_conv<CP, 1, EPI>), grid, dim3(512), 0, s, a);
+}
+
+// The convolution of n images X with cp channels (a multiple of 8, <= 64).
+template <int EPI>
+static vam_status conv(ConvArgs a, int n, int H, int W, int cp, hipStream_t s) {
+  a.H = H;
+  a.W = W;
+  a.tiles_x = (W + kTile - 1) / kTile;
+  a.tiles_y = (H + kTile - 1) / kTile;
+  a.tiles = n * a.tiles_x * a.tiles_y;
+  switch (cp) {
+    case 8: launch_conv<8, EPI>(a, s); break;
+    case 16: launch_conv<16, EPI>(a, s); break;
+    case 24: launch_conv<24, EPI>(a, s); break;
+    case 32: launch_conv<32, EPI>(a, s); break;
+    case 40: launch_conv<40, EPI>(a, s); break;
+    case 48: launch_conv<48, EPI>(a, s); break;
+    case 56: launch_conv<56, EPI>(a, s); break;
+    default: launch_conv<64, EPI>(a, s); break;
+  }
+  VAM_HIP_TRY(hipGetLastError(), "launching a convolution");
   return VAM_OK;
+}
+
+// Sums of the weight gradient; returns the number of workgroups (splits).
+static int wgrad(WgradArgs a, int n, int H, int W, hipStream_t s) {
+  a.H = H;
+  a.W = W;
+  a.tiles_x = (W + kTile - 1) / kTile;
+  a.tiles_y = (H + 7) / 8;
+  a.tiles = n * a.tiles_x * a.tiles_y;
+  const int splits = std::min(a.tiles, kMaxSplits);
+  if (a.cp > 32 && a.cpg > 32) hipLaunchKernelGGL((k_wgrad<2, 2>), dim3(splits), dim3(576), 0, s, a);
+  else if (a.cp > 32) hipLaunchKernelGGL((k_wgrad<2, 1>), dim3(splits), dim3(576), 0, s, a);
+  else if (a.cpg > 32) hipLaunchKernelGGL((k_wgrad<1, 2>), dim3(splits), dim3(576), 0, s, a);
+  else hipLaunchKernelGGL((k_wgrad<1, 1>), dim3(splits), dim3(576), 0, s, a);
+  return splits;
 }
 
 static vam_status pack_all(vam_cnn* h, hipStream_t s) {
   for (int l = 1; l <= h->L; ++l) {
     const int i = l - 1;
     const int n = std::max(h->coutp[i] * h->kp[i], h->cinp[i] * h->kpb[i]);
-    hipLaunchKernelGGL(k_pack_weights, dim3(nblocks(n, 256)), dim3(256), 0, s, h->master + h->woff[i], h->cin[i],
-                       h->cout[i], h->cinp[i], h->coutp[i], h->kp[i], h->kpb[i], h->wb[i], h->wf[i]);
+    hipLaunchKernelGGL(k_pack_weights, dim3(nblocks(n, 256)), dim3(256), 0, s, h->master + h->woff[i],
+                       h->master + h->boff[i], h->cin[i], h->cout[i], h->cinp[i], h->coutp[i], h->kp[i], h->kpb[i],
+                       h->wb[i], h->wf[i], h->bias + (int64_t)i * kMaxChannels);
   }
   VAM_HIP_TRY(hipGetLastError(), "launching the weight packing");
   return VAM_OK;
@@ -402,45 +587,32 @@ static vam_status pack_all(vam_cnn* h, hipStream_t s) {
     if (st_ != VAM_OK) return st_;      \
   } while (0)
 
-// Forward pass of n images; leaves a_0 .. a_{L-1} and z in the workspace.
-static vam_status forward(vam_cnn* h, const float* x, int n, hipStream_t s) {
+// Forward pass of n images; leaves a_0 .. a_{L-1} in the workspace, and either
+// z there (y NULL) or the output y = x1 + z / s1 in y.
+static vam_status forward(vam_cnn* h, const float* x, int n, float* y, hipStream_t s) {
   const int64_t npix = (int64_t)n * h->H * h->W;
   hipLaunchKernelGGL(k_pack_input, dim3(nblocks(npix, 256)), dim3(256), 0, s, x, npix, h->H * h->W, h->s0, h->s1,
                      h->act[0]);
   VAM_HIP_TRY(hipGetLastError(), "launching the input packing");
   for (int l = 1; l <= h->L; ++l) {
     const int i = l - 1;
-    GemmArgs a = {};
+    ConvArgs a = {};
     a.X = h->act[i];
-    a.H = h->H;
-    a.W = h->W;
-    a.cp = h->cinp[i];
     a.B = h->wb[i];
     a.ldb = h->kp[i];
-    a.M = (int)npix;
-    a.N = h->cout[i];
-    a.K = h->kp[i];
-    a.bias = h->master + h->boff[i];
+    a.rows = h->coutp[i];
+    a.bias = h->bias + (int64_t)i * kMaxChannels;
     if (l < h->L) {
       a.C = h->act[l];
-      a.ldc = h->coutp[i];
-      CNN_TRY((gemm<EPI_RELU_BF16, false>(a, 1, s)));
+      CNN_TRY((conv<EPI_RELU_BF16>(a, n, h->H, h->W, h->cinp[i], s)));
     } else {
-      a.C = h->z;
-      a.ldc = h->coutp[i];
-      CNN_TRY((gemm<EPI_BIAS_F32, false>(a, 1, s)));
+      a.C = y ? y : h->z;
+      a.x = y ? x : nullptr;
+      a.s1 = h->s1;
+      CNN_TRY((conv<EPI_OUT_F32>(a, n, h->H, h->W, h->cinp[i], s)));
     }
   }
   return VAM_OK;
-}
-
-static int choose_splits(int64_t npix) {
-  // the pixel sum of the weight gradient, in equal multiples of BK
-  const int64_t tiles = npix / BK;
-  int best = 1;
-  for (int s = 1; s <= kMaxSplits; ++s)
-    if (tiles % s == 0 && tiles / s >= 16) best = s;
-  return best;
 }
 
 }  // namespace cnn
@@ -502,6 +674,7 @@ vam_status vam_cnn_create(int32_t layers, int32_t channels, int32_t height, int3
   alloc((void**)&h->m1, h->nparam * 4);
   alloc((void**)&h->m2, h->nparam * 4);
   alloc((void**)&h->grad, h->nparam * 4);
+  alloc((void**)&h->bias, (size_t)layers * kMaxChannels * 4);
   h->wb.assign(layers, nullptr);
   h->wf.assign(layers, nullptr);
   h->act.assign(layers, nullptr);
@@ -510,10 +683,10 @@ vam_status vam_cnn_create(int32_t layers, int32_t channels, int32_t height, int3
     if (i > 0) alloc((void**)&h->wf[i], (size_t)h->cinp[i] * h->kpb[i] * 2);
     alloc((void**)&h->act[i], (size_t)npix * h->cinp[i] * 2);
   }
-  alloc((void**)&h->z, (size_t)npix * h->coutp[layers - 1] * 4);
+  alloc((void**)&h->z, (size_t)npix * 4);
   alloc((void**)&h->g[0], (size_t)npix * cmax * 2);
   alloc((void**)&h->g[1], (size_t)npix * cmax * 2);
-  alloc((void**)&h->part, (size_t)kMaxSplits * (kmax + 1) * cmax * 4);  // choose_splits() <= kMaxSplits
+  alloc((void**)&h->part, (size_t)kMaxSplits * (kmax + 1) * cmax * 4);  // one set of sums per workgroup
   alloc((void**)&h->lpart, (size_t)lblocks * 8);
   alloc((void**)&h->loss, 8);
   if (e == hipSuccess) e = hipMemset(h->master, 0, h->nparam * 4);
@@ -615,12 +788,7 @@ vam_status vam_cnn_forward(vam_cnn_t h, const float* x, int32_t n, float* y, hip
   if (!x || !y) return fail(VAM_ERR_INVALID_ARG, "NULL buffer");
   if (n < 1 || n > h->maxn) return fail(VAM_ERR_INVALID_ARG, "batch %d outside [1, %d]", n, h->maxn);
   VAM_HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
-  CNN_TRY(forward(h, x, n, s));
-  const int64_t npix = (int64_t)n * h->H * h->W;
-  hipLaunchKernelGGL(k_output, dim3(nblocks(npix, 256)), dim3(256), 0, s, h->z, h->coutp[h->L - 1], x, npix,
-                     h->H * h->W, h->s1, y);
-  VAM_HIP_TRY(hipGetLastError(), "launching the CNN output");
-  return VAM_OK;
+  return forward(h, x, n, y, s);
 }
 
 vam_status vam_cnn_loss_grad(vam_cnn_t h, const float* x, const float* t, int32_t n, double* loss_out,
@@ -632,60 +800,43 @@ vam_status vam_cnn_loss_grad(vam_cnn_t h, const float* x, const float* t, int32_
   const int64_t npix = (int64_t)n * h->H * h->W;
   if (npix % BK) return fail(VAM_ERR_INVALID_ARG, "n * height * width must be a multiple of 32");
   VAM_HIP_TRY(hipSetDevice(h->device), "hipSetDevice");
-  CNN_TRY(forward(h, x, n, s));
+  CNN_TRY(forward(h, x, n, nullptr, s));
   const int L = h->L;
   const unsigned lblocks = nblocks(npix, 256);
   // g_L = d loss / d z (8 channels, channel 0 used)
   uint16_t* gcur = h->g[0];
   uint16_t* gnext = h->g[1];
-  hipLaunchKernelGGL(k_loss, dim3(lblocks), dim3(256), 0, s, h->z, h->coutp[L - 1], x, t, npix, h->H * h->W, h->s1,
+  hipLaunchKernelGGL(k_loss, dim3(lblocks), dim3(256), 0, s, h->z, x, t, npix, h->H * h->W, h->s1,
                      gcur, h->lpart);
   hipLaunchKernelGGL(k_sum_in_order, dim3(1), dim3(256), 0, s, h->lpart, (int)lblocks, 1.0 / (double)npix, h->loss);
   VAM_HIP_TRY(hipGetLastError(), "launching the CNN loss");
-  const int splits = choose_splits(npix);
-  const int ksplit = (int)(npix / splits);
   for (int l = L; l >= 1; --l) {
     const int i = l - 1;
-    // weight gradient: dW^T[kc][co] = sum_p col(a_{l-1})[p][kc] g_l[p][co],
-    // both operands staged along the pixel sum straight from a_{l-1} and g_l
-    GemmArgs a = {};
+    // weight gradient: dW^T[kc][co] = sum_p col(a_{l-1})[p][kc] g_l[p][co] in
+    // rows 0 .. 9 cinp - 1, and row kp = sum_p g_l[p][co] (the bias gradient)
+    WgradArgs a = {};
     a.X = h->act[i];
-    a.H = h->H;
-    a.W = h->W;
     a.cp = h->cinp[i];
     a.G = gcur;
     a.cpg = h->coutp[i];
-    // rows 0 .. kp - 1 of dW^T, then row kp = sum_p g_l[p][co] (the bias
-    // gradient, from a row of ones in A)
-    a.M = h->kp[i] + 1;
-    a.ones_row = h->kp[i];
-    a.N = h->cout[i];
-    a.K = ksplit;
-    a.C = h->part;
-    a.ldc = h->coutp[i];
-    a.split_stride = (int64_t)(h->kp[i] + 1) * h->coutp[i];
-    CNN_TRY((gemm<EPI_PART_F32, true>(a, splits, s)));
-    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nblocks(a.split_stride, 64)), dim3(256), 0, s, h->part, splits, a.split_stride,
-                       h->coutp[i], h->cinp[i], h->cin[i], h->cout[i], h->kp[i], h->grad + h->woff[i],
+    a.part = h->part;
+    a.stride = (int64_t)(h->kp[i] + 1) * h->coutp[i];
+    a.bias_row = h->kp[i];
+    const int splits = wgrad(a, n, h->H, h->W, s);
+    hipLaunchKernelGGL(k_wgrad_reduce, dim3(nblocks(a.stride, 64)), dim3(kReduceWaves * 64), 0, s, h->part, splits,
+                       a.stride, h->coutp[i], h->cinp[i], h->cin[i], h->cout[i], h->kp[i], h->grad + h->woff[i],
                        h->grad + h->boff[i]);
     VAM_HIP_TRY(hipGetLastError(), "launching the gradient reductions");
     if (l == 1) break;
     // data gradient through the ReLU of a_{l-1}
-    GemmArgs d = {};
+    ConvArgs d = {};
     d.X = gcur;
-    d.H = h->H;
-    d.W = h->W;
-    d.cp = h->coutp[i];
     d.B = h->wf[i];
     d.ldb = h->kpb[i];
-    d.M = (int)npix;
-    d.N = h->cinp[i];
-    d.K = h->kpb[i];
+    d.rows = h->cinp[i];
     d.C = gnext;
-    d.ldc = h->cinp[i];
     d.mask = h->act[i];
-    d.ldm = h->cinp[i];
-    CNN_TRY((gemm<EPI_MASK_BF16, false>(d, 1, s)));
+    CNN_TRY((conv<EPI_MASK_BF16>(d, n, h->H, h->W, h->coutp[i], s)));
     std::swap(gcur, gnext);
   }
   if (loss_out) {
