@@ -18,6 +18,7 @@
 #include <cmath>
 #include <cstring>
 #include <new>
+#include <type_traits>
 #include <vector>
 
 #include "vam_cnn.h"
@@ -48,8 +49,8 @@ struct ConvArgs {
   const uint16_t* X;       // NHWC [pixels][CP]
   int H, W;                // image size
   int tiles_x, tiles_y, tiles;  // 16 x 16 tiles of an image, and of the batch
-  const uint16_t* B;       // packed weights [rows][ldb]
-  int rows, ldb;           // output channels (padded), row length
+  const uint16_t* B;       // packed weights (weight_place)
+  int rows, kp;            // output channels (padded), im2col entries (padded)
   void* C;                 // BF16 [pixels][rows], or FP32 [pixels] (EPI_OUT_F32)
   const float* bias;       // EPI_RELU_BF16, EPI_OUT_F32
   const uint16_t* mask;    // EPI_MASK_BF16: BF16 [pixels][rows]
@@ -58,6 +59,23 @@ struct ConvArgs {
 };
 
 constexpr int kTile = 16, kTileP = kTile + 2;  // tile edge, with its border
+
+// Channel of a 32-channel block in MFMA row m: register r of lane l of an
+// accumulator is row 8 (r / 4) + 4 (l / 32) + r % 4, and holds channel 16 (r / 8)
+// + 8 (l / 32) + r % 8 so.
+__host__ __device__ constexpr int row_channel(int m) {
+  const int r = 4 * (m / 8) + m % 4, half = m / 4 % 2;
+  return 16 * (r / 8) + 8 * half + r % 8;
+}
+
+// Place of weight (channel co, im2col entry k) in the packed array of a layer
+// whose rows have kp entries: for every block of 32 channels and every 16
+// entries, the 64 lanes' 8 entries one after the other.
+__host__ __device__ inline int weight_place(int co, int k, int kp) {
+  const int c = co % 32, r = 8 * (c / 16) + c % 8, half = c / 8 % 2;  // row_channel's inverse
+  const int m = 8 * (r / 4) + 4 * half + r % 4, lane = m + 32 * (k / 8 % 2);
+  return ((co / 32 * (kp / 16) + k / 16) * 64 + lane) * 8 + k % 8;
+}
 
 // Element offset, in a staged tile of `pitch` elements a pixel, of the k-th
 // entry of a pixel's im2col row of CP channels a tap.
@@ -81,8 +99,11 @@ constexpr int col_offset(int k) {
 //    number of 16-byte units apart, so 16 lanes read 16 different bank groups.
 //  * The next tile's loads are issued before the current tile's products and
 //    written to the other LDS buffer after them: one barrier a tile.
-//  * Weights are the MFMA's first operand and pixels its second, so a lane
-//    holds four neighbouring channels of one pixel: 8-byte stores.
+//  * Weights are the MFMA's first operand, their rows in the order row_channel,
+//    and pixels its second: a lane holds two runs of eight channels of one
+//    pixel, so outputs (and masks) move 16 bytes at a time.
+//  * Packed weights lie in the order the waves load them (weight_place).
+//  * The LDS reads run four ahead of the products.
 // The products of an output are added in ascending k, 16 at a time, from
 // zero: the same bits as any other tiling of that order.
 template <int CP, int NB, int EPI>
@@ -90,17 +111,21 @@ __global__ __launch_bounds__(512) void k_conv(ConvArgs g) {
   constexpr int U = CP / 8, PITCH = (U | 1) * 8, PIX = kTileP * kTileP;
   constexpr int KS = (9 * CP + 15) / 16, CHUNKS = PIX * U, PER = (CHUNKS + 511) / 512;
   constexpr int MB = NB == 2 ? 2 : 1;  // 32-pixel blocks (two tile rows) of a wave
+  // weights of the last KL steps stay in LDS, so that everything fits 256
+  // registers (two waves a SIMD) without spilling
+  constexpr int KL = NB == 2 && KS > 28 ? KS - 28 : 0, KR = KS - KL;
   __shared__ __attribute__((aligned(16))) uint16_t tile[2][PIX * PITCH];
+  __shared__ __attribute__((aligned(16))) uint16_t wl[(KL ? KL : 1) * NB * 64 * 8];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5;
   const int nb = NB == 2 ? wave & 1 : 0, mg = NB == 2 ? wave >> 1 : wave;
-  bf16x8 w[KS];
-  {
-    const int co = nb * 32 + (lane & 31);
+  bf16x8 w[KR];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      w[s] = bf16x8{};
-      if (co < g.rows) w[s] = *(const bf16x8*)(g.B + (int64_t)co * g.ldb + 16 * s + 8 * half);
-    }
+  for (int s = 0; s < KR; ++s) w[s] = *(const bf16x8*)(g.B + ((nb * (g.kp / 16) + s) * 64 + lane) * 8);
+  __shared__ __attribute__((aligned(32))) float bias[kMaxChannels];
+  if (EPI != EPI_MASK_BF16 && threadIdx.x < kMaxChannels) bias[threadIdx.x] = g.bias[threadIdx.x];
+  for (int i = threadIdx.x; i < KL * NB * 64; i += 512) {
+    const int s = i / (NB * 64), rest = i % (NB * 64);
+    *(uint4*)(wl + i * 8) = *(const uint4*)(g.B + ((rest / 64 * (g.kp / 16) + KR + s) * 64 + rest % 64) * 8);
   }
   // lane's pixel in block b: tile row 2 (mg MB + b) + (lane / 16) % 2, column lane % 16.
   // The upper half of the wave takes the second 8 of a step's 16 entries:
@@ -109,107 +134,136 @@ __global__ __launch_bounds__(512) void k_conv(ConvArgs g) {
   const int base = (row0 * kTileP + col) * PITCH;
   const int at_chan = base + half * 8, at_tap = base + half * (PITCH - (CP - 8)),
             at_row = base + half * ((kTileP - 2) * PITCH - (CP - 8));
-  constexpr int BATCH = (PER + 1) / 2;
-  uint4 r[BATCH];
+  uint4 r[PER];
   auto origin = [&](int t, int& img, int& y0, int& x0) {
     img = t / (g.tiles_x * g.tiles_y);
     const int rest = t - img * (g.tiles_x * g.tiles_y), ty = rest / g.tiles_x;
     y0 = ty * kTile;
     x0 = (rest - ty * g.tiles_x) * kTile;
   };
-  auto fetch = [&](int t, int batch) {
+  // buffer loads: an offset past the image reads zeros, the border's value
+  const uint32_t image_bytes = (uint32_t)g.H * g.W * CP * 2;
+  auto fetch = [&](int t) {
     int img, y0, x0;
     origin(t, img, y0, x0);
+    const __amdgpu_buffer_rsrc_t X = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(g.X + (int64_t)img * g.H * g.W * CP), (short)0, image_bytes, 0x00020000);
 #pragma unroll
-    for (int k = 0; k < BATCH; ++k) {
-      const int i = (batch * BATCH + k) * 512 + threadIdx.x, px = i / U, ch = i - px * U;
+    for (int k = 0; k < PER; ++k) {
+      const int i = k * 512 + threadIdx.x, px = i / U, ch = i - px * U;
       const int y = y0 + px / kTileP - 1, x = x0 + px % kTileP - 1;
-      r[k] = make_uint4(0, 0, 0, 0);
-      if (i < CHUNKS && y >= 0 && y < g.H && x >= 0 && x < g.W)
-        r[k] = *(const uint4*)(g.X + (((int64_t)img * g.H + y) * g.W + x) * CP + ch * 8);
+      const bool inside = (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W && i < CHUNKS;
+      const auto v = __builtin_amdgcn_raw_buffer_load_b128(
+          X, inside ? (y * g.W + x) * (CP * 2) + ch * 16 : (int)image_bytes, 0, 0);
+      __builtin_memcpy(&r[k], &v, 16);
     }
   };
-  auto stage = [&](uint16_t* to, int batch) {
+  auto stage = [&](uint16_t* to) {
 #pragma unroll
-    for (int k = 0; k < BATCH; ++k) {
-      const int i = (batch * BATCH + k) * 512 + threadIdx.x, px = i / U, ch = i - px * U;
+    for (int k = 0; k < PER; ++k) {
+      const int i = k * 512 + threadIdx.x, px = i / U, ch = i - px * U;
       if (i < CHUNKS) *(uint4*)(to + px * PITCH + ch * 8) = r[k];
     }
   };
   int t = blockIdx.x, cur = 0;
   if (t < g.tiles) {
-    for (int batch = 0; batch < 2; ++batch) {
-      fetch(t, batch);
-      stage(tile[0], batch);
-    }
+    fetch(t);
+    stage(tile[0]);
   }
   __syncthreads();
   for (; t < g.tiles; t += gridDim.x, cur ^= 1) {
-    // the next tile's chunks in two batches, so that half the registers hold them
     const bool more = t + (int)gridDim.x < g.tiles;
-    if (more) fetch(t + gridDim.x, 0);
+    if (more) fetch(t + gridDim.x);
+    int img, y0, x0;
+    origin(t, img, y0, x0);
+    // outputs (and masks) of the image as a buffer: lanes outside it, or past
+    // the last channel, get an offset past its end, where stores do nothing
+    const int out_bytes = g.H * g.W * g.rows * 2;
+    int at_out[MB][2];
+    uint4 mask[MB][2];  // loaded with the next tile, before any store
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int y = y0 + row0 + 2 * b, x = x0 + col, co = nb * 32 + 16 * j + 8 * half;
+        at_out[b][j] = y < g.H && x < g.W && co < g.rows ? ((y * g.W + x) * g.rows + co) * 2 : out_bytes;
+        if constexpr (EPI == EPI_MASK_BF16) {
+          const __amdgpu_buffer_rsrc_t M = __builtin_amdgcn_make_buffer_rsrc(
+              const_cast<uint16_t*>(g.mask + (int64_t)img * g.H * g.W * g.rows), (short)0, out_bytes, 0x00020000);
+          const auto v = __builtin_amdgcn_raw_buffer_load_b128(M, at_out[b][j], 0, 0);
+          __builtin_memcpy(&mask[b][j], &v, 16);
+        }
+      }
     const uint16_t* in = tile[cur];
     f32x16 acc[MB];
 #pragma unroll
     for (int b = 0; b < MB; ++b)
       for (int i = 0; i < 16; ++i) acc[b][i] = 0.0f;
+    auto products = [&](auto first, auto end) {
+      constexpr int S0 = decltype(first)::value, S1 = decltype(end)::value, READS = (S1 - S0) * MB + (S0 == KR ? KL : 0);
+      constexpr int AHEAD = READS < 4 ? READS : 4;
 #pragma unroll
-    for (int s = 0; s < KS; ++s) {
-      if (s == KS / 2 && more) {
-        stage(tile[cur ^ 1], 0);
-        fetch(t + gridDim.x, 1);
+      for (int s = S0; s < S1; ++s) {
+        const int lo = 16 * s, hi = lo + 8;
+        const int o = col_offset<CP, PITCH>(lo);
+        // past the last tap (weights zero) the upper half rereads the lower's
+        const bf16x8 ws = s < KR ? w[s < KR ? s : 0] : *(const bf16x8*)(wl + (((s - KR) * NB + nb) * 64 + lane) * 8);
+        const int at = hi >= 9 * CP ? base : lo / CP == hi / CP ? at_chan : hi / CP % 3 != 0 ? at_tap : at_row;
+#pragma unroll
+        for (int b = 0; b < MB; ++b) {
+          const bf16x8 a = *(const bf16x8*)(in + at + o + b * 2 * kTileP * PITCH);
+          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ws, a, acc[b], 0, 0, 0);
+        }
       }
-      constexpr int last = 9 * CP;
-      const int lo = 16 * s, hi = lo + 8;
-      const int o = col_offset<CP, PITCH>(lo);
-      // past the last tap (weights zero) the upper half rereads the lower's
-      const int at = hi >= last ? base : lo / CP == hi / CP ? at_chan : hi / CP % 3 != 0 ? at_tap : at_row;
+      // schedule: AHEAD LDS reads, then a product and a read in turn
+      __builtin_amdgcn_sched_group_barrier(0x100, AHEAD, 0);
+#pragma unroll
+      for (int i = 0; i < READS - AHEAD; ++i) {
+        if (S0 != KR || i % 3 != 2) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // KL: three reads, two products
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, AHEAD, 0);
+    };
+    products(std::integral_constant<int, 0>{}, std::integral_constant<int, KR>{});
+    if constexpr (KL > 0) products(std::integral_constant<int, KR>{}, std::integral_constant<int, KS>{});
+    // into LDS before this tile's stores are issued: loads and stores complete
+    // in order, so waiting for the loads later would wait for the stores too
+    if (more) stage(tile[cur ^ 1]);
+    if constexpr (EPI == EPI_OUT_F32) {
 #pragma unroll
       for (int b = 0; b < MB; ++b) {
-        const bf16x8 a = *(const bf16x8*)(in + at + o + b * 2 * kTileP * PITCH);
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[s], a, acc[b], 0, 0, 0);
+        const int y = y0 + row0 + 2 * b, x = x0 + col;
+        if (y >= g.H || x >= g.W || half != 0) continue;  // channel 0 is row 0
+        const int64_t hw = (int64_t)g.H * g.W, p = img * hw + y * g.W + x;
+        const float z = acc[b][0] + bias[0];
+        ((float*)g.C)[p] = g.x ? g.x[p + (img + 1) * hw] + z / g.s1 : z;
       }
-    }
-    int img, y0, x0;
-    origin(t, img, y0, x0);
+    } else {
+      const __amdgpu_buffer_rsrc_t C = __builtin_amdgcn_make_buffer_rsrc(
+          (uint16_t*)g.C + (int64_t)img * g.H * g.W * g.rows, (short)0, out_bytes, 0x00020000);
 #pragma unroll
-    for (int b = 0; b < MB; ++b) {
-      const int y = y0 + row0 + 2 * b, x = x0 + col;
-      if (y >= g.H || x >= g.W) continue;
-      const int64_t p = ((int64_t)img * g.H + y) * g.W + x;
-      if (EPI == EPI_OUT_F32) {
-        // accumulator layout: register r of lane l holds row 8 (r / 4) +
-        // 4 (l / 32) + r % 4 (channel), column l % 32 (pixel)
-        if (half == 0) {
-          const float z = acc[b][0] + g.bias[0];
-          const int64_t hw = (int64_t)g.H * g.W;
-          ((float*)g.C)[p] = g.x ? g.x[p + (img + 1) * hw] + z / g.s1 : z;
+      for (int b = 0; b < MB; ++b)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          uint16_t q[8];
+          if constexpr (EPI == EPI_RELU_BF16) {
+            const float* bj = bias + nb * 32 + 16 * j + 8 * half;
+            float bv[8];
+            __builtin_memcpy(bv, __builtin_assume_aligned(bj, 32), 32);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q[i] = f2bf(fmaxf(acc[b][8 * j + i] + bv[i], 0.0f));
+          } else {
+            uint16_t m[8];
+            __builtin_memcpy(m, &mask[b][j], 16);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q[i] = bf_positive(m[i]) ? f2bf(acc[b][8 * j + i]) : (uint16_t)0;
+          }
+          typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+          u32x4 v;
+          __builtin_memcpy(&v, q, 16);
+          __builtin_amdgcn_raw_buffer_store_b128(v, C, at_out[b][j], 0, 0);
         }
-        continue;
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int co = nb * 32 + 8 * j + 4 * half;
-        if (co >= g.rows) continue;
-        uint16_t q[4];
-        if (EPI == EPI_RELU_BF16) {
-          const float4 bias = *(const float4*)(g.bias + co);
-          const float bv[4] = {bias.x, bias.y, bias.z, bias.w};
-#pragma unroll
-          for (int i = 0; i < 4; ++i) q[i] = f2bf(fmaxf(acc[b][4 * j + i] + bv[i], 0.0f));
-        } else {
-          uint16_t m[4];
-          const uint2 mw = *(const uint2*)(g.mask + p * g.rows + co);
-          __builtin_memcpy(m, &mw, 8);
-#pragma unroll
-          for (int i = 0; i < 4; ++i) q[i] = bf_positive(m[i]) ? f2bf(acc[b][4 * j + i]) : (uint16_t)0;
-        }
-        uint2 qw;
-        __builtin_memcpy(&qw, q, 8);
-        *(uint2*)((uint16_t*)g.C + p * g.rows + co) = qw;
-      }
     }
-    if (more) stage(tile[cur ^ 1], 1);
     __syncthreads();
   }
 }
@@ -442,23 +496,27 @@ __global__ __launch_bounds__(kReduceWaves * 64) void k_wgrad_reduce(const float*
     grad[(co * 9 + tap) * cin + ci] = (float)v;
 }
 
-// Forward weights wb[co][kc] (kc = tap * cinp + ci) and, for the data
-// gradient, wf[ci][kc'] (kc' = tap' * coutp + co) = W[co][8 - tap'][ci].
-// And the layer's biases, zero beyond cout (read four at a time).
+// Forward weights W(co, kc) with kc = tap * cinp + ci and, for the data
+// gradient, Wflip(ci, kc') = W[co][8 - tap'][ci] with kc' = tap' * coutp + co,
+// at their places (weight_place), zero in the padding of channels (to blocks
+// of 32) and entries; and the layer's biases, zero beyond cout (read four at
+// a time).
+static inline int round32(int c) { return (c + 31) / 32 * 32; }
 __global__ void k_pack_weights(const float* __restrict__ W, const float* __restrict__ b, int cin, int cout, int cinp,
                                int coutp, int kp, int kpb, uint16_t* __restrict__ wb, uint16_t* __restrict__ wf,
                                float* __restrict__ bias) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < kMaxChannels) bias[i] = i < cout ? b[i] : 0.0f;
-  if (i < coutp * kp) {
+  {
     const int co = i / kp, kc = i % kp, tap = kc / cinp, ci = kc % cinp;
-    const float v = (co < cout && tap < 9 && ci < cin) ? W[(co * 9 + tap) * cin + ci] : 0.0f;
-    wb[i] = f2bf(v);
+    if (co < (coutp + 31) / 32 * 32)
+      wb[weight_place(co, kc, kp)] = f2bf(co < cout && tap < 9 && ci < cin ? W[(co * 9 + tap) * cin + ci] : 0.0f);
   }
-  if (wf && i < cinp * kpb) {
+  if (wf) {
     const int ci = i / kpb, kc = i % kpb, tap = kc / coutp, co = kc % coutp;
-    const float v = (ci < cin && co < cout && tap < 9) ? W[(co * 9 + (8 - tap)) * cin + ci] : 0.0f;
-    wf[i] = f2bf(v);
+    if (ci < (cinp + 31) / 32 * 32)
+      wf[weight_place(ci, kc, kpb)] =
+          f2bf(ci < cin && co < cout && tap < 9 ? W[(co * 9 + (8 - tap)) * cin + ci] : 0.0f);
   }
 }
 
@@ -572,7 +630,7 @@ static int wgrad(WgradArgs a, int n, int H, int W, hipStream_t s) {
 static vam_status pack_all(vam_cnn* h, hipStream_t s) {
   for (int l = 1; l <= h->L; ++l) {
     const int i = l - 1;
-    const int n = std::max(h->coutp[i] * h->kp[i], h->cinp[i] * h->kpb[i]);
+    const int n = std::max(round32(h->coutp[i]) * h->kp[i], round32(h->cinp[i]) * h->kpb[i]);
     hipLaunchKernelGGL(k_pack_weights, dim3(nblocks(n, 256)), dim3(256), 0, s, h->master + h->woff[i],
                        h->master + h->boff[i], h->cin[i], h->cout[i], h->cinp[i], h->coutp[i], h->kp[i], h->kpb[i],
                        h->wb[i], h->wf[i], h->bias + (int64_t)i * kMaxChannels);
@@ -599,7 +657,7 @@ static vam_status forward(vam_cnn* h, const float* x, int n, float* y, hipStream
     ConvArgs a = {};
     a.X = h->act[i];
     a.B = h->wb[i];
-    a.ldb = h->kp[i];
+    a.kp = h->kp[i];
     a.rows = h->coutp[i];
     a.bias = h->bias + (int64_t)i * kMaxChannels;
     if (l < h->L) {
@@ -679,8 +737,8 @@ vam_status vam_cnn_create(int32_t layers, int32_t channels, int32_t height, int3
   h->wf.assign(layers, nullptr);
   h->act.assign(layers, nullptr);
   for (int i = 0; i < layers; ++i) {
-    alloc((void**)&h->wb[i], (size_t)h->coutp[i] * h->kp[i] * 2);
-    if (i > 0) alloc((void**)&h->wf[i], (size_t)h->cinp[i] * h->kpb[i] * 2);
+    alloc((void**)&h->wb[i], (size_t)round32(h->coutp[i]) * h->kp[i] * 2);
+    if (i > 0) alloc((void**)&h->wf[i], (size_t)round32(h->cinp[i]) * h->kpb[i] * 2);
     alloc((void**)&h->act[i], (size_t)npix * h->cinp[i] * 2);
   }
   alloc((void**)&h->z, (size_t)npix * 4);
@@ -832,7 +890,7 @@ vam_status vam_cnn_loss_grad(vam_cnn_t h, const float* x, const float* t, int32_
     ConvArgs d = {};
     d.X = gcur;
     d.B = h->wf[i];
-    d.ldb = h->kpb[i];
+    d.kp = h->kpb[i];
     d.rows = h->cinp[i];
     d.C = gnext;
     d.mask = h->act[i];
