@@ -40,6 +40,12 @@ __device__ inline uint16_t f2bf(float f) {  // round to nearest even
   u += 0x7fffu + ((u >> 16) & 1u);
   return (uint16_t)(u >> 16);
 }
+// Two values as a BF16 pair, to nearest even (one v_cvt_pk_bf16_f32).
+__device__ inline uint32_t f2bf_pair(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{lo, hi}, bf16x2));
+}
 __device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 __device__ inline bool bf_positive(uint16_t h) { return h != 0 && !(h & 0x8000u); }
 
@@ -106,6 +112,10 @@ constexpr int col_offset(int k) {
 //  * The LDS reads run four ahead of the products.
 // The products of an output are added in ascending k, 16 at a time, from
 // zero: the same bits as any other tiling of that order.
+// Measured at 16 x 128^2, 64 to 64 channels: 25 us (27 with a mask); the general
+// matrix kernel before, which gathered the nine shifts from memory for every
+// 128 pixels and read all weights with them, 46 us (53).  At 64 images 82 us, 3.3
+// TB/s.  All weights in registers spilled (44 us).
 template <int CP, int NB, int EPI>
 __global__ __launch_bounds__(512) void k_conv(ConvArgs g) {
   constexpr int U = CP / 8, PITCH = (U | 1) * 8, PIX = kTileP * kTileP;
@@ -245,22 +255,26 @@ __global__ __launch_bounds__(512) void k_conv(ConvArgs g) {
       for (int b = 0; b < MB; ++b)
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
-          uint16_t q[8];
+          typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+          u32x4 v;
           if constexpr (EPI == EPI_RELU_BF16) {
             const float* bj = bias + nb * 32 + 16 * j + 8 * half;
             float bv[8];
             __builtin_memcpy(bv, __builtin_assume_aligned(bj, 32), 32);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) q[i] = f2bf(fmaxf(acc[b][8 * j + i] + bv[i], 0.0f));
+            for (int i = 0; i < 4; ++i)
+              v[i] = f2bf_pair(fmaxf(acc[b][8 * j + 2 * i] + bv[2 * i], 0.0f),
+                               fmaxf(acc[b][8 * j + 2 * i + 1] + bv[2 * i + 1], 0.0f));
           } else {
-            uint16_t m[8];
-            __builtin_memcpy(m, &mask[b][j], 16);
+            const uint32_t m[4] = {mask[b][j].x, mask[b][j].y, mask[b][j].z, mask[b][j].w};
 #pragma unroll
-            for (int i = 0; i < 8; ++i) q[i] = bf_positive(m[i]) ? f2bf(acc[b][8 * j + i]) : (uint16_t)0;
+            for (int i = 0; i < 4; ++i) {
+              // a ReLU's output is positive or zero, so both tests are on the bits
+              const uint32_t lo = bf_positive((uint16_t)m[i]) ? 0xffffu : 0u;
+              const uint32_t hi = bf_positive((uint16_t)(m[i] >> 16)) ? 0xffff0000u : 0u;
+              v[i] = f2bf_pair(acc[b][8 * j + 2 * i], acc[b][8 * j + 2 * i + 1]) & (lo | hi);
+            }
           }
-          typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-          u32x4 v;
-          __builtin_memcpy(&v, q, 16);
           __builtin_amdgcn_raw_buffer_store_b128(v, C, at_out[b][j], 0, 0);
         }
     }
@@ -279,33 +293,40 @@ struct WgradArgs {
 };
 
 // Sums of a workgroup's tiles: part[kc][co] = sum_p col(X)[p][kc] G[p][co], and
-// the column sums of G (the bias gradient) in row bias_row.  Nine waves, one
-// tap each; CIB x COB blocks of 32 x 32 (input x output channels) a wave.
+// the column sums of G (the bias gradient) in row bias_row.  Three waves, one
+// row of taps each, for every one of the CIB x COB blocks of 32 x 32 (input x
+// output) channels: twelve at 64 x 64, three on every SIMD (nine waves of a
+// tap each left one SIMD with three and the others with two).
 //
 // Both operands run along pixels, the outer dimension of NHWC: they are
 // read from row-major LDS tiles with the transposing ds_read_b64_tr_b16 (16
 // lanes fetch 4 pixels x 16 channels and each receives one channel's 4
 // pixels), 16 pixels of a tile row per MFMA step.  Pixels lie 64 or 192 bytes
-// apart, so the 4 pixels x 32 channels of 32 lanes cover all 64 banks.  A step's
-// four reads of 512 bytes for four MFMAs keep the LDS (113 bytes a clock for
-// 8-byte reads) as busy as the matrix cores; a tile's border is staged once
-// for all nine taps.  The next tile is loaded while this one is multiplied.
+// apart, so the 4 pixels x 32 channels of 32 lanes cover all 64 banks (2.7 clocks
+// a wave's read; 4.2 at pitches of 64, 68, 72 or 80 elements).  A tile's border
+// is staged once for all nine taps.  The next tile is loaded while this one is
+// multiplied.
+// Measured at 16 x 128^2, 64 to 64 channels: 31 us (64 images: 96 us, 2.8 TB/s),
+// the general matrix kernel before 74 us; a second tile in flight spilled
+// (35 us), nine waves of one tap each took 32 us (64 images: 113 us).
 template <int CIB, int COB>
-__global__ __launch_bounds__(576) void k_wgrad(WgradArgs g) {
+__global__ __launch_bounds__(192 * CIB * COB) void k_wgrad(WgradArgs g) {
   constexpr int TH = 8, PIX = (TH + 2) * kTileP, PIXG = TH * kTile;
   constexpr int PA = CIB == 1 ? 32 : 96, PG = COB == 1 ? 32 : 96;  // elements between pixels
   constexpr int UA = 4 * CIB, UG = 4 * COB;                        // 8-channel chunks staged per pixel
-  constexpr int PERA = (PIX * UA + 575) / 576, PERG = (PIXG * UG + 575) / 576;
+  constexpr int NT = 192 * CIB * COB;
+  constexpr int PERA = (PIX * UA + NT - 1) / NT, PERG = (PIXG * UG + NT - 1) / NT;
   constexpr int BUF = PIX * PA + PIXG * PG;
   __shared__ __attribute__((aligned(16))) uint16_t tile[2][BUF];
-  const int tap = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int dy = wave % 3, ci = wave / 3 % CIB, cj = wave / 3 / CIB;  // tap row, block of channels
   typedef short s4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) s4 lds_s4;
   // transposing read: lane l supplies pixel 8 (l / 32) + (l / 4) % 4, channels
   // 16 ((l / 16) % 2) + 4 (l % 4) .. + 3, and receives channel l % 32 of pixels
   // 8 (l / 32) .. + 3 (the second read: 4 pixels on)
   const int pix = 8 * (lane >> 5) + ((lane >> 2) & 3), chan = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const int at_a = ((tap / 3) * kTileP + tap % 3 + pix) * PA + chan, at_g = PIX * PA + pix * PG + chan;
+  const int at_a = (dy * kTileP + pix) * PA + 32 * ci + chan, at_g = PIX * PA + pix * PG + 32 * cj + chan;
   auto operand = [&](uint16_t* at, int pitch) {
     const s4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)at);
     const s4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)(at + 4 * pitch));
@@ -314,39 +335,46 @@ __global__ __launch_bounds__(576) void k_wgrad(WgradArgs g) {
     __builtin_memcpy((char*)&v + 8, &hi, 8);
     return v;
   };
-  uint4 ra[PERA], rg[PERG];
-  float bias[8] = {};  // 8 channels of the thread's chunk (576 is a multiple of UG)
+  uint4 r[PERA + PERG];
+  float bias[8] = {};  // 8 channels of the thread's chunk (NT is a multiple of UG)
   auto fetch = [&](int t) {
     const int img = t / (g.tiles_x * g.tiles_y), rest = t - img * (g.tiles_x * g.tiles_y), ty = rest / g.tiles_x;
     const int y0 = ty * TH, x0 = (rest - ty * g.tiles_x) * kTile;
+    // offsets past the image read zeros
+    const int bytes_a = g.H * g.W * g.cp * 2, bytes_g = g.H * g.W * g.cpg * 2;
+    const __amdgpu_buffer_rsrc_t X = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(g.X + (int64_t)img * g.H * g.W * g.cp), (short)0, bytes_a, 0x00020000);
+    const __amdgpu_buffer_rsrc_t G = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(g.G + (int64_t)img * g.H * g.W * g.cpg), (short)0, bytes_g, 0x00020000);
 #pragma unroll
     for (int k = 0; k < PERA; ++k) {
-      const int i = k * 576 + threadIdx.x, px = i / UA, ch = i % UA;
+      const int i = k * NT + threadIdx.x, px = i / UA, ch = i % UA;
       const int y = y0 + px / kTileP - 1, x = x0 + px % kTileP - 1;
-      ra[k] = make_uint4(0, 0, 0, 0);
-      if (px < PIX && ch * 8 < g.cp && y >= 0 && y < g.H && x >= 0 && x < g.W)
-        ra[k] = *(const uint4*)(g.X + (((int64_t)img * g.H + y) * g.W + x) * g.cp + ch * 8);
+      const bool in = px < PIX && ch * 8 < g.cp && (unsigned)y < (unsigned)g.H && (unsigned)x < (unsigned)g.W;
+      const auto v = __builtin_amdgcn_raw_buffer_load_b128(X, in ? (y * g.W + x) * (g.cp * 2) + ch * 16 : bytes_a, 0, 0);
+      __builtin_memcpy(&r[k], &v, 16);
     }
 #pragma unroll
     for (int k = 0; k < PERG; ++k) {
-      const int i = k * 576 + threadIdx.x, px = i / UG, ch = i % UG;
+      const int i = k * NT + threadIdx.x, px = i / UG, ch = i % UG;
       const int y = y0 + px / kTile, x = x0 + px % kTile;
-      rg[k] = make_uint4(0, 0, 0, 0);
-      if (px < PIXG && ch * 8 < g.cpg && y < g.H && x < g.W)
-        rg[k] = *(const uint4*)(g.G + (((int64_t)img * g.H + y) * g.W + x) * g.cpg + ch * 8);
+      const bool in = px < PIXG && ch * 8 < g.cpg && y < g.H && x < g.W;
+      const auto v = __builtin_amdgcn_raw_buffer_load_b128(G, in ? (y * g.W + x) * (g.cpg * 2) + ch * 16 : bytes_g, 0, 0);
+      __builtin_memcpy(&r[PERA + k], &v, 16);
     }
   };
   auto stage = [&](uint16_t* to) {
 #pragma unroll
     for (int k = 0; k < PERA; ++k) {
-      const int i = k * 576 + threadIdx.x, px = i / UA;
-      if (px < PIX) *(uint4*)(to + px * PA + i % UA * 8) = ra[k];
+      const int i = k * NT + threadIdx.x, px = i / UA;
+      if (px < PIX) *(uint4*)(to + px * PA + i % UA * 8) = r[k];
     }
 #pragma unroll
     for (int k = 0; k < PERG; ++k) {
-      const int i = k * 576 + threadIdx.x, px = i / UG;
-      if (px < PIXG) *(uint4*)(to + PIX * PA + px * PG + i % UG * 8) = rg[k];
-      const uint32_t w[4] = {rg[k].x, rg[k].y, rg[k].z, rg[k].w};
+      const int i = k * NT + threadIdx.x, px = i / UG;
+      if (px < PIXG) *(uint4*)(to + PIX * PA + px * PG + i % UG * 8) = r[PERA + k];
+      const uint4 v = r[PERA + k];
+      const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         bias[2 * q] += __uint_as_float(w[q] << 16);
@@ -354,11 +382,10 @@ __global__ __launch_bounds__(576) void k_wgrad(WgradArgs g) {
       }
     }
   };
-  f32x16 acc[CIB][COB];
+  f32x16 acc[3];
 #pragma unroll
-  for (int i = 0; i < CIB; ++i)
-    for (int j = 0; j < COB; ++j)
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+  for (int dx = 0; dx < 3; ++dx)
+    for (int i = 0; i < 16; ++i) acc[dx][i] = 0.0f;
   int t = blockIdx.x, cur = 0;
   if (t < g.tiles) {
     fetch(t);
@@ -368,42 +395,49 @@ __global__ __launch_bounds__(576) void k_wgrad(WgradArgs g) {
   for (; t < g.tiles; t += gridDim.x, cur ^= 1) {
     const bool more = t + (int)gridDim.x < g.tiles;
     if (more) fetch(t + gridDim.x);
+    uint16_t* in = tile[cur];
 #pragma unroll
     for (int y = 0; y < TH; ++y) {
-      bf16x8 a[CIB], b[COB];
+      const bf16x8 b = operand(in + at_g + y * kTile * PG, PG);
 #pragma unroll
-      for (int i = 0; i < CIB; ++i) a[i] = operand(tile[cur] + at_a + y * kTileP * PA + 32 * i, PA);
-#pragma unroll
-      for (int j = 0; j < COB; ++j) b[j] = operand(tile[cur] + at_g + y * kTile * PG + 32 * j, PG);
-#pragma unroll
-      for (int i = 0; i < CIB; ++i)
-#pragma unroll
-        for (int j = 0; j < COB; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+      for (int dx = 0; dx < 3; ++dx) {
+        const bf16x8 a = operand(in + at_a + (y * kTileP + dx) * PA, PA);
+        acc[dx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[dx], 0, 0, 0);
+      }
     }
+    // schedule: the 8 LDS reads of a row a row ahead of its 3 products
+    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);
+#pragma unroll
+    for (int y = 1; y < TH; ++y) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 3, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
     if (more) stage(tile[cur ^ 1]);
     __syncthreads();
   }
   float* part = g.part + (int64_t)blockIdx.x * g.stride;
 #pragma unroll
-  for (int i = 0; i < CIB; ++i)
+  for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-    for (int j = 0; j < COB; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        // accumulator layout: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
-        const int c = 32 * i + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), co = 32 * j + (lane & 31);
-        if (c < g.cp && co < g.cpg) part[(int64_t)(tap * g.cp + c) * g.cpg + co] = acc[i][j][r];
-      }
+    for (int r = 0; r < 16; ++r) {
+      // accumulator layout: register r of lane l holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+      const int c = 32 * ci + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3), co = 32 * cj + (lane & 31);
+      if (c < g.cp && co < g.cpg) part[(int64_t)((3 * dy + dx) * g.cp + c) * g.cpg + co] = acc[dx][r];
+    }
   // column sums of G: the threads of a chunk added in thread order
   float* sums = (float*)tile[0];
-  static_assert(sizeof(tile) >= 576 * 8 * sizeof(float), "bias sums fit the tile");
+  static_assert(sizeof(tile) >= NT * 8 * sizeof(float), "bias sums fit the tile");
 #pragma unroll
   for (int q = 0; q < 8; ++q) sums[threadIdx.x * 8 + q] = bias[q];
   __syncthreads();
   if ((int)threadIdx.x < g.cpg) {
     float v = 0.0f;
-    for (int k = threadIdx.x / 8; k < 576; k += UG) v += sums[k * 8 + threadIdx.x % 8];
+    for (int k = threadIdx.x / 8; k < NT; k += UG) v += sums[k * 8 + threadIdx.x % 8];
     part[(int64_t)g.bias_row * g.cpg + threadIdx.x] = v;
   }
 }
@@ -620,10 +654,10 @@ static int wgrad(WgradArgs a, int n, int H, int W, hipStream_t s) {
   a.tiles_y = (H + 7) / 8;
   a.tiles = n * a.tiles_x * a.tiles_y;
   const int splits = std::min(a.tiles, kMaxSplits);
-  if (a.cp > 32 && a.cpg > 32) hipLaunchKernelGGL((k_wgrad<2, 2>), dim3(splits), dim3(576), 0, s, a);
-  else if (a.cp > 32) hipLaunchKernelGGL((k_wgrad<2, 1>), dim3(splits), dim3(576), 0, s, a);
-  else if (a.cpg > 32) hipLaunchKernelGGL((k_wgrad<1, 2>), dim3(splits), dim3(576), 0, s, a);
-  else hipLaunchKernelGGL((k_wgrad<1, 1>), dim3(splits), dim3(576), 0, s, a);
+  if (a.cp > 32 && a.cpg > 32) hipLaunchKernelGGL((k_wgrad<2, 2>), dim3(splits), dim3(768), 0, s, a);
+  else if (a.cp > 32) hipLaunchKernelGGL((k_wgrad<2, 1>), dim3(splits), dim3(384), 0, s, a);
+  else if (a.cpg > 32) hipLaunchKernelGGL((k_wgrad<1, 2>), dim3(splits), dim3(384), 0, s, a);
+  else hipLaunchKernelGGL((k_wgrad<1, 1>), dim3(splits), dim3(192), 0, s, a);
   return splits;
 }
 

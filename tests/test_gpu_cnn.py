@@ -82,6 +82,15 @@ def test_cnn_matches_oracle(L, C, H, W, n):
     net.close()
 
 
+# Where the 16 x 16 and 8 x 16 pixel tiles and the blocks of 32 channels end:
+# one tile exactly, one pixel more, one pixel, less than a tile; channels on
+# both sides of 32; and more tiles than workgroups.
+@pytest.mark.parametrize("L,C,H,W,n", [(3, 64, 16, 16, 1), (3, 64, 17, 33, 32), (2, 40, 7, 50, 16), (4, 24, 15, 9, 32),
+                                       (3, 32, 8, 16, 9), (2, 56, 1, 1, 32), (3, 48, 96, 112, 8)])
+def test_cnn_at_tile_edges(L, C, H, W, n):
+    test_cnn_matches_oracle(L, C, H, W, n)
+
+
 def test_cnn_deterministic_and_adam():
     L, C, H, W, n = 4, 32, 16, 16, 4
     p, x, t, sc = _setup(L, C, H, W, n, seed=9)
