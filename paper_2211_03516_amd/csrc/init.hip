@@ -24,33 +24,130 @@
 
 namespace vam {
 
-constexpr int kRowTile = 256;
-
-// One block per projection row; the row is staged in LDS and each thread
-// convolves outputs u = threadIdx.x, threadIdx.x + blockDim.x, ...
-__global__ __launch_bounds__(kRowTile) void k_ramlak(const float* __restrict__ in, float* __restrict__ out, int nu,
-                                                     float tau, int clip) {
-  extern __shared__ float row[];  // [nu] row values, then [nu / 2] odd-tap weights
-  float* hodd = row + nu;
-  const int64_t base = (int64_t)blockIdx.x * nu;
-  for (int u = threadIdx.x; u < nu; u += blockDim.x) row[u] = in[base + u];
-  for (int m = threadIdx.x; 2 * m + 1 < nu; m += blockDim.x) {
-    const float n = (float)(2 * m + 1);
-    hodd[m] = -1.0f / ((float)(M_PI * M_PI) * n * n);
-  }
-  __syncthreads();
-  for (int u = threadIdx.x; u < nu; u += blockDim.x) {
-    float acc = 0.25f * row[u];
-    for (int n = 1; n < nu; n += 2) {
-      const float hn = hodd[n >> 1];
-      float s = 0.0f;
-      if (u - n >= 0) s += row[u - n];
-      if (u + n < nu) s += row[u + n];
-      acc = fmaf(hn, s, acc);
+// out = in * h for 32 rows and 64 NB columns of them: a product of the rows with
+// the banded (Toeplitz) matrix of h.  h is zero at even distances, so even
+// columns take only odd ones and the other way round: with u = 2 a + e and
+// u' = 2 b + 1 - e, out(u) = in(u) / 4 + sum_b T(a - b + e) in(u'), where
+// T(d) = h[2 d - 1] (h is even).
+//
+// What bounds it: n_u / 2 multiplications a value, 6 GFLOP for 92160 rows of
+// 256 (39 us at the rate of a large FP32 product; moving the rows takes 36 us).
+// One thread an output read two values and a weight from LDS for each pair of
+// taps, 660 us.  Here the FP32 matrix instructions multiply: a wave has 32 rows
+// x 64 columns (even and odd), and per 8 products of 32 x 32 x 2 it reads two
+// times four values and five weights a lane, a third of the LDS's time.
+// 85 us; 12000 rows of 1024 143 us.
+//
+// Precision: the filter all but cancels the value itself and its neighbours,
+// so a sum over ascending b carries large partial sums through most of its
+// roundings (six times the error of adding pairs from the middle outwards).
+// The kNear nearest pairs are therefore added apart, from the middle outwards,
+// and the matrix instructions add the rest from both ends towards the middle.
+// The error against FP64 is then that of adding pairs, or less, for rows of 64
+// to 1000 values of noise, smooth bumps, boxes and waves.
+//
+// Columns go in groups of 512 (above that NB is 8 and blockIdx.y is the group)
+// and so does the sum over u', its own group last.  Rows in LDS are K + 12
+// floats apart, so 16 rows read at 16 bytes a lane cover all 64 banks.
+constexpr int kRampRows = 32, kRampMax = 8, kNear = 4;
+__device__ inline constexpr float ramp_weight(int m) {
+  const float n = (float)(2 * m + 1);
+  return -1.0f / ((float)(M_PI * M_PI) * n * n);
+}
+template <int NB>
+__global__ __launch_bounds__(64 * NB) void k_ramlak(const float* __restrict__ in, float* __restrict__ out, int n_rows,
+                                                    int nu, float tau, int clip) {
+  typedef float f32x16 __attribute__((ext_vector_type(16)));
+  constexpr int K = 32 * NB, P = K + 12;  // columns of one parity in a group; row pitch
+  // columns of one parity of a group with four more on each side (the last 32
+  // floats put a wave's even and odd columns into different banks)
+  __shared__ __attribute__((aligned(16))) float x[2][kRampRows * P + 32];
+  __shared__ float ramp[2 * K];  // T(i - (K - 1) + (group - c) K), zero for the nearest
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, col = lane & 31, half = lane >> 5;
+  const int r0 = blockIdx.x * kRampRows, group = blockIdx.y, groups = gridDim.y;
+  const bool any = 2 * K * group + 64 * wave < nu;
+  f32x16 acc[2];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[0][i] = acc[1][i] = 0.0f;
+  for (int i = 0; i < groups; ++i) {
+    const int c = i < group ? i : groups - 1 - (i - group), u0 = 2 * K * c;
+    if (i) __syncthreads();
+    // (the reads past the last row or column are of the last one)
+#pragma unroll 4
+    for (int r = wave; r < kRampRows; r += NB) {
+      const float* src = in + (int64_t)min(r0 + r, n_rows - 1) * nu;
+      float v[NB];
+#pragma unroll
+      for (int k = 0; k < NB; ++k) v[k] = src[min(u0 + 64 * k + lane, nu - 1)];
+#pragma unroll
+      for (int k = 0; k < NB; ++k)
+        x[lane & 1][r * P + 4 + 32 * k + (lane >> 1)] = u0 + 64 * k + lane < nu ? v[k] : 0.0f;
     }
-    acc /= tau;
-    out[base + u] = clip ? fmaxf(acc, 0.0f) : acc;
+    if (c == group)
+      for (int e = threadIdx.x; e < 16 * kRampRows; e += 64 * NB) {
+        const int r = e >> 4, at = (e & 15) < 8 ? (e & 15) : 2 * K + (e & 15), u = u0 - 8 + at;
+        x[at & 1][r * P + (at >> 1)] = u >= 0 && u < nu ? in[(int64_t)min(r0 + r, n_rows - 1) * nu + u] : 0.0f;
+      }
+    for (int e = threadIdx.x; e < 2 * K; e += 64 * NB) {
+      const int d = e - (K - 1) + (group - c) * K, m = d > 0 ? d - 1 : -d;
+      ramp[e] = m < kNear ? 0.0f : ramp_weight(m);
+    }
+    __syncthreads();
+    if (!any) continue;
+    const float *xe = x[0] + col * P + 4 + 4 * half, *xo = x[1] + col * P + 4 + 4 * half;
+    const float* t = ramp + 32 * wave + col - 4 * half + K - 1;
+    // 8 columns at a time, of the two ends left the one further from the wave's 32
+    const int middle = 2 * (32 * wave + (group - c) * K + 12);
+    for (int lo = 0, hi = (min(K, (nu + 1) / 2 - K * c) - 1) & ~7; lo <= hi;) {
+      const bool left = middle >= lo + hi;
+      const int b = left ? lo : hi;
+      lo += left ? 8 : 0;
+      hi -= left ? 0 : 8;
+      const float4 o = *(const float4*)(xo + b), e = *(const float4*)(xe + b);
+      const float vo[4] = {o.x, o.y, o.z, o.w}, ve[4] = {e.x, e.y, e.z, e.w};
+      float w[5];
+#pragma unroll
+      for (int j = 0; j < 5; ++j) w[j] = t[1 - j - b];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(vo[j], w[j + 1], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(ve[j], w[j], acc[1], 0, 0, 0);
+      }
+    }
   }
+  if (!any) return;
+  const int u = 2 * (K * group + 32 * wave + col);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int r = 8 * (i >> 2) + 4 * half + (i & 3);
+    const float *e = x[0] + r * P + 4 + 32 * wave + col, *o = x[1] + r * P + 4 + 32 * wave + col;
+    float v[2] = {0.25f * e[0], 0.25f * o[0]};
+#pragma unroll
+    for (int m = 0; m < kNear; ++m) {
+      v[0] = fmaf(ramp_weight(m), o[-1 - m] + o[m], v[0]);
+      v[1] = fmaf(ramp_weight(m), e[-m] + e[1 + m], v[1]);
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      v[k] = (v[k] + acc[k][i]) / tau;
+      if (clip) v[k] = fmaxf(v[k], 0.0f);
+    }
+    if (r0 + r >= n_rows) continue;
+    float* to = out + (int64_t)(r0 + r) * nu + u;
+    if (u + 1 < nu)
+      __builtin_memcpy(to, v, 8);
+    else if (u < nu)
+      *to = v[0];
+  }
+}
+
+// (NB of the narrowest kernel that has all columns, or the widest)
+template <int NB>
+void launch_ramlak(const float* in, float* out, int n_rows, int nu, float tau, int clip, hipStream_t s) {
+  if constexpr (NB < kRampMax)
+    if (64 * NB < nu) return launch_ramlak<NB + 1>(in, out, n_rows, nu, tau, clip, s);
+  hipLaunchKernelGGL((k_ramlak<NB>), dim3((n_rows + kRampRows - 1) / kRampRows, (nu + 64 * NB - 1) / (64 * NB)),
+                     dim3(64 * NB), 0, s, in, out, n_rows, nu, tau, clip);
 }
 
 constexpr int kErrThreads = 256;
@@ -173,9 +270,7 @@ vam_status vam_ramlak_filter(const float* proj_in, float* proj_out, int32_t n_ro
   if (!(pitch > 0) || !std::isfinite(pitch)) return fail(VAM_ERR_INVALID_ARG, "pitch must be finite and > 0");
   if (proj_in == proj_out) return fail(VAM_ERR_INVALID_ARG, "in-place filtering is not supported");
   if (n_rows == 0) return VAM_OK;
-  hipLaunchKernelGGL(k_ramlak, dim3(n_rows), dim3(kRowTile), (n_u + n_u / 2 + 1) * sizeof(float), stream, proj_in,
-                     proj_out, n_u,
-                     (float)pitch, clip_negative);
+  launch_ramlak<1>(proj_in, proj_out, n_rows, n_u, (float)pitch, clip_negative, stream);
   VAM_HIP_TRY(hipGetLastError(), "launching the Ram-Lak filter");
   return VAM_OK;
 }

@@ -43,6 +43,26 @@ def test_ramlak_kernel_matches_definition():
             assert np.abs(got - ref).max() <= 1e-5 * max(np.abs(ref).max(), 1.0)
 
 
+# Both sides of the blocks of 32 rows, of 64 columns and of 512 columns.  Each
+# output adds at most n_u / 2 + 1 products in FP32 with up to two roundings
+# each, to which a weight adds four and the division by the pitch one: at most
+# n_u + 8 relative errors of 2^-24 on the sum of the products' magnitudes.
+@pytest.mark.parametrize("nu", [2, 63, 64, 65, 129, 192, 257, 321, 448, 511, 512, 513, 1089])
+def test_ramlak_at_block_edges(nu):
+    tau, n_rows = 0.8, (31, 32, 33, 1)[nu % 4]
+    rng = synth.SplitMix64(nu)
+    rows = (rng.uniform(n_rows * nu).reshape(n_rows, nu) - 0.3).astype(np.float32)
+    say("ramlak %d x %d" % (n_rows, nu))
+    got = vam.ramlak_filter(torch.from_numpy(rows).to(DEV), pitch=tau, clip_negative=False).cpu().numpy()
+    d = np.abs(np.arange(nu)[:, None] - np.arange(nu)[None, :])
+    h = np.where(d == 0, 0.25, np.where(d % 2 == 1, -1.0 / (np.pi * np.maximum(d, 1)) ** 2, 0.0)) / tau
+    x = rows.astype(np.float64)
+    assert np.abs(x @ h - ramlak.ramlak_filter(x, tau, clip_negative=False)).max() <= 1e-12
+    assert np.all(np.abs(got - x @ h) <= (nu + 8) * 2.0 ** -24 * (np.abs(x) @ np.abs(h)))
+    clipped = vam.ramlak_filter(torch.from_numpy(rows).to(DEV), pitch=tau, clip_negative=True).cpu().numpy()
+    assert np.array_equal(clipped, np.maximum(got, 0.0))
+
+
 def test_dose_error_matches_fp64_definition():
     rng = synth.SplitMix64(32)
     n = 100003
