@@ -553,6 +553,7 @@ struct BoxParams {
   const int* box_supp; // fixed-point deposit: per-box n_supp
   int wxy_max, wz_max;
   int npix;            // n_u * n_v
+  unsigned per_npix;   // 2^32 / npix, rounded down (at most 2^32 - 1)
   int px, py, pz;
   double w_coef;       // step / n_pupil: no sample weight exceeds it times |P|
   // one-angle forward: angle a is member a / turn_stride of representative
@@ -572,6 +573,7 @@ static BoxParams box_params(const vam_geometry* h, const SegTable& t, int na, in
   Bp.box_supp = h->box_supp;
   footprint_bound(h->boxes.B, h->px, h->py, h->pz, Bp.wxy_max, Bp.wz_max);
   Bp.npix = h->desc.n_u * h->desc.n_v;
+  Bp.per_npix = (unsigned)std::min<uint64_t>((uint64_t(1) << 32) / (unsigned)Bp.npix, 0xffffffffu);
   Bp.px = h->px;
   Bp.py = h->py;
   Bp.pz = h->pz;
@@ -579,6 +581,13 @@ static BoxParams box_params(const vam_geometry* h, const SegTable& t, int na, in
   Bp.turn_stride = h->desc.n_angles;
   Bp.member0 = 0;
   return Bp;
+}
+
+// Pixel of a segment's slot (rank * n_rays + pupil * npix + pixel): slot modulo
+// npix, by the reciprocal (the quotient is exact or one too small).
+__device__ inline unsigned pixel_of(const BoxParams& Bp, unsigned slot) {
+  const unsigned r = slot - __umulhi(slot, Bp.per_npix) * (unsigned)Bp.npix;
+  return min(r, r - (unsigned)Bp.npix);
 }
 
 // Work order of the (box, angle) workgroups.
@@ -657,6 +666,36 @@ __device__ inline Foot footprint(const BoxParams& Bp, int64_t box, double c, dou
 // Number of the footprint's first cell in the padded grid.
 __device__ inline int64_t tile_base(const BoxParams& Bp, const Foot& f) {
   return ((int64_t)f.Z0 * Bp.py + f.Y0) * Bp.px + f.X0;
+}
+
+// A footprint's cells among NT lanes: a lane has one column (x, y) and every
+// kSlices-th slice of it, so the divisions and the comparisons in x and y are
+// made once, the slices' addresses are scalar and their LDS offsets constant.
+// (With the cells dealt out one after the other their numbers cost 50 clocks of
+// vector work for 64 cells, an eighth of a forward with 1300 segments a box.)
+template <int COL, int NT>
+constexpr int kSlices = NT >= COL ? NT / COL : 1;
+
+// Loads the footprint's cells of a padded volume; put(i, v) takes cell i of the
+// LDS tile (slice pitch SZ), zero outside the footprint.  All loads of a column
+// are in flight before the first is waited for.
+template <int SY, int SZ, int WZ, int NT, class T, class F>
+__device__ inline void load_tile(const T* tile, int px, int py, const Foot& f, F put) {
+  constexpr int COL = SY * SY, G = kSlices<COL, NT>, PER = (WZ + G - 1) / G;
+  for (int i = threadIdx.x; i < G * COL; i += NT) {
+    const int zg = G == 1 ? 0 : i / COL, c = i - zg * COL, y = c / SY, x = c - y * SY;
+    const bool in = x < f.WX && y < f.WY;
+    const unsigned from = (unsigned)((zg * py + y) * px + x);
+    T v[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+      v[k] = T{};
+      if (in && zg + k * G < f.WZ) v[k] = (tile + (int64_t)k * G * py * px)[from];
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k)
+      if (WZ % G == 0 || zg + k * G < WZ) put(zg * SZ + c + k * G * SZ, v[k]);
+  }
 }
 
 // Middle sample and step of a segment in footprint cells at angle (c, s);
@@ -831,8 +870,47 @@ __device__ inline float march_forward_cached(const uint32_t* sv, const SegPos& g
   return S;
 }
 
+// Number of the cell at whole coordinates: in FP32 (exact below 2^24) with one
+// conversion, which costs twice an addition, where integers took three and two
+// multiplications of that cost.
+template <int SY, int SZ>
+__device__ inline unsigned cell_number(float x, float y, float z) {
+  return (unsigned)fmaf(z, (float)SZ, fmaf(y, (float)SY, x));
+}
+
+// The same sum from FP32 cells that hold a voxel and its x neighbour (float2).
+template <int SY, int SZ, bool CLAMP>
+__device__ inline float march_forward_cells(const float2* sv, const SegPos& g, float hx, float hy, float hz,
+                                            float r_hi, float r_lo) {
+  float S = 0.0f;
+  unsigned cur = 0xffffffffu;
+  float2 w[4] = {};
+  for (float kf = g.k1; kf >= g.k0; kf -= 1.0f) {
+    const float x = coord<CLAMP>(kf, g.dx, g.px, hx);
+    const float y = coord<CLAMP>(kf, g.dy, g.py, hy);
+    const float z = coord<CLAMP>(kf, g.dz, g.pz, hz);
+    const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y), fz = __builtin_amdgcn_fractf(z);
+    const unsigned o = cell_number<SY, SZ>(x - fx, y - fy, z - fz);
+    if (o != cur) {
+      cur = o;
+      w[0] = sv[o];
+      w[1] = sv[o + SY];
+      w[2] = sv[o + SZ];
+      w[3] = sv[o + SZ + SY];
+    }
+    float c[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) c[j] = fmaf(fx, w[j].y - w[j].x, w[j].x);
+    const float c0 = fmaf(fy, c[1] - c[0], c[0]);
+    const float c1 = fmaf(fy, c[3] - c[2], c[2]);
+    const float val = fmaf(fz, c1 - c0, c0);
+    S = fmaf(S, r_hi, fmaf(S, r_lo, val));
+  }
+  return S;
+}
+
 // March modes of the fixed-point box forward (k_forward_box's MODE).
-constexpr int kMarchOne = 1, kMarchPair = 2, kMarchCached = 3;
+constexpr int kMarchOne = 1, kMarchPair = 2, kMarchCached = 3, kMarchCells = 4;
 
 // Fixed-point forward (the default).  A pixel's value is a sum of segment
 // partials pw.w S, each at most (step / n_pupil) n V in magnitude (sample
@@ -854,37 +932,41 @@ constexpr int kMarchOne = 1, kMarchPair = 2, kMarchCached = 3;
 // S_even + r S_odd); their samples are half a voxel apart, so they often
 // read the same LDS words, which the LDS serves as one broadcast.
 // kMarchCached: one lane, the current cell's LDS words kept in registers.
+// kMarchCells (the default): the same with FP32 cells of a voxel and its x
+// neighbour, so a sample's corners are four 8-byte reads (7.7 clocks for 64
+// unrelated lanes, as much as one of 4 bytes) and 16-bit values are widened once
+// a cell.  Bound by vector issue and LDS reads, each about 70 % of the time.
+template <int MODE>
+constexpr int kForwardThreads = MODE == kMarchCells ? 512 : 256;
 template <int B, int FMT, bool FX, int MODE>
-__global__ __launch_bounds__(256) void k_forward_box(MarchParams P, BoxParams Bp, const uint32_t* __restrict__ vol,
+__global__ __launch_bounds__(kForwardThreads<MODE>) void k_forward_box(MarchParams P, BoxParams Bp, const uint32_t* __restrict__ vol,
                                                      float* __restrict__ part, int64_t slots,
                                                      unsigned long long* __restrict__ pfx,
                                                      const unsigned* __restrict__ vmax, double fx_coef) {
   constexpr int SY = Fixed<B>::WXY, SZ = SY * SY, NC = SZ * Fixed<B>::WZ;
-  __shared__ uint32_t sv[NC];
+  using Cell = std::conditional_t<MODE == kMarchCells, float2, uint32_t>;
+  __shared__ Cell sv[NC];
   int b, a;
   if (!work_item(Bp.nboxes, Bp.na, Bp.xcd, b, a)) return;
   const int member = (P.a0 + a) / Bp.turn_stride;
   const double2 cs = P.cs[P.a0 + a - member * Bp.turn_stride];
   vol += (int64_t)(member - Bp.member0) * Bp.px * Bp.py * Bp.pz;
   const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
-  {
-    // the tile's loads in two batches, each in flight before it is waited for
-    // (offsets inside a tile, at most 18 slices, fit 32 bits)
-    const uint32_t* tile = vol + tile_base(Bp, f);
-    constexpr int NT = 256, PER = (NC + NT - 1) / NT, HALF = (PER + 1) / 2;
-    for (int k0 = 0; k0 < PER; k0 += HALF) {
-      uint32_t v[HALF];
-#pragma unroll
-      for (int k = 0; k < HALF; ++k) {
-        const int i = (k0 + k) * NT + threadIdx.x, z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
-        v[k] = 0u;
-        if (x < f.WX && y < f.WY && z < f.WZ) v[k] = tile[(unsigned)((z * Bp.py + y) * Bp.px + x)];
-      }
-#pragma unroll
-      for (int k = 0; k < HALF; ++k)
-        if ((k0 + k) * NT + (int)threadIdx.x < NC) sv[(k0 + k) * NT + threadIdx.x] = v[k];
-    }
-  }
+  load_tile<SY, SZ, Fixed<B>::WZ, kForwardThreads<MODE>>(
+      vol + tile_base(Bp, f), Bp.px, Bp.py, f, [&](int i, uint32_t v) {
+        if constexpr (MODE != kMarchCells) {
+          sv[i] = v;
+        } else if constexpr (FMT == kVolF32) {
+          // (the last cell of a row gets a neighbour that no sample reads)
+          sv[i].x = __uint_as_float(v);
+          if (i > 0) sv[i - 1].y = __uint_as_float(v);
+        } else if constexpr (FMT == kVolBF16Pairs) {
+          sv[i] = make_float2(__uint_as_float(v << 16), __uint_as_float(v & 0xffff0000u));
+        } else {
+          sv[i] = make_float2((float)__builtin_bit_cast(_Float16, (uint16_t)v),
+                              (float)__builtin_bit_cast(_Float16, (uint16_t)(v >> 16)));
+        }
+      });
   __syncthreads();
   const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
   const float c = (float)cs.x, s = (float)cs.y, sc = P.step * c, ss = P.step * s;
@@ -904,7 +986,10 @@ __global__ __launch_bounds__(256) void k_forward_box(MarchParams P, BoxParams Bp
     const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
     const SegPos g = seg_pos(pw, dn, __float_as_int(dn.w), f, c, s, sc, ss, P.step);
     float S;
-    if constexpr (MODE == kMarchCached) {
+    if constexpr (MODE == kMarchCells) {
+      S = seg_inside(g, hx, hy, hz) ? march_forward_cells<SY, SZ, false>(sv, g, hx, hy, hz, P.r_hi, P.r_lo)
+                                    : march_forward_cells<SY, SZ, true>(sv, g, hx, hy, hz, P.r_hi, P.r_lo);
+    } else if constexpr (MODE == kMarchCached) {
       S = seg_inside(g, hx, hy, hz) ? march_forward_cached<SY, SZ, false, FMT>(sv, g, hx, hy, hz, P.r_hi, P.r_lo)
                                     : march_forward_cached<SY, SZ, true, FMT>(sv, g, hx, hy, hz, P.r_hi, P.r_lo);
     } else if constexpr (MODE == kMarchOne) {
@@ -924,9 +1009,8 @@ __global__ __launch_bounds__(256) void k_forward_box(MarchParams P, BoxParams Bp
     }
     const float v = pw.w * S;
     if constexpr (FX) {
-      // the slot rank * n_rays + pupil * npix + pixel, modulo npix, is the pixel
       if (part_of == 0 && finite && v != 0.0f)
-        atomicAdd(row + (unsigned)Bp.seg.idx[si] % (unsigned)Bp.npix,
+        atomicAdd(row + pixel_of(Bp, (unsigned)Bp.seg.idx[si]),
                   (unsigned long long)__double2ll_rn((double)v * scale));
     } else {
       out[Bp.seg.idx[si]] = v;
@@ -981,7 +1065,7 @@ __device__ inline void march_forward_turned(const typename CellVec<NQ>::T* sv, c
     const float y = coord<CLAMP>(kf, g.dy, g.py, hy);
     const float z = coord<CLAMP>(kf, g.dz, g.pz, hz);
     const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y), fz = __builtin_amdgcn_fractf(z);
-    const unsigned o = __umul24((unsigned)z, SZ) + __umul24((unsigned)y, SY) + (unsigned)x;
+    const unsigned o = cell_number<SY, SZ>(x - fx, y - fy, z - fz);
     if (o != cur) {
       cur = o;
 #pragma unroll
@@ -1054,7 +1138,7 @@ __global__ __launch_bounds__(NT) void k_forward_turned(
     MarchParams P, BoxParams Bp, const typename CellVec<NQ>::T* __restrict__ vol,
     unsigned long long* __restrict__ pfx, const unsigned* __restrict__ vmax, double fx_coef) {
   // slice pitch two cells longer than a slice: 69.7 against 71.0 ms at 256^3
-  constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY + 2, NC = SY * SY * Fixed<kBox>::WZ;
+  constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY + 2;
   using Vec = typename CellVec<NQ>::T;
   __shared__ Vec sv[SZ * Fixed<kBox>::WZ];
   int b, a;
@@ -1063,24 +1147,7 @@ __global__ __launch_bounds__(NT) void k_forward_turned(
   if (vm >= 0x7f800000u) return;  // a non-finite value: k_fx_store writes NaN
   const double2 cs = P.cs[P.a0 + a];
   const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
-  {
-    // every load of the tile in flight before the first is waited for
-    const Vec* tile = vol + tile_base(Bp, f);
-    constexpr int PER = (NC + NT - 1) / NT;
-    Vec v[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) {
-      const int i = k * NT + threadIdx.x, z = i / (SY * SY), rem = i - z * (SY * SY), y = rem / SY, x = rem - y * SY;
-      v[k] = Vec{};
-      if (x < f.WX && y < f.WY && z < f.WZ) v[k] = tile[(unsigned)((z * Bp.py + y) * Bp.px + x)];
-    }
-#pragma unroll
-    for (int k = 0; k < PER; ++k)
-      if ((k + 1) * NT <= NC || k * NT + (int)threadIdx.x < NC) {
-        const int i = k * NT + threadIdx.x, z = i / (SY * SY);
-        sv[i + z * (SZ - SY * SY)] = v[k];
-      }
-  }
+  load_tile<SY, SZ, Fixed<kBox>::WZ, NT>(vol + tile_base(Bp, f), Bp.px, Bp.py, f, [&](int i, const Vec& v) { sv[i] = v; });
   __syncthreads();
   const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
   const float c = (float)cs.x, s = (float)cs.y, sc = P.step * c, ss = P.step * s;
@@ -1101,8 +1168,7 @@ __global__ __launch_bounds__(NT) void k_forward_turned(
         march_forward_turned<SY, SZ, false, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
       else
         march_forward_turned<SY, SZ, true, NQ>(sv, g, hx, hy, hz, P.r_hi, P.r_lo, S);
-      // the slot rank * n_rays + pupil * npix + pixel, modulo npix, is the pixel
-      pixel = slot % (unsigned)Bp.npix;
+      pixel = pixel_of(Bp, slot);
 #pragma unroll
       for (int q = 0; q < NQ; ++q) sum[q] = (unsigned long long)__double2ll_rn((double)(pw.w * S[q]) * scale);
     }
@@ -1239,7 +1305,10 @@ struct FwdOut {
 template <int B, int FMT, bool FX>
 static void launch_forward_box_f(dim3 grid, hipStream_t s, const MarchParams& P, const BoxParams& Bp,
                                  const uint32_t* vol, const FwdOut& o) {
-  if (FX && o.mode == kMarchCached)
+  if (FX && o.mode == kMarchCells)
+    hipLaunchKernelGGL((k_forward_box<B, FMT, true, kMarchCells>), grid, dim3(kForwardThreads<kMarchCells>), 0, s, P,
+                       Bp, vol, o.part, o.slots, o.pfx, o.vmax, o.fx_coef);
+  else if (FX && o.mode == kMarchCached)
     hipLaunchKernelGGL((k_forward_box<B, FMT, true, kMarchCached>), grid, dim3(256), 0, s, P, Bp, vol, o.part,
                        o.slots, o.pfx, o.vmax, o.fx_coef);
   else if (FX && o.mode == kMarchPair)
@@ -1452,10 +1521,10 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
       BoxParams Bp = box_params(h, h->seg_fwd, last - first, h->xcd_forward);
       Bp.turn_stride = Q;
       Bp.member0 = together ? m0 : m;
-      // the loops are bound by their LDS reads (FP32) or VALU issue (16-bit
-      // pairs); keeping the cell's words in registers saves LDS reads for FP32
-      // and BF16, while FP16's mixed-precision FMA reads its word directly
-      const int mode = h->forward_lanes ? h->forward_lanes : (fmt == kVolF16Pairs ? kMarchOne : kMarchCached);
+      // (128^3, 60 of 180 angles, FP32: one lane 1.75 ms, its words in
+      // registers 1.47, FP32 cells 1.45; 64^3, 180 angles 0.51 and 0.48; FP16,
+      // 45 angles of 128^3: 1.16, 1.16, 1.14)
+      const int mode = h->forward_lanes ? h->forward_lanes : kMarchCells;
       const FwdOut o{nullptr, 0, pfx + (first - a0) * npix, h->vol_absmax, coef, mode};
       launch_forward_box_edge<true>(h->boxes.B, work_grid(h->n_boxes, Bp.na, Bp.xcd), s, march_params(h, first), Bp,
                                     fmt, together ? (const uint32_t*)vol : (const uint32_t*)h->vol_pad, o);
@@ -1594,13 +1663,14 @@ __device__ inline void flush8(int* acc, unsigned cur, const float* w) {
 template <int SY, int SZ, bool CLAMP>
 __device__ inline void march_deposit(int* acc, const SegPos& g, int zc, float e, float hx, float hy, float r_hi,
                                      float r_lo) {
-  auto cell_bytes = [](float x, float y) { return __umul24((unsigned)y, SY * 4) + (unsigned)x * 4; };
+  // at whole coordinates (see cell_number)
+  auto cell_bytes = [](float x, float y) { return (unsigned)fmaf(y, (float)(SY * 4), x * 4.0f); };
   acc += zc * SZ;
   const float pz = g.pz - (float)zc;
   float w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   // byte offset of the cell whose corners w holds, starting at the first
   // sample's (w is zero until its first add)
-  unsigned cur = cell_bytes(coord<CLAMP>(g.k0, g.dx, g.px, hx), coord<CLAMP>(g.k0, g.dy, g.py, hy));
+  unsigned cur = cell_bytes(floorf(coord<CLAMP>(g.k0, g.dx, g.px, hx)), floorf(coord<CLAMP>(g.k0, g.dy, g.py, hy)));
   // exact: a segment has fewer than 2^24 samples
   for (float kf = g.k0; kf <= g.k1; kf += 1.0f) {
     const float x = coord<CLAMP>(kf, g.dx, g.px, hx);
@@ -1609,7 +1679,7 @@ __device__ inline void march_deposit(int* acc, const SegPos& g, int zc, float e,
     const float z1 = e * fz, z0 = e - z1;
     const float y01 = z0 * fy, y00 = z0 - y01;
     const float y11 = z1 * fy, y10 = z1 - y11;
-    const unsigned ob = cell_bytes(x, y);
+    const unsigned ob = cell_bytes(x - fx, y - fy);
     const bool fl = ob != cur;
     if (fl) flush8<SY, SZ>(acc, cur, w);
     const float keep = fl ? 0.0f : 1.0f;
@@ -1680,12 +1750,16 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
   }
   __syncthreads();
   unsigned long long* tile = acc64 + tile_base(Bp, f);
-  for (int i = threadIdx.x; i < NC; i += blockDim.x) {
-    const int raw = acc[i];
-    if (raw == 0) continue;
-    const int z = i / SZ, rem = i - z * SZ, y = rem / SY, x = rem - y * SY;
-    if (x >= f.WX || y >= f.WY || z >= f.WZ) continue;
-    atomicAdd(tile + (unsigned)((z * Bp.py + y) * Bp.px + x), (unsigned long long)__double2ll_rn((double)raw * toG));
+  constexpr int COL = SY * SY, Z = kSlices<COL, NT>;
+  for (int i = threadIdx.x; i < Z * COL; i += NT) {
+    const int zg = Z == 1 ? 0 : i / COL, col = i - zg * COL, y = col / SY, x = col - y * SY;
+    if (x >= f.WX || y >= f.WY) continue;
+    for (int z = zg; z < f.WZ; z += Z) {
+      const int raw = acc[z * SZ + col];
+      if (raw != 0)
+        atomicAdd(tile + (int64_t)z * Bp.py * Bp.px + (unsigned)(y * Bp.px + x),
+                  (unsigned long long)__double2ll_rn((double)raw * toG));
+    }
   }
 }
 
@@ -1921,16 +1995,19 @@ __global__ __launch_bounds__(NT) void k_back_planes(MarchParams P, BoxParams Bp,
     else if (q == 2) { first = (Bp.py - 1 - Y) * Bp.px + (Bp.px - 1 - X); px = -1; py = -Bp.px; }
     else { first = X * Bp.px + (Bp.px - 1 - Y); px = Bp.px; py = -1; }
     unsigned long long* tile = acc64 + (int64_t)f.Z0 * Bp.py * Bp.px + first;
-    for (int i = threadIdx.x; i < SY * SY * Fixed<kBox>::WZ; i += NT) {
-      const int z = i / (SY * SY), rem = i - z * (SY * SY), hi = rem / SY, lo = rem - hi * SY;
+    constexpr int COL = SY * SY, Z = kSlices<COL, NT>;
+    for (int i = threadIdx.x; i < Z * COL; i += NT) {
+      const int zg = Z == 1 ? 0 : i / COL, rem = i - zg * COL, hi = rem / SY, lo = rem - hi * SY;
       const int x = q & 1 ? hi : lo, y = q & 1 ? lo : hi;
-      const unsigned long long w = acc[q / 2 * PLANE + z * SZ + y * SY + x];
-      int raw = (int)(uint32_t)w;
-      if (q & 1) raw = (int)(((long long)w - (long long)raw) >> 32);
-      if (raw == 0) continue;
-      if (x >= f.WX || y >= f.WY || z >= f.WZ) continue;
-      atomicAdd(tile + ((int64_t)z * Bp.py * Bp.px + y * py + x * px),
-                (unsigned long long)__double2ll_rn((double)raw * toG));
+      if (x >= f.WX || y >= f.WY) continue;
+      for (int z = zg; z < f.WZ; z += Z) {
+        const unsigned long long w = acc[q / 2 * PLANE + z * SZ + y * SY + x];
+        int raw = (int)(uint32_t)w;
+        if (q & 1) raw = (int)(((long long)w - (long long)raw) >> 32);
+        if (raw != 0)
+          atomicAdd(tile + (int64_t)z * Bp.py * Bp.px + (y * py + x * px),
+                    (unsigned long long)__double2ll_rn((double)raw * toG));
+      }
     }
   }
 }

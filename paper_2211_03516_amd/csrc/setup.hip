@@ -407,7 +407,7 @@ vam_status vam_setup_geometry(const vam_geometry_desc* desc, hipStream_t stream,
   h->deposit_threads = 256;
   h->xcd_deposit = -1;  // XCD-aware deposit order, block size by kernel (deposit_order)
   h->xcd_forward = 16;  // the same for the forward, in blocks of 16: its segment records come from the XCD's L2
-  h->forward_lanes = 0;  // by volume format: cached cell words for FP32 and BF16, one lane for FP16 (fastest measured)
+  h->forward_lanes = 0;  // FP32 cells kept in registers (fastest measured for every format)
   h->angles.resize(desc->n_angles);
   for (int a = 0; a < desc->n_angles; ++a)
     h->angles[a] = desc->angles_rad ? desc->angles_rad[a] : 2.0 * M_PI * a / desc->n_angles;

@@ -423,6 +423,28 @@ def test_fixed_point_forward():
     g.close()
 
 
+@pytest.mark.parametrize("nu,nv", [(1, 1), (2, 1), (3, 5), (37, 21)])
+@pytest.mark.parametrize("edge", [8, 12, 16])
+def test_one_angle_at_a_time_from_cells(edge, nu, nv):
+    """The default march of angles that have no quarter-turn partners (FP32
+    cells of a voxel and its neighbour) against the oracle, with the same bits
+    as one lane a segment; every box edge and type, few pixels (a segment's
+    pixel is found by a reciprocal) and odd grids."""
+    p = c2_small(30, n_pupil=5, n_angles=3, nx=31, ny=29, nz=27, nu=nu, nv=nv)
+    g = gpu_geom(p)
+    g.set_box_edge(edge)
+    og = oracle.Geometry(p)
+    x = synth.SplitMix64(51).uniform(27 * 29 * 31).reshape(27, 29, 31) - 0.3
+    for tdt in (torch.float32, torch.bfloat16, torch.float16):
+        xs = torch.from_numpy(x).to(tdt)
+        P = g.forward(xs.to(DEV))
+        check(P.cpu().numpy(), oracle.forward(og, xs.double().numpy()), what="edge %d, %d x %d, %s" % (edge, nu, nv, tdt))
+        g.set_forward_lanes(1)
+        assert torch.equal(g.forward(xs.to(DEV)), P)
+        g.set_forward_lanes(0)
+    g.close()
+
+
 def test_forward_lanes_per_segment():
     """The fixed-point forward's march modes against the oracle: two lanes
     per segment (alternate samples, each lane's Horner sum over r^2, combined
