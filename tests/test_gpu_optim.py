@@ -147,6 +147,30 @@ def test_equalize_u8_matches_definition():
     say("equalize: mean %.6f std %.6f clip %.6f, %d ambiguous" % (mean, sd, clip, int(ambiguous.sum())))
 
 
+# Whole-array passes take four values a lane, four of them ahead, on up to 2048
+# workgroups of 256: both sides of those counts, at every alignment of 4 bytes.
+# A sum of n terms in FP64 is within n 2^-53 of its magnitudes' sum; the bytes
+# follow exactly from the returned clip.
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 5, 1023, 1029, 4095, 4096 * 256 + 2, 2048 * 256 * 16 + 7])
+def test_whole_array_passes_at_any_size_and_alignment(n):
+    rng = synth.SplitMix64(n)
+    x = (rng.uniform(n + 3) ** 3 * 5.0 - 0.1).astype(np.float32)
+    t = (rng.uniform(n + 3) > 0.5).astype(np.float32)
+    t[:4] = 1.0
+    xd, td = torch.from_numpy(x).to(DEV), torch.from_numpy(t).to(DEV)
+    for off in range(4):
+        say("whole arrays n %d offset %d" % (n, off))
+        xs, ts = x[off:off + n].astype(np.float64), t[off:off + n].astype(np.float64)
+        q, (mean, sd, clip) = vam.equalize_u8(xd[off:off + n])
+        assert abs(mean - xs.mean()) <= 2 * n * 2.0 ** -53 * np.abs(xs).mean() + 1e-15
+        ref = np.rint(np.minimum(np.maximum(xs, 0.0), clip) * (255.0 / clip)) if clip > 0 else np.zeros(n)
+        assert np.array_equal(q.cpu().numpy(), ref.astype(np.uint8))
+        e, rate = vam.dose_error(xd[off:off + n], td[off:off + n], 0.8, 20.0)
+        sig = 1.0 / (1.0 + np.exp(-20.0 * (xs - np.float64(np.float32(0.8)))))
+        assert e == pytest.approx(np.abs(sig - ts).sum() / ts.sum(), rel=1e-9)
+        assert rate == np.count_nonzero((xs >= np.float32(0.8)) != (ts >= 0.5)) / n
+
+
 def test_bf16_storage_optimisation_tracks_fp32():
     # c3-style loop with the projections stored in BF16 inside the library:
     # same start, same step size, losses within a few percent of FP32
