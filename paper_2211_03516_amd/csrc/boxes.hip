@@ -1052,8 +1052,8 @@ struct CellVec<4> {
 };
 
 // march_forward_cached for NQ members: S[q] is member q's Horner sum.
-template <int SY, int SZ, bool CLAMP, int NQ>
-__device__ inline void march_forward_turned(const typename CellVec<NQ>::T* sv, const SegPos& g, float hx, float hy,
+template <int SY, int SZ, bool CLAMP, int NQ, class Cell>
+__device__ inline void march_forward_turned(const Cell* sv, const SegPos& g, float hx, float hy,
                                             float hz, float r_hi, float r_lo, float (&S)[NQ]) {
   constexpr int off[8] = {0, 1, SY, SY + 1, SZ, SZ + 1, SZ + SY, SZ + SY + 1};
   float w[8][NQ] = {};
@@ -1069,8 +1069,8 @@ __device__ inline void march_forward_turned(const typename CellVec<NQ>::T* sv, c
     if (o != cur) {
       cur = o;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const auto v = sv[o + off[j]];
+      for (int j = 0; j < 8; j += sizeof(Cell) / (4 * NQ)) {
+        const Cell v = sv[o + off[j]];
         __builtin_memcpy(w[j], &v, sizeof(v));
       }
     }
@@ -1133,21 +1133,27 @@ __device__ inline unsigned lane_of(unsigned v, int j) {
 // pfx[a][pixel][member].  A pixel's members lie side by side, and NQ lanes
 // exchange their segments' sums first, so that the NQ lanes add to one
 // pixel's members at a time: one request of 8 NQ bytes instead of NQ of 8.
-template <int NQ, int NT>
+// Cell: the members' values, or for two members theirs and their x neighbours'.
+template <int NQ, int NT, class Cell>
 __global__ __launch_bounds__(NT) void k_forward_turned(
     MarchParams P, BoxParams Bp, const typename CellVec<NQ>::T* __restrict__ vol,
     unsigned long long* __restrict__ pfx, const unsigned* __restrict__ vmax, double fx_coef) {
   // slice pitch two cells longer than a slice: 69.7 against 71.0 ms at 256^3
   constexpr int SY = Fixed<kBox>::WXY, SZ = SY * SY + 2;
   using Vec = typename CellVec<NQ>::T;
-  __shared__ Vec sv[SZ * Fixed<kBox>::WZ];
+  __shared__ Cell sv[SZ * Fixed<kBox>::WZ];
   int b, a;
   if (!work_item(Bp.nboxes, Bp.na, Bp.xcd, b, a)) return;
   const unsigned vm = *vmax;
   if (vm >= 0x7f800000u) return;  // a non-finite value: k_fx_store writes NaN
   const double2 cs = P.cs[P.a0 + a];
   const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
-  load_tile<SY, SZ, Fixed<kBox>::WZ, NT>(vol + tile_base(Bp, f), Bp.px, Bp.py, f, [&](int i, const Vec& v) { sv[i] = v; });
+  load_tile<SY, SZ, Fixed<kBox>::WZ, NT>(vol + tile_base(Bp, f), Bp.px, Bp.py, f, [&](int i, const Vec& v) {
+    // (the last cell of a row gets a neighbour that no sample reads)
+    __builtin_memcpy(__builtin_assume_aligned(&sv[i], sizeof(Vec)), &v, sizeof(Vec));
+    if constexpr (sizeof(Cell) > sizeof(Vec))
+      if (i > 0) __builtin_memcpy(__builtin_assume_aligned((char*)&sv[i - 1] + sizeof(Vec), sizeof(Vec)), &v, sizeof(Vec));
+  });
   __syncthreads();
   const float hx = (float)f.WX - 1.001f, hy = (float)f.WY - 1.001f, hz = (float)f.WZ - 1.001f;
   const float c = (float)cs.x, s = (float)cs.y, sc = P.step * c, ss = P.step * s;
@@ -1445,20 +1451,66 @@ static int members_together(const vam_geometry* h, int a0, int na) {
   return na == 4 * Q ? 4 : na == 2 * Q ? 2 : 1;
 }
 
+// Segments a box from which the forward's cells take 16 bytes, so that two
+// workgroups fit a CU's LDS instead of four: four members together (fewer: two
+// and two), and pairs with their x neighbours (four 16-byte reads a sample
+// instead of eight of 8).  With fewer segments two workgroups keep too few
+// waves busy.  180 angles, members by fours / by twos: 64^3 and 128^3 with one
+// pupil point (150 segments) 0.252 / 0.226 and 1.50 / 1.28 ms, two points (300)
+// 1.62 / 1.63, four (600) 1.97 / 2.74.  90 angles by twos, 16-byte / 8-byte
+// cells: 128^3 one point 1.11 / 0.65 ms, two 1.16 / 0.82, four 1.32 / 1.33, eight
+// (1300, thin lens) 1.50 / 2.13; 64^3 eight 0.31 / 0.37; 256^3 telecentric eight
+// 19.1 / 20.2.
+constexpr int kQuadSegments = 250, kWideSegments = 800;
+static bool segments_a_box(const vam_geometry* h, int least) {
+  return h->seg_fwd.n >= least * (int64_t)h->n_boxes;
+}
+
 // Default forward: every segment adds its partial to its pixel in 64-bit
 // fixed point (scale from the volume's largest |value|), then one pass
 // rounds the integers to the stored projections.  Variant 2 (below) writes
 // FP32 partial sums instead and adds them per pixel in a fixed order.
-// Workgroup sizes: four angles take 81 KB of LDS, so two workgroups fit a CU
-// (256^3: 512 lanes 74.4 ms, 768 71.0, 1024 70.0; 128^3: 3.21, 3.19, 3.27);
-// two angles take 41 KB, four fit (256^3 telecentric, 90 angles: 512 lanes
-// 20.0 ms, 768 22.5, 1024 23.2).
+// Workgroup sizes: 16-byte cells take 81 KB of LDS, so two workgroups fit a CU
+// (four members, 256^3: 512 lanes 74.4 ms, 768 71.0, 1024 70.0; 128^3: 3.21,
+// 3.19, 3.27); 8-byte cells 41 KB, four fit (256^3 telecentric, 90 angles: 512
+// lanes 20.0 ms, 768 22.5, 1024 23.2).
 template <int NQ>
-static void launch_forward_turned(const vam_geometry* h, const MarchParams& P, const BoxParams& Bp,
+static void launch_forward_turned(const vam_geometry* h, const MarchParams& P, const BoxParams& Bp, const float* vol,
                                   unsigned long long* pfx, double coef, hipStream_t s) {
-  constexpr int NT = NQ == 4 ? 768 : 512;
-  hipLaunchKernelGGL((k_forward_turned<NQ, NT>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(NT), 0, s, P, Bp,
-                     (const typename CellVec<NQ>::T*)h->vol_turn, pfx, h->vol_absmax, coef);
+  using Vec = typename CellVec<NQ>::T;
+  const dim3 grid = work_grid(Bp.nboxes, Bp.na, Bp.xcd);
+  if constexpr (NQ == 2)
+    if (!segments_a_box(h, kWideSegments)) {
+      hipLaunchKernelGGL((k_forward_turned<2, 512, Vec>), grid, dim3(512), 0, s, P, Bp, (const Vec*)vol, pfx,
+                         h->vol_absmax, coef);
+      return;
+    }
+  hipLaunchKernelGGL((k_forward_turned<NQ, 768, float4>), grid, dim3(768), 0, s, P, Bp, (const Vec*)vol, pfx,
+                     h->vol_absmax, coef);
+}
+
+// The members m0 .. m0 + n - 1 of every representative, NQ at a time.
+template <int NQ, typename PT>
+static vam_status forward_members(vam_geometry* h, const void* volume, PT* proj, int m0, int n, int fmt, double coef,
+                                  hipStream_t s) {
+  const int Q = h->turn_stride, T = h->turn_quarters;
+  const int64_t npix = (int64_t)h->desc.n_u * h->desc.n_v, groups = Q * npix;
+  const MarchParams P = march_params(h, 0);
+  const BoxParams Bp = box_params(h, h->seg_fwd, Q, h->xcd_forward);
+  unsigned long long* pfx = (unsigned long long*)h->proj_fx;
+  float* vol = (float*)h->vol_turn;
+  for (int j = 0; j < n; j += NQ) {
+    const int m = m0 + j;
+    pad_turned<NQ>(h, volume, fmt, vol + j * h->pad_voxels, Turns{{m * T, (m + 1) * T, (m + 2) * T, (m + 3) * T}},
+                   j == 0 ? h->vol_absmax : nullptr, s);
+  }
+  VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
+  for (int j = 0; j < n && h->n_boxes > 0; j += NQ)
+    launch_forward_turned<NQ>(h, P, Bp, vol + j * h->pad_voxels, pfx + j * groups, coef, s);
+  for (int j = 0; j < n; j += NQ)
+    hipLaunchKernelGGL((k_fx_store_turned<PT, NQ>), dim3((unsigned)((groups + 255) / 256)), dim3(256), 0, s,
+                       pfx + j * groups, proj + j * groups, groups, groups, h->vol_absmax, coef);
+  return VAM_OK;
 }
 
 template <typename PT>
@@ -1488,23 +1540,10 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
   // a chosen march mode or box edge takes one angle at a time
   const int nq = h->vol_turn && h->forward_lanes == 0 && h->boxes.B == kBox ? members_together(h, a0, na) : 1;
   if (nq > 1) {
-    const Turns turns{{m0 * T, (m0 + 1) * T, (m0 + 2) * T, (m0 + 3) * T}};
-    const MarchParams P = march_params(h, 0);
-    const BoxParams Bp = box_params(h, h->seg_fwd, Q, h->xcd_forward);
-    if (nq == 4) pad_turned<4>(h, volume, fmt, h->vol_turn, turns, h->vol_absmax, s);
-    else pad_turned<2>(h, volume, fmt, h->vol_turn, turns, h->vol_absmax, s);
-    VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
-    const int64_t pairs = Q * npix;
-    const dim3 store_grid((unsigned)((pairs + 255) / 256));
-    if (nq == 4) {
-      if (h->n_boxes > 0) launch_forward_turned<4>(h, P, Bp, pfx, coef, s);
-      hipLaunchKernelGGL((k_fx_store_turned<PT, 4>), store_grid, dim3(256), 0, s, pfx, proj, pairs, pairs,
-                         h->vol_absmax, coef);
-    } else {
-      if (h->n_boxes > 0) launch_forward_turned<2>(h, P, Bp, pfx, coef, s);
-      hipLaunchKernelGGL((k_fx_store_turned<PT, 2>), store_grid, dim3(256), 0, s, pfx, proj, pairs, pairs,
-                         h->vol_absmax, coef);
-    }
+    const vam_status st = nq == 4 && segments_a_box(h, kQuadSegments)
+                              ? forward_members<4>(h, volume, proj, m0, nq, fmt, coef, s)
+                              : forward_members<2>(h, volume, proj, m0, nq, fmt, coef, s);
+    if (st != VAM_OK) return st;
   } else {
     // one turned copy of the volume per member in the call, beside each other
     // (in vol_turn) and one launch, or without that memory one after the other

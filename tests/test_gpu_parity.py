@@ -445,6 +445,29 @@ def test_one_angle_at_a_time_from_cells(edge, nu, nv):
     g.close()
 
 
+# (about 140, 550 and 1600 segments a box: members by twos, by fours, and pairs
+# from wide cells)
+@pytest.mark.parametrize("n_pupil", [1, 4, 12])
+def test_members_together_by_density(n_pupil):
+    """Whole turns and half turns of angles a quarter turn apart against the
+    oracle and, with the same bits, one angle at a time; every type."""
+    p = c2_small(33, n_pupil=n_pupil, n_angles=8, nx=34, ny=31, nz=35, nu=37, nv=37)
+    g = gpu_geom(p)
+    og = oracle.Geometry(p)
+    x = synth.SplitMix64(53).uniform(35 * 31 * 34).reshape(35, 31, 34) - 0.3
+    for tdt in (torch.float32, torch.bfloat16, torch.float16):
+        xs = torch.from_numpy(x).to(tdt)
+        xd = xs.to(DEV)
+        P = g.forward(xd)
+        check(P.cpu().numpy(), oracle.forward(og, xs.double().numpy()), what="%d pupil points, %s" % (n_pupil, tdt))
+        for a0 in (0, 2, 4):
+            assert torch.equal(g.forward(xd, angle_begin=a0, angle_count=4), P[a0:a0 + 4])
+        g.set_forward_lanes(1)
+        assert torch.equal(g.forward(xd), P)
+        g.set_forward_lanes(0)
+    g.close()
+
+
 def test_forward_lanes_per_segment():
     """The fixed-point forward's march modes against the oracle: two lanes
     per segment (alternate samples, each lane's Horner sum over r^2, combined
