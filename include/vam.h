@@ -118,7 +118,10 @@ vam_status vam_destroy_geometry(vam_geometry_t h);
  * <= 2^-61 of a bound per add, see vam_set_variant, op 0) and the total is
  * rounded once; a NaN or infinity anywhere in the volume makes every
  * projection value of the call NaN.  The first call allocates
- * n_angles x n_u x n_v x 8 bytes in the handle.
+ * n_angles x n_u x n_v x 8 bytes in the handle and, where angles lie whole
+ * quarter turns apart, m x (nx+4)(ny+4)(nz+4) x 4 bytes for the m = 2 or 4 of
+ * them that are taken together (without that memory the angles are taken one
+ * at a time, with the same bits).
  * Errors: VAM_ERR_BAD_HANDLE; VAM_ERR_INVALID_ARG for NULL pointers, bad
  * dtypes, angle_count < 1 or an angle range outside [0, n_angles);
  * VAM_ERR_OUT_OF_MEMORY; VAM_ERR_HIP. */

@@ -43,7 +43,8 @@ def counters(path, out=sys.stdout):
             out.write("%-58s %-22s %8d %16.6g\n" % (k[:58], c, len(v), sum(v) / len(v)))
 
 
-KERNELS = {"deposit": "k_back_box", "forward": "k_forward_box"}
+# each operator's kernels: one angle at a time, or several together
+KERNELS = {"deposit": ("k_back_box", "k_back_planes"), "forward": ("k_forward_box", "k_forward_turned")}
 
 
 def kernel_source_hash(root):
@@ -67,7 +68,7 @@ def _sums(path, counters):
         if "copyBuffer" in r["Kernel_Name"]:
             copy[c] = max(copy[c], v)
         for name, pat in KERNELS.items():
-            if pat in r["Kernel_Name"]:
+            if any(p in r["Kernel_Name"] for p in pat):
                 per[name][c][0] += v
                 per[name][c][1] += 1
     return per, copy
@@ -91,7 +92,7 @@ def traffic(fetch_csv, write_csv, copy_mib, root, calls=None, sq_csv=None, l2_cs
         per = collections.defaultdict(list)
         for r in rows:
             for name, pat in KERNELS.items():
-                if pat in r["Kernel_Name"]:
+                if any(p in r["Kernel_Name"] for p in pat):
                     per[name].append(float(r["Counter_Value"]))
         return copy, per
     cf, fetch = load(fetch_csv, "FETCH_SIZE")
@@ -148,7 +149,7 @@ def l2(counter_csv, stats_csv, copy_mib, calls=None, out=sys.stdout):
         if "copyBuffer" in r["Kernel_Name"]:
             copy[c] = max(copy[c], v)
         for name, pat in KERNELS.items():
-            if pat in r["Kernel_Name"]:
+            if any(p in r["Kernel_Name"] for p in pat):
                 acc[name][c] += v
                 ndisp[name][c] += 1
     nbytes = copy_mib * 1048576.0
@@ -157,7 +158,7 @@ def l2(counter_csv, stats_csv, copy_mib, calls=None, out=sys.stdout):
     avg_ms = {}
     for r in csv.DictReader(open(stats_csv)):
         for name, pat in KERNELS.items():
-            if pat in r["Name"]:
+            if any(p in r["Name"] for p in pat):
                 avg_ms[name] = float(r["AverageNs"]) / 1e6
     out.write("# calibration (%g MiB copy): %.0f B per L1->L2 read request, %.0f B per write request\n"
               % (copy_mib, rd or 0, wr or 0))
