@@ -288,8 +288,9 @@ vam_status vam_export_rays(vam_geometry_t h, double* out);
  *   op 8, 9:        work order of the deposit (8) or forward (9) box
  *                   kernels: 0 = boxes fastest, 1 = XCD-aware with all
  *                   angles of a box on one XCD, A >= 2 = XCD-aware with the
- *                   angles of a box in blocks of A (up to 4096; default 4
- *                   or 8 for the deposit, by kernel, 16 for the forward).
+ *                   angles of a box in blocks of at most A (up to 4096; default 4
+ *                   for the deposit, for the forward 16 or a quarter of the
+ *                   call's angles, the smaller).
  *                   Angles that the kernel takes together count as one.
  *   op 10, mode:    how the default (fixed-point) box forward marches a
  *                   segment: 1 = one lane; 2 = two lanes take alternate

@@ -595,7 +595,7 @@ __device__ inline unsigned pixel_of(const BoxParams& Bp, unsigned slot) {
 //   xcd = 1: each XCD takes a contiguous range of (box, all angles) items, so
 //            a box's segment records are reused from that XCD's L2 across
 //            all angles;
-//   xcd = A >= 2: the same, with the angles in blocks of A: a box's records
+//   xcd = A >= 2: the same, with the angles in blocks of at most A: a box's records
 //            are reused across A angles while at most A workgroups of one box
 //            flush into the same dose cells at a time.
 __device__ inline bool work_item(int nboxes, int na, int xcd, int& b, int& a) {
@@ -607,25 +607,27 @@ __device__ inline bool work_item(int nboxes, int na, int xcd, int& b, int& a) {
     b = (int)(L - a * nb);
     return true;
   }
-  const unsigned A = xcd == 1 ? na : xcd;
-  const unsigned nblk = (na + A - 1) / A;
-  const unsigned W = nblk * nb * A;
-  const unsigned per = (W + kXcds - 1) / kXcds;
-  const unsigned i = L / kXcds;
-  const unsigned w = (L % kXcds) * per + i;
+  // nblk blocks of A or, the first `more` of them, A + 1 angles: every XCD gets
+  // as many items as the next (blocks of exactly A left the last one short, and
+  // its XCDs idle: 256^3, 90 representatives in
+  // blocks of 16 69.4 against 64.3 ms)
+  const unsigned nblk = xcd == 1 ? 1u : (unsigned)(na + xcd - 1) / (unsigned)xcd;
+  const unsigned A = (unsigned)na / nblk, more = (unsigned)na - A * nblk;
+  const unsigned W = nb * (unsigned)na, per = (W + kXcds - 1) / kXcds;
+  const unsigned i = L / kXcds, w = (L % kXcds) * per + i;
   if (i >= per || w >= W) return false;
-  const unsigned blk = w / (nb * A);
-  const unsigned rem = w - blk * (nb * A);
-  b = (int)(rem / A);
-  a = (int)(blk * A + (rem - b * A));
-  return a < na;
+  const unsigned head = more * (A + 1) * nb;  // items of the longer blocks
+  const bool longer = w < head;
+  const unsigned len = longer ? A + 1 : A, first = longer ? 0u : head;
+  const unsigned blk = (w - first) / (nb * len), rem = (w - first) - blk * (nb * len);
+  b = (int)(rem / len);
+  a = (int)((longer ? 0u : more * (A + 1)) + blk * len + (rem - b * len));
+  return true;
 }
 
 static inline dim3 work_grid(int nboxes, int na, int xcd) {
-  if (!xcd) return dim3((unsigned)((int64_t)nboxes * na));
-  const int A = xcd == 1 ? na : xcd;
-  const int64_t W = (int64_t)((na + A - 1) / A) * nboxes * A;
-  return dim3((unsigned)(((W + kXcds - 1) / kXcds) * kXcds));
+  const int64_t W = (int64_t)nboxes * na;
+  return dim3((unsigned)(xcd ? (W + kXcds - 1) / kXcds * kXcds : W));
 }
 
 // Rotated-box footprint [X0, X0 + WX) x [Y0, Y0 + WY) x [Z0, Z0 + WZ) in
@@ -1451,6 +1453,15 @@ static int members_together(const vam_geometry* h, int a0, int na) {
   return na == 4 * Q ? 4 : na == 2 * Q ? 2 : 1;
 }
 
+// Work order of the forward of na angles (or representatives) where none was
+// chosen: blocks of at most 16, and at least four blocks, so that the XCDs'
+// parts of a block's boxes are alike (45 of them in blocks of 16 / 12: 128^3 2.35
+// / 2.23 ms, one at a time in FP16 1.11 / 1.01, 256^3 telecentric 18.9 / 18.3; 90
+// in blocks of 16 / 12, 256^3: 64.3 / 67.0).
+static int forward_order(const vam_geometry* h, int na) {
+  return h->xcd_forward >= 0 ? h->xcd_forward : std::max(2, std::min(16, (na + 3) / 4));
+}
+
 // Segments a box from which the forward's cells take 16 bytes, so that two
 // workgroups fit a CU's LDS instead of four: four members together (fewer: two
 // and two), and pairs with their x neighbours (four 16-byte reads a sample
@@ -1496,7 +1507,7 @@ static vam_status forward_members(vam_geometry* h, const void* volume, PT* proj,
   const int Q = h->turn_stride, T = h->turn_quarters;
   const int64_t npix = (int64_t)h->desc.n_u * h->desc.n_v, groups = Q * npix;
   const MarchParams P = march_params(h, 0);
-  const BoxParams Bp = box_params(h, h->seg_fwd, Q, h->xcd_forward);
+  const BoxParams Bp = box_params(h, h->seg_fwd, Q, forward_order(h, Q));
   unsigned long long* pfx = (unsigned long long*)h->proj_fx;
   float* vol = (float*)h->vol_turn;
   for (int j = 0; j < n; j += NQ) {
@@ -1557,7 +1568,7 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
       if (together || m == m0) VAM_HIP_TRY(hipEventRecord(h->ev[0], s), "recording an event");
       if (h->n_boxes == 0) continue;
       const int first = together ? a0 : std::max(a0, m * Q), last = together ? a0 + na : std::min(a0 + na, (m + 1) * Q);
-      BoxParams Bp = box_params(h, h->seg_fwd, last - first, h->xcd_forward);
+      BoxParams Bp = box_params(h, h->seg_fwd, last - first, forward_order(h, last - first));
       Bp.turn_stride = Q;
       Bp.member0 = together ? m0 : m;
       // (128^3, 60 of 180 angles, FP32: one lane 1.75 ms, its words in
@@ -1606,7 +1617,7 @@ static vam_status forward_box_t(vam_geometry* h, const void* volume, PT* proj, i
     MarchParams P = P0;
     P.a0 = P0.a0 + c0;
     if (h->n_boxes > 0) {
-      const BoxParams Bp = box_params(h, h->seg_fwd, nc, h->xcd_forward);
+      const BoxParams Bp = box_params(h, h->seg_fwd, nc, forward_order(h, nc));
       const FwdOut o{h->seg_part, slots, nullptr, nullptr, 0.0, kMarchOne};
       launch_forward_box_edge<false>(h->boxes.B, work_grid(h->n_boxes, nc, Bp.xcd), s, P, Bp, fmt,
                                      (const uint32_t*)h->vol_pad, o);
@@ -2088,15 +2099,17 @@ double deposit_coef(const vam_geometry* h, int na) {
   return (double)na * (double)std::max<int64_t>(h->supp_bound, 1) * h->desc.step / h->desc.n_pupil;
 }
 
-// Work order of the deposit where none was chosen: angles in blocks of 8, or of
-// 4 representatives (256^3: blocks of 4 / 8 / 16 representatives 117.9 / 120.1 /
-// 120.3 ms; one angle at a time, 45 of 360: blocks of 4 / 8 25.3 / 25.0).
-static int deposit_order(const vam_geometry* h, int blocks) { return h->xcd_deposit >= 0 ? h->xcd_deposit : blocks; }
+// Work order of the deposit where none was chosen: angles (or representatives)
+// in blocks of 4.  Corner by corner, blocks of 4 / 8: 45 angles of 128^3 1.64 /
+// 1.74 ms, 128^3 with one pupil point 2.57 / 2.66, 64^3 0.348 / 0.365, 256^3
+// telecentric on dark-edged projections 19.2 / 19.4; plane by plane 128^3 3.92 /
+// 4.14, 256^3 103.5 / 104.1.
+static int deposit_order(const vam_geometry* h) { return h->xcd_deposit >= 0 ? h->xcd_deposit : 4; }
 
 template <int B, typename PT>
 static void launch_back_box(vam_geometry* h, const MarchParams& P, const PT* proj, int na, double* acc,
                             hipStream_t s) {
-  const BoxParams Bp = box_params(h, h->seg_dep, na, deposit_order(h, 8));
+  const BoxParams Bp = box_params(h, h->seg_dep, na, deposit_order(h));
   const dim3 grid = work_grid(h->n_boxes, na, Bp.xcd);
   unsigned long long* a64 = (unsigned long long*)acc;
   const unsigned* pm = (const unsigned*)(acc + h->pad_voxels);
@@ -2125,7 +2138,7 @@ static void launch_back_box_t(vam_geometry* h, const MarchParams& P, const PT* p
     // two workgroups fit a CU's LDS: 24 waves at 77 registers (256^3: 512 lanes
     // 141 ms, 768 120; 1024 need 64 registers to fit twice, 170 in one)
     constexpr int NT = 768;
-    const BoxParams Bp = box_params(h, h->seg_dep, h->turn_stride, deposit_order(h, 4));
+    const BoxParams Bp = box_params(h, h->seg_dep, h->turn_stride, deposit_order(h));
     hipLaunchKernelGGL((k_back_planes<PT, NT>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(NT), 0, s, P, Bp, proj,
                        (int64_t)h->turn_stride, (unsigned long long*)acc, (const unsigned*)(acc + h->pad_voxels),
                        deposit_coef(h, na));

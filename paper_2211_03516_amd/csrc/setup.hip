@@ -405,8 +405,8 @@ vam_status vam_setup_geometry(const vam_geometry_desc* desc, hipStream_t stream,
   h->seg_order = 11;  // pixel classes (u mod 3, v mod 2), then by length (fastest measured)
   h->seg_order_fwd = 16;  // ray order, then the box by length in steps of two samples (fastest measured)
   h->deposit_threads = 256;
-  h->xcd_deposit = -1;  // XCD-aware deposit order, block size by kernel (deposit_order)
-  h->xcd_forward = 16;  // the same for the forward, in blocks of 16: its segment records come from the XCD's L2
+  h->xcd_deposit = -1;  // XCD-aware orders, block sizes by kernel and number of angles (deposit_order, forward_order)
+  h->xcd_forward = -1;
   h->forward_lanes = 0;  // FP32 cells kept in registers (fastest measured for every format)
   h->angles.resize(desc->n_angles);
   for (int a = 0; a < desc->n_angles; ++a)

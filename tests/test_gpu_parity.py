@@ -445,6 +445,23 @@ def test_one_angle_at_a_time_from_cells(edge, nu, nv):
     g.close()
 
 
+@pytest.mark.parametrize("na", [1, 2, 5, 17])
+def test_angle_blocks_of_unequal_size(na):
+    """Every work order covers every box and angle once: blocks that do not
+    divide the number of angles, one block, blocks larger than it."""
+    p = c2_small(26, n_pupil=2, n_angles=na, nu=19, nv=17)
+    g = gpu_geom(p)
+    x = to_dev(synth.SplitMix64(57).uniform(26 ** 3).reshape(26, 26, 26))
+    P = g.forward(x)
+    D = g.back(P)
+    og = oracle.Geometry(p)
+    check(P.cpu().numpy(), oracle.forward(og, x.cpu().double().numpy()), what="%d angles" % na)
+    for block in (0, 1, 2, 3, 4, 7, 4096):
+        g.set_angle_blocks(deposit=block, forward=block)
+        assert torch.equal(g.forward(x), P) and torch.equal(g.back(P), D), block
+    g.close()
+
+
 # (about 140, 550 and 1600 segments a box: members by twos, by fours, and pairs
 # from wide cells)
 @pytest.mark.parametrize("n_pupil", [1, 4, 12])
