@@ -1036,11 +1036,12 @@ __global__ __launch_bounds__(kForwardThreads<MODE>) void k_forward_box(MarchPara
 // bytes do (256^3, 360 angles: 71.1 ms with FP32 cells, 91.2 with FP16 cells
 // read by mixed-precision FMAs; BF16 at 512^3 338 against 300 ms).
 //
-// Bounds: a wave's step takes 84 VALU instructions for its 4 x 64 samples (about
-// 60 % of the time at 256^3) and up to eight 16-byte reads.  A read of 64
+// Bounds: a wave's step takes about 80 VALU instructions for its 4 x 64 samples (71 %
+// of the issue slots at 256^3) and up to eight 16-byte reads.  A read of 64
 // unrelated cells takes 7.6 clocks for 4 bytes a lane, 7.7 for 8 and 12.8 for
 // 16 (measured: 20 words a clock against 8.4), so wide cells move 2.4 times the
-// words.  256^3, 360 angles: 71 ms against 123 one angle at a time.
+// words.  256^3, 360 angles: 64 ms against 123 one angle at a time (512^3, BF16
+// 273 against 532).
 
 template <int NQ>
 struct CellVec;
@@ -1844,7 +1845,8 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
 //    integer hi 2^32 + lo of two members' 32-bit sums, whose bound is
 //    k_back_box's: a corner gets at most one add per sample of its support.
 //
-// 256^3, 360 angles: 110.9 ms against 181.0 corner by corner (91.7 against
+// 256^3, 360 angles: 104 ms against 181 corner by corner (when first built 110.9,
+// as the figures below are; 91.7 against
 // 118.0 on projections dark outside a part's shadow); 128^3, 180 angles, 8
 // pupil points 4.50 against 6.49; one pupil point 4.40 against 4.55 (there the
 // adds into the voxels bind, the same for both).  Without its LDS adds and
