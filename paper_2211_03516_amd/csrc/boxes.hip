@@ -24,12 +24,12 @@
 #include <thread>
 #include <type_traits>
 
+#include "launch_cut.h"
 #include "vam_internal.h"
 
 namespace vam {
 
 constexpr int kBox = 12;  // default lab box edge (fastest measured for both operators)
-constexpr int kXcds = 8;  // XCDs of an MI355X; workgroup L of a launch runs on XCD L mod 8
 
 // Compile-time footprints for the supported box edges: row pitch WXY, WZ
 // slices (the largest footprint of a rotated box: extent B(|cos| + |sin|) <=
@@ -599,7 +599,7 @@ __device__ inline unsigned pixel_of(const BoxParams& Bp, unsigned slot) {
 //            are reused across A angles while at most A workgroups of one box
 //            flush into the same dose cells at a time.
 __device__ inline bool work_item(int nboxes, int na, int xcd, int& b, int& a) {
-  // the grid has fewer than 2^31 workgroups, so 32 bits hold every number here
+  // a launch has fewer than 2^32 lanes (for_launches), so 32 bits hold every number here
   const unsigned L = blockIdx.x, nb = nboxes;
   if (!xcd) {
     if (L >= nb * (unsigned)na) return false;
@@ -628,6 +628,25 @@ __device__ inline bool work_item(int nboxes, int na, int xcd, int& b, int& a) {
 static inline dim3 work_grid(int nboxes, int na, int xcd) {
   const int64_t W = (int64_t)nboxes * na;
   return dim3((unsigned)(xcd ? (W + kXcds - 1) / kXcds * kXcds : W));
+}
+
+// Calls launch(grid, part, a0) for the launches that the boxes and angles of Bp
+// take (launch_cut): part has a launch's boxes and angles, the first of which
+// is Bp's angle a0.
+template <class F>
+static void for_launches(const BoxParams& Bp, int threads, F launch) {
+  if (Bp.nboxes < 1 || Bp.na < 1) return;
+  const LaunchCut cut = launch_cut(Bp.nboxes, Bp.na, threads);
+  for (int a0 = 0; a0 < Bp.na; a0 += cut.angles)
+    for (int64_t b0 = 0; b0 < Bp.nboxes; b0 += cut.boxes) {
+      BoxParams part = Bp;
+      part.na = std::min(cut.angles, Bp.na - a0);
+      part.nboxes = (int)std::min<int64_t>(cut.boxes, Bp.nboxes - b0);
+      part.box_begin += b0;
+      part.box_id += b0;
+      part.box_supp += b0;
+      launch(work_grid(part.nboxes, part.na, part.xcd), part, a0);
+    }
 }
 
 // Rotated-box footprint [X0, X0 + WX) x [Y0, Y0 + WY) x [Z0, Z0 + WZ) in
@@ -1308,43 +1327,50 @@ struct FwdOut {
   unsigned long long* pfx;  // fixed-point projections (fx = true)
   const unsigned* vmax;
   double fx_coef;
-  int mode;                 // march mode (fx = true): kMarchOne, kMarchPair or kMarchCached
+  int mode;                 // march mode (fx = true): kMarchOne, kMarchPair, kMarchCached or kMarchCells
 };
 
+template <int B, int FMT, bool FX, int MODE>
+static void launch_forward_box_m(hipStream_t s, const MarchParams& P, const BoxParams& Bp, const uint32_t* vol,
+                                 const FwdOut& o) {
+  constexpr int NT = kForwardThreads<MODE>;
+  for_launches(Bp, NT, [&](dim3 grid, const BoxParams& part, int64_t a0) {
+    MarchParams Pa = P;
+    Pa.a0 += (int)a0;
+    hipLaunchKernelGGL((k_forward_box<B, FMT, FX, MODE>), grid, dim3(NT), 0, s, Pa, part, vol,
+                       FX ? o.part : o.part + a0 * o.slots, o.slots, FX ? o.pfx + a0 * Bp.npix : o.pfx, o.vmax,
+                       o.fx_coef);
+  });
+}
+
 template <int B, int FMT, bool FX>
-static void launch_forward_box_f(dim3 grid, hipStream_t s, const MarchParams& P, const BoxParams& Bp,
-                                 const uint32_t* vol, const FwdOut& o) {
-  if (FX && o.mode == kMarchCells)
-    hipLaunchKernelGGL((k_forward_box<B, FMT, true, kMarchCells>), grid, dim3(kForwardThreads<kMarchCells>), 0, s, P,
-                       Bp, vol, o.part, o.slots, o.pfx, o.vmax, o.fx_coef);
-  else if (FX && o.mode == kMarchCached)
-    hipLaunchKernelGGL((k_forward_box<B, FMT, true, kMarchCached>), grid, dim3(256), 0, s, P, Bp, vol, o.part,
-                       o.slots, o.pfx, o.vmax, o.fx_coef);
-  else if (FX && o.mode == kMarchPair)
-    hipLaunchKernelGGL((k_forward_box<B, FMT, true, kMarchPair>), grid, dim3(256), 0, s, P, Bp, vol, o.part, o.slots,
-                       o.pfx, o.vmax, o.fx_coef);
-  else
-    hipLaunchKernelGGL((k_forward_box<B, FMT, FX, kMarchOne>), grid, dim3(256), 0, s, P, Bp, vol, o.part, o.slots,
-                       o.pfx, o.vmax, o.fx_coef);
+static void launch_forward_box_f(hipStream_t s, const MarchParams& P, const BoxParams& Bp, const uint32_t* vol,
+                                 const FwdOut& o) {
+  if constexpr (FX) {
+    if (o.mode == kMarchCells) return launch_forward_box_m<B, FMT, FX, kMarchCells>(s, P, Bp, vol, o);
+    if (o.mode == kMarchCached) return launch_forward_box_m<B, FMT, FX, kMarchCached>(s, P, Bp, vol, o);
+    if (o.mode == kMarchPair) return launch_forward_box_m<B, FMT, FX, kMarchPair>(s, P, Bp, vol, o);
+  }
+  launch_forward_box_m<B, FMT, FX, kMarchOne>(s, P, Bp, vol, o);
 }
 
 template <int B, bool FX>
-static void launch_forward_box(dim3 grid, hipStream_t s, const MarchParams& P, const BoxParams& Bp, int fmt,
+static void launch_forward_box(hipStream_t s, const MarchParams& P, const BoxParams& Bp, int fmt,
                                const uint32_t* vol, const FwdOut& o) {
   switch (fmt) {
-    case kVolBF16Pairs: launch_forward_box_f<B, kVolBF16Pairs, FX>(grid, s, P, Bp, vol, o); break;
-    case kVolF16Pairs: launch_forward_box_f<B, kVolF16Pairs, FX>(grid, s, P, Bp, vol, o); break;
-    default: launch_forward_box_f<B, kVolF32, FX>(grid, s, P, Bp, vol, o); break;
+    case kVolBF16Pairs: launch_forward_box_f<B, kVolBF16Pairs, FX>(s, P, Bp, vol, o); break;
+    case kVolF16Pairs: launch_forward_box_f<B, kVolF16Pairs, FX>(s, P, Bp, vol, o); break;
+    default: launch_forward_box_f<B, kVolF32, FX>(s, P, Bp, vol, o); break;
   }
 }
 
 template <bool FX>
-static void launch_forward_box_edge(int edge, dim3 grid, hipStream_t s, const MarchParams& P, const BoxParams& Bp,
-                                    int fmt, const uint32_t* vol, const FwdOut& o) {
+static void launch_forward_box_edge(int edge, hipStream_t s, const MarchParams& P, const BoxParams& Bp, int fmt,
+                                    const uint32_t* vol, const FwdOut& o) {
   switch (edge) {
-    case 8: launch_forward_box<8, FX>(grid, s, P, Bp, fmt, vol, o); break;
-    case 12: launch_forward_box<12, FX>(grid, s, P, Bp, fmt, vol, o); break;
-    default: launch_forward_box<16, FX>(grid, s, P, Bp, fmt, vol, o); break;
+    case 8: launch_forward_box<8, FX>(s, P, Bp, fmt, vol, o); break;
+    case 12: launch_forward_box<12, FX>(s, P, Bp, fmt, vol, o); break;
+    default: launch_forward_box<16, FX>(s, P, Bp, fmt, vol, o); break;
   }
 }
 
@@ -1490,15 +1516,17 @@ template <int NQ>
 static void launch_forward_turned(const vam_geometry* h, const MarchParams& P, const BoxParams& Bp, const float* vol,
                                   unsigned long long* pfx, double coef, hipStream_t s) {
   using Vec = typename CellVec<NQ>::T;
-  const dim3 grid = work_grid(Bp.nboxes, Bp.na, Bp.xcd);
-  if constexpr (NQ == 2)
-    if (!segments_a_box(h, kWideSegments)) {
-      hipLaunchKernelGGL((k_forward_turned<2, 512, Vec>), grid, dim3(512), 0, s, P, Bp, (const Vec*)vol, pfx,
+  auto launch = [&](auto kernel, int threads) {
+    for_launches(Bp, threads, [&](dim3 grid, const BoxParams& part, int64_t a0) {
+      MarchParams Pa = P;
+      Pa.a0 += (int)a0;
+      hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, Pa, part, (const Vec*)vol, pfx + a0 * Bp.npix * NQ,
                          h->vol_absmax, coef);
-      return;
-    }
-  hipLaunchKernelGGL((k_forward_turned<NQ, 768, float4>), grid, dim3(768), 0, s, P, Bp, (const Vec*)vol, pfx,
-                     h->vol_absmax, coef);
+    });
+  };
+  if constexpr (NQ == 2)
+    if (!segments_a_box(h, kWideSegments)) return launch(k_forward_turned<2, 512, Vec>, 512);
+  launch(k_forward_turned<NQ, 768, float4>, 768);
 }
 
 // The members m0 .. m0 + n - 1 of every representative, NQ at a time.
@@ -1577,8 +1605,8 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
       // 45 angles of 128^3: 1.16, 1.16, 1.14)
       const int mode = h->forward_lanes ? h->forward_lanes : kMarchCells;
       const FwdOut o{nullptr, 0, pfx + (first - a0) * npix, h->vol_absmax, coef, mode};
-      launch_forward_box_edge<true>(h->boxes.B, work_grid(h->n_boxes, Bp.na, Bp.xcd), s, march_params(h, first), Bp,
-                                    fmt, together ? (const uint32_t*)vol : (const uint32_t*)h->vol_pad, o);
+      launch_forward_box_edge<true>(h->boxes.B, s, march_params(h, first), Bp, fmt,
+                                    together ? (const uint32_t*)vol : (const uint32_t*)h->vol_pad, o);
     }
     hipLaunchKernelGGL(k_fx_store<PT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, pfx, proj, n,
                        h->vol_absmax, coef);
@@ -1620,8 +1648,7 @@ static vam_status forward_box_t(vam_geometry* h, const void* volume, PT* proj, i
     if (h->n_boxes > 0) {
       const BoxParams Bp = box_params(h, h->seg_fwd, nc, forward_order(h, nc));
       const FwdOut o{h->seg_part, slots, nullptr, nullptr, 0.0, kMarchOne};
-      launch_forward_box_edge<false>(h->boxes.B, work_grid(h->n_boxes, nc, Bp.xcd), s, P, Bp, fmt,
-                                     (const uint32_t*)h->vol_pad, o);
+      launch_forward_box_edge<false>(h->boxes.B, s, P, Bp, fmt, (const uint32_t*)h->vol_pad, o);
     }
     const int64_t n = (int64_t)nc * npix;
     hipLaunchKernelGGL(k_reduce_segments<PT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, h->seg_part,
@@ -1938,7 +1965,7 @@ __device__ inline void march_planes(unsigned long long* acc, float k0, float k1,
   }
 }
 
-// Work item (b, a): the box at the members of representative angle a: rows a,
+// Work item (b, a): the box at the members of representative angle P.a0 + a: rows a,
 // a + member_rows, ... of proj, member q turned by q quarter turns.  acc64, pmax, dep_coef: as for k_back_box.
 template <typename PT, int NT>
 __global__ __launch_bounds__(NT) void k_back_planes(MarchParams P, BoxParams Bp, const PT* __restrict__ proj,
@@ -1954,7 +1981,7 @@ __global__ __launch_bounds__(NT) void k_back_planes(MarchParams P, BoxParams Bp,
   const unsigned pm_bits = *pmax;
   if (pm_bits >= 0x7f800000u) return;  // a non-finite projection value: the dose is NaN
   const double G = fx_scale(pm_bits, dep_coef);
-  const double2 cs = P.cs[a];
+  const double2 cs = P.cs[P.a0 + a];
   const Foot f = footprint(Bp, Bp.box_id[b], cs.x, cs.y, P.cx, P.cy);
   for (int i = threadIdx.x; i < NC; i += NT) acc[i] = 0;
   if (threadIdx.x < NQ) s_pvmax[threadIdx.x] = 0u;
@@ -2112,14 +2139,20 @@ template <int B, typename PT>
 static void launch_back_box(vam_geometry* h, const MarchParams& P, const PT* proj, int na, double* acc,
                             hipStream_t s) {
   const BoxParams Bp = box_params(h, h->seg_dep, na, deposit_order(h));
-  const dim3 grid = work_grid(h->n_boxes, na, Bp.xcd);
   unsigned long long* a64 = (unsigned long long*)acc;
   const unsigned* pm = (const unsigned*)(acc + h->pad_voxels);
   const double coef = deposit_coef(h, na);
+  auto launch = [&](auto kernel, int threads) {
+    for_launches(Bp, threads, [&](dim3 grid, const BoxParams& part, int64_t a0) {
+      MarchParams Pa = P;
+      Pa.a0 += (int)a0;
+      hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, Pa, part, proj + a0 * Bp.npix, a64, pm, coef);
+    });
+  };
   if (h->deposit_threads == 512)
-    hipLaunchKernelGGL((k_back_box<B, PT, 512>), grid, dim3(512), 0, s, P, Bp, proj, a64, pm, coef);
+    launch(k_back_box<B, PT, 512>, 512);
   else
-    hipLaunchKernelGGL((k_back_box<B, PT, 256>), grid, dim3(256), 0, s, P, Bp, proj, a64, pm, coef);
+    launch(k_back_box<B, PT, 256>, 256);
 }
 
 template <typename PT>
@@ -2141,9 +2174,13 @@ static void launch_back_box_t(vam_geometry* h, const MarchParams& P, const PT* p
     // 141 ms, 768 120; 1024 need 64 registers to fit twice, 170 in one)
     constexpr int NT = 768;
     const BoxParams Bp = box_params(h, h->seg_dep, h->turn_stride, deposit_order(h));
-    hipLaunchKernelGGL((k_back_planes<PT, NT>), work_grid(Bp.nboxes, Bp.na, Bp.xcd), dim3(NT), 0, s, P, Bp, proj,
-                       (int64_t)h->turn_stride, (unsigned long long*)acc, (const unsigned*)(acc + h->pad_voxels),
-                       deposit_coef(h, na));
+    for_launches(Bp, NT, [&](dim3 grid, const BoxParams& part, int64_t a0) {
+      MarchParams Pa = P;
+      Pa.a0 += (int)a0;
+      hipLaunchKernelGGL((k_back_planes<PT, NT>), grid, dim3(NT), 0, s, Pa, part, proj + a0 * Bp.npix,
+                         (int64_t)h->turn_stride, (unsigned long long*)acc, (const unsigned*)(acc + h->pad_voxels),
+                         deposit_coef(h, na));
+    });
     return;
   }
   switch (h->boxes.B) {

@@ -1202,3 +1202,45 @@ def test_deposit_of_whole_turns(what, na, kw):
     g.back(yd, out=acc, accumulate=True)
     check(acc.cpu().numpy(), (D.double() + 1.0).cpu().numpy(), tol=1e-6, what="%s, accumulated" % what)
     g.close()
+
+
+# ------------------------------ calls of more than one launch ----------------
+
+@pytest.mark.parametrize("what,nx,ny,n_u,n_v,n_pupil,na", [
+    ("one angle at a time", 96, 96, 16, 16, 1, 60001),
+    ("pairs", 90, 100, 16, 16, 1, 65534),
+    ("fours", 96, 96, 40, 40, 12, 65532),
+])
+def test_calls_of_more_than_one_launch(what, nx, ny, n_u, n_v, n_pupil, na):
+    """A call whose boxes and angles exceed one launch's lanes: the forward gives
+    the same bits as calls on ranges of the angles, and both operators agree
+    with the oracle at angles of every part of the turn (1e-5; the dose on
+    projections that are zero elsewhere)."""
+    nz = 120
+    p = c2_small(96, n_pupil=n_pupil, n_angles=na, nx=nx, ny=ny, nz=nz, nu=n_u, nv=n_v,
+                 pitch_u=82.0 / n_u, pitch_v=110.0 / n_v)
+    og = oracle.Geometry(p)
+    g = gpu_geom(p)
+    rng = synth.SplitMix64(53)
+    x = rng.uniform(nz * ny * nx).reshape(nz, ny, nx)
+    xd = to_dev(x)
+    P = g.forward(xd)
+    torch.cuda.synchronize()
+    say("whole forward done")
+    quarter = na // 4 if na % 4 == 0 else na // 2 if na % 2 == 0 else 20000
+    for a0 in range(0, na, quarter):
+        n = min(quarter, na - a0)
+        assert torch.equal(g.forward(xd, angle_begin=a0, angle_count=n), P[a0:a0 + n]), a0
+    some = [0, 1, na // 3, na // 2, na // 2 + 1, 2 * na // 3, na - 2, na - 1]
+    for a in some:
+        check(P[a].cpu().numpy(), oracle.forward(og, x, a0=a, na=1)[0], what="%s, angle %d" % (what, a))
+    say("whole deposit")
+    y = torch.zeros_like(P)
+    ref = 0.0
+    for a in some:
+        ya = rng.uniform(n_v * n_u).reshape(n_v, n_u)
+        y[a] = to_dev(ya)
+        ref = ref + oracle.adjoint(og, y[a:a + 1].double().cpu().numpy(), a0=a, na=1)
+    D = g.back(y)
+    check(D.cpu().numpy(), ref, what="%s, dose" % what)
+    g.close()
