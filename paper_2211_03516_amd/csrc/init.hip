@@ -46,6 +46,11 @@ namespace vam {
 // The error against FP64 is then that of adding pairs, or less, for rows of 64
 // to 1000 values of noise, smooth bumps, boxes and waves.
 //
+// Infinities and NaN: the matrix instructions multiply the nearest values by
+// zero, which makes NaN of an infinity that is added apart.  A sum that is not
+// finite when they are done is therefore formed again, pair by pair; one that
+// is finite had no such value at any odd distance.
+//
 // Columns go in groups of 512 (above that NB is 8 and blockIdx.y is the group)
 // and so does the sum over u', its own group last.  Rows in LDS are K + 12
 // floats apart, so 16 rows read at 16 bytes a lane cover all 64 banks.
@@ -54,6 +59,16 @@ __device__ inline constexpr float ramp_weight(int m) {
   const float n = (float)(2 * m + 1);
   return -1.0f / ((float)(M_PI * M_PI) * n * n);
 }
+// One output of a row, adding pairs from the middle outwards.
+__device__ inline float ramp_pairs(const float* __restrict__ row, int u, int nu) {
+  float acc = 0.25f * row[u];
+  for (int m = 0; 2 * m + 1 < nu; ++m) {
+    const int l = u - (2 * m + 1), r = u + 2 * m + 1;
+    acc = fmaf(ramp_weight(m), (l >= 0 ? row[l] : 0.0f) + (r < nu ? row[r] : 0.0f), acc);
+  }
+  return acc;
+}
+
 template <int NB>
 __global__ __launch_bounds__(64 * NB) void k_ramlak(const float* __restrict__ in, float* __restrict__ out, int n_rows,
                                                     int nu, float tau, int clip) {
@@ -117,9 +132,11 @@ __global__ __launch_bounds__(64 * NB) void k_ramlak(const float* __restrict__ in
   }
   if (!any) return;
   const int u = 2 * (K * group + 32 * wave + col);
+  float not_finite = 0.0f;  // NaN if one of the sums is not finite
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int r = 8 * (i >> 2) + 4 * half + (i & 3);
+    not_finite = fmaf(acc[0][i], 0.0f, fmaf(acc[1][i], 0.0f, not_finite));
     const float *e = x[0] + r * P + 4 + 32 * wave + col, *o = x[1] + r * P + 4 + 32 * wave + col;
     float v[2] = {0.25f * e[0], 0.25f * o[0]};
 #pragma unroll
@@ -138,6 +155,16 @@ __global__ __launch_bounds__(64 * NB) void k_ramlak(const float* __restrict__ in
       __builtin_memcpy(to, v, 8);
     else if (u < nu)
       *to = v[0];
+  }
+  if (not_finite == 0.0f) return;
+  unsigned again = 0u;
+#pragma unroll
+  for (int i = 0; i < 32; ++i) again |= acc[i & 1][i >> 1] * 0.0f == 0.0f ? 0u : 1u << i;
+  for (; again != 0u; again &= again - 1u) {
+    const int i = __ffs(again) - 1, r = r0 + 8 * (i >> 3) + 4 * half + (i >> 1 & 3), at = u + (i & 1);
+    if (r >= n_rows || at >= nu) continue;
+    const float v = ramp_pairs(in + (int64_t)r * nu, at, nu) / tau;
+    out[(int64_t)r * nu + at] = clip ? fmaxf(v, 0.0f) : v;
   }
 }
 

@@ -63,6 +63,45 @@ def test_ramlak_at_block_edges(nu):
     assert np.array_equal(clipped, np.maximum(got, 0.0))
 
 
+# Blocks of one and two rows of workgroups, one and several groups of columns,
+# both parities; the special values near the middle, at both ends and next to
+# each other.
+@pytest.mark.parametrize("nu", [1, 2, 9, 64, 130, 513, 1089])
+def test_ramlak_of_infinities_and_nan(nu):
+    """Rows with infinities or NaN follow the definition (odd distances and the
+    value itself, so a single infinity reaches every second value, and clipping
+    makes 0 of -Inf and NaN); the other rows keep their bits."""
+    tau, n_rows = 0.8, 37
+    rng = synth.SplitMix64(nu + 7)
+    rows = (rng.uniform(n_rows * nu).reshape(n_rows, nu) - 0.3).astype(np.float32)
+    clean = vam.ramlak_filter(torch.from_numpy(rows).to(DEV), pitch=tau, clip_negative=False).cpu().numpy()
+    inf, nan = np.float32(np.inf), np.float32(np.nan)
+    for i, r in enumerate((0, 3, 17, 31, 32, 36)):
+        at = [nu // 2, 0, nu - 1, nu // 3, nu // 2, nu // 4][i]
+        rows[r, at] = [inf, -inf, inf, nan, -inf, inf][i]
+    rows[5, [nu // 2, min(nu // 2 + 2, nu - 1)]] = inf, -inf
+    rows[6, [nu // 4, nu - 1]] = inf, inf
+    special = ~np.isfinite(rows).all(axis=1)
+    d = np.abs(np.arange(nu)[:, None] - np.arange(nu)[None, :])
+    h = np.where(d == 0, 0.25, np.where(d % 2 == 1, -1.0 / (np.pi * np.maximum(d, 1)) ** 2, 0.0)) / tau
+    for clip in (False, True):
+        say("ramlak nu %d, clip %s" % (nu, clip))
+        got = vam.ramlak_filter(torch.from_numpy(rows).to(DEV), pitch=tau, clip_negative=clip).cpu().numpy()
+        assert np.array_equal(got[~special], np.maximum(clean, 0.0)[~special] if clip else clean[~special])
+        for r in np.flatnonzero(special):
+            x = rows[r].astype(np.float64)
+            with np.errstate(invalid="ignore"):
+                terms = np.where(h != 0, x[None, :] * h, 0.0)
+                ref = terms.sum(axis=1)
+            bound = (nu + 8) * 2.0 ** -24 * np.abs(terms).sum(axis=1)
+            if clip:
+                ref = np.where(np.isnan(ref), 0.0, np.maximum(ref, 0.0))
+            finite = np.isfinite(ref)
+            assert np.array_equal(got[r][~finite], ref[~finite].astype(np.float32), equal_nan=True), (clip, r)
+            ok = np.isfinite(terms).all(axis=1)
+            assert np.all(np.abs(got[r][finite] - ref[finite]) <= np.where(ok, bound, 0.0)[finite]), (clip, r)
+
+
 def test_dose_error_matches_fp64_definition():
     rng = synth.SplitMix64(32)
     n = 100003
