@@ -118,10 +118,14 @@ vam_status vam_destroy_geometry(vam_geometry_t h);
  * <= 2^-61 of a bound per add, see vam_set_variant, op 0) and the total is
  * rounded once; a NaN or infinity anywhere in the volume makes every
  * projection value of the call NaN.  The first call allocates
- * n_angles x n_u x n_v x 8 bytes in the handle and, where angles lie whole
- * quarter turns apart, m x (nx+4)(ny+4)(nz+4) x 4 bytes for the m = 2 or 4 of
- * them that are taken together (without that memory the angles are taken one
- * at a time, with the same bits).
+ * n_angles x n_u x n_v x 8 bytes in the handle.  Where angles lie whole
+ * quarter turns apart, the first call on more than one such quarter also
+ * allocates m x (nx+4)(ny+4)(nz+4) x 4 bytes for the m = 2 or 4 quarters, if
+ * that is at most half of the free device memory; without it (also in a call
+ * whose stream is being captured before any call allocated it) the angles are
+ * taken one at a time, with the same bits.  The handle gives it back when
+ * memory is short at another of its allocations, unless a call was captured
+ * that uses it.
  * Errors: VAM_ERR_BAD_HANDLE; VAM_ERR_INVALID_ARG for NULL pointers, bad
  * dtypes, angle_count < 1 or an angle range outside [0, n_angles);
  * VAM_ERR_OUT_OF_MEMORY; VAM_ERR_HIP. */

@@ -256,6 +256,9 @@ static void free_table(SegTable& t) {
 void free_boxes(vam_geometry* h) {
   free_table(h->seg_dep);
   free_table(h->seg_fwd);
+  if (h->vol_turn) (void)hipFree(h->vol_turn);
+  h->vol_turn = nullptr;
+  h->vol_turn_captured = 0;
   void* ptrs[] = {h->box_id, h->box_supp, h->ray_nseg, h->seg_part};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -1504,6 +1507,30 @@ static bool segments_a_box(const vam_geometry* h, int least) {
   return h->seg_fwd.n >= least * (int64_t)h->n_boxes;
 }
 
+// The members' padded FP32 volumes side by side (vol_turn), allocated by the first
+// call that needs them; false without that memory.  They are more than a call
+// has to have, so they take at most half of what is free, are given back when
+// the handle needs the memory for what it has to have (dev_alloc_for), and no
+// call allocates them while its stream is captured.
+static bool turned_volumes(vam_geometry* h, hipStream_t s) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusActive;
+  if (hipStreamIsCapturing(s, &status) != hipSuccess) (void)hipGetLastError();
+  const bool capturing = status != hipStreamCaptureStatusNone;
+  if (h->vol_turn) {
+    if (capturing) h->vol_turn_captured = 1;
+    return true;
+  }
+  size_t free_bytes = 0, total = 0;
+  const size_t bytes = (size_t)h->pad_voxels * h->turn_members * sizeof(float);
+  if (capturing || hipMemGetInfo(&free_bytes, &total) != hipSuccess || bytes > free_bytes / 2 ||
+      dev_alloc(&h->vol_turn, bytes) != hipSuccess) {
+    (void)hipGetLastError();  // handled here
+    h->vol_turn = nullptr;
+    return false;
+  }
+  return true;
+}
+
 // Default forward: every segment adds its partial to its pixel in 64-bit
 // fixed point (scale from the volume's largest |value|), then one pass
 // rounds the integers to the stored projections.  Variant 2 (below) writes
@@ -1563,22 +1590,19 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
                 "allocating the fixed-point projections");
   }
   if (!h->vol_absmax) VAM_HIP_TRY(dev_alloc((void**)&h->vol_absmax, sizeof(unsigned)), "allocating a maximum");
-  // the turned copies need the members' FP32 volumes side by side; without
-  // that memory the angles go one at a time, with the same bits
-  if (h->turn_members > 1 && !h->vol_turn && !h->vol_turn_failed &&
-      dev_alloc(&h->vol_turn, h->pad_voxels * h->turn_members * sizeof(float)) != hipSuccess) {
-    (void)hipGetLastError();  // handled here
-    h->vol_turn = nullptr;
-    h->vol_turn_failed = 1;
-  }
+  const int Q = h->turn_stride, T = h->turn_quarters, m0 = a0 / Q, m1 = (a0 + na - 1) / Q;
+  // members taken together (a chosen march mode or box edge takes one angle at
+  // a time) and calls over several members need their volumes side by side;
+  // without that memory the angles go one at a time, member after member, with
+  // the same bits
+  int nq = h->forward_lanes == 0 && h->boxes.B == kBox ? members_together(h, a0, na) : 1;
+  const bool turned = m0 != m1 && turned_volumes(h, s);
+  if (!turned) nq = 1;
   unsigned long long* pfx = (unsigned long long*)h->proj_fx;
   const int64_t n = (int64_t)na * npix;
   hipLaunchKernelGGL(k_fx_clear, dim3((unsigned)std::max<int64_t>((n + 255) / 256, 1)), dim3(256), 0, s, pfx, n,
                      h->vol_absmax);
   const double coef = D.step / D.n_pupil * (double)h->pix_samples_max;
-  const int Q = h->turn_stride, T = h->turn_quarters, m0 = a0 / Q;
-  // a chosen march mode or box edge takes one angle at a time
-  const int nq = h->vol_turn && h->forward_lanes == 0 && h->boxes.B == kBox ? members_together(h, a0, na) : 1;
   if (nq > 1) {
     const vam_status st = nq == 4 && segments_a_box(h, kQuadSegments)
                               ? forward_members<4>(h, volume, proj, m0, nq, fmt, coef, s)
@@ -1587,8 +1611,7 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
   } else {
     // one turned copy of the volume per member in the call, beside each other
     // (in vol_turn) and one launch, or without that memory one after the other
-    const int m1 = (a0 + na - 1) / Q;
-    const bool together = m0 == m1 || h->vol_turn;
+    const bool together = m0 == m1 || turned;
     void* vol = m0 == m1 ? (void*)h->vol_pad : h->vol_turn;
     for (int m = m0; m <= m1; ++m) {
       pad_turned<1>(h, volume, fmt, together ? (uint32_t*)vol + (m - m0) * h->pad_voxels : (uint32_t*)h->vol_pad,
@@ -1631,7 +1654,7 @@ static vam_status forward_box_t(vam_geometry* h, const void* volume, PT* proj, i
     // much, halve the chunk until the allocation succeeds
     int64_t angles = std::max<int64_t>(1, std::min<int64_t>(D.n_angles, (int64_t(1) << 31) / slots));
     for (;;) {
-      const hipError_t e = dev_alloc((void**)&h->seg_part, slots * angles * sizeof(float));
+      const hipError_t e = dev_alloc_for(h, (void**)&h->seg_part, slots * angles * sizeof(float));
       if (e == hipSuccess) break;
       h->seg_part = nullptr;
       if (e != hipErrorOutOfMemory || angles == 1) return hip_check(e, "allocating segment partial sums");

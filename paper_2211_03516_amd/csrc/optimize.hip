@@ -87,10 +87,10 @@ static vam_status optimize_buffers(vam_geometry* h, int64_t nvox, int64_t nproj)
   if (h->resid) return VAM_OK;
   float *resid = nullptr, *grad = nullptr, *dose = nullptr;
   double* part = nullptr;
-  hipError_t e = dev_alloc((void**)&resid, nvox * sizeof(float));
-  if (e == hipSuccess) e = dev_alloc((void**)&grad, nproj * sizeof(float));
-  if (e == hipSuccess) e = dev_alloc((void**)&dose, nvox * sizeof(float));
-  if (e == hipSuccess) e = dev_alloc((void**)&part, (kLossBlocks + 1) * sizeof(double));
+  hipError_t e = dev_alloc_for(h, (void**)&resid, nvox * sizeof(float));
+  if (e == hipSuccess) e = dev_alloc_for(h, (void**)&grad, nproj * sizeof(float));
+  if (e == hipSuccess) e = dev_alloc_for(h, (void**)&dose, nvox * sizeof(float));
+  if (e == hipSuccess) e = dev_alloc_for(h, (void**)&part, (kLossBlocks + 1) * sizeof(double));
   if (e != hipSuccess) {
     void* ptrs[] = {resid, grad, dose, part};
     for (void* p : ptrs)

@@ -392,7 +392,7 @@ vam_status launch_back(vam_geometry* h, const void* proj, vam_dtype proj_t, floa
                                      "set the box edge again or create a new geometry");
   if (!acc) {
     if (!h->dose_pad64)
-      VAM_HIP_TRY(dev_alloc((void**)&h->dose_pad64, (h->pad_voxels + kAccTail) * sizeof(double)),
+      VAM_HIP_TRY(dev_alloc_for(h, (void**)&h->dose_pad64, (h->pad_voxels + kAccTail) * sizeof(double)),
                   "allocating the dose accumulator");
     acc = h->dose_pad64;
   }

@@ -52,6 +52,17 @@ hipError_t dev_alloc(void** p, size_t bytes) {
   return hipMalloc(p, bytes);
 }
 
+hipError_t dev_alloc_for(vam_geometry* h, void** p, size_t bytes) {
+  hipError_t e = dev_alloc(p, bytes);
+  if (e != hipErrorOutOfMemory || !h->vol_turn || h->vol_turn_captured) return e;
+  (void)hipGetLastError();  // handled here
+  e = hipDeviceSynchronize();  // a forward may still read them
+  if (e != hipSuccess) return e;
+  (void)hipFree(h->vol_turn);
+  h->vol_turn = nullptr;
+  return dev_alloc(p, bytes);
+}
+
 // ------------------------------------------------------------ device math --
 
 struct TraceParams {
@@ -371,7 +382,7 @@ static void free_handle(vam_geometry* h) {
     if (h->ev[i]) (void)hipEventDestroy(h->ev[i]);
   free_boxes(h);
   free_gather(h);
-  void* ptrs[] = {h->rays, h->ray64, h->angle_cs, h->vol_pad, h->vol_turn, h->dose_pad64,
+  void* ptrs[] = {h->rays, h->ray64, h->angle_cs, h->vol_pad, h->dose_pad64,
                   h->resid, h->grad, h->dose_tmp, h->loss_part, h->proj_fx, h->vol_absmax};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);

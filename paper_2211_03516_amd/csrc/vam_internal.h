@@ -102,8 +102,8 @@ struct vam_geometry {
   // member turn_quarters quarter turns after the one before; turn_members is
   // 1 when the angles have no such structure
   int turn_members, turn_quarters, turn_stride;
-  void* vol_turn;                // padded volume, the members' turned copies interleaved, on first use
-  int vol_turn_failed;           // its allocation failed once: one angle at a time from then on
+  void* vol_turn;                // padded volume, the members' turned copies interleaved (see turned_volumes)
+  int vol_turn_captured;         // a captured graph may hold its address: not given back
   double* dose_pad64;            // padded dose accumulator (+ kAccTail words), allocated on first use:
                                  // 64-bit integers (box deposit) or FP64 (ray-driven deposit)
   // optimisation buffers, allocated on first vam_optimize_step
@@ -222,6 +222,9 @@ vam_status hip_check(hipError_t e, const char* what);
 // Every device allocation of the library goes through dev_alloc, so that
 // vam_debug_fail_allocations can make a chosen one fail.
 hipError_t dev_alloc(void** p, size_t bytes);
+// The same for what a call on h has to have: if memory is short, the forward's
+// turned volumes (h->vol_turn) are given back first.
+hipError_t dev_alloc_for(vam_geometry* h, void** p, size_t bytes);
 
 // projector launches (project.hip)
 vam_status launch_forward(vam_geometry* h, const void* vol, vam_dtype vol_t,

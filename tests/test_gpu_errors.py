@@ -137,3 +137,78 @@ def test_failed_first_forward_allocations():
         assert bool((out == 7.0).all())
         assert torch.equal(g.forward(t), ref)
         g.close()
+
+
+def test_turned_volumes_only_where_calls_need_them():
+    """The volumes of the angles a quarter turn apart: not allocated by calls
+    inside one quarter, tried again after an attempt that failed, and given back
+    when memory is short at an allocation that a call has to make; the results
+    are the same bits throughout."""
+    p = _p(24, n_angles=8)
+    x, y = _inputs(p, 53)
+    g0 = vam.Geometry(p)
+    P0, D0 = g0.forward(x), g0.back(y)
+    g0.close()
+    g = vam.Geometry(p)
+    say("inside one quarter")
+    vam.debug_fail_allocations(3)              # projections, maximum, then the next one
+    assert torch.equal(g.forward(x, angle_begin=2, angle_count=2), P0[2:4])
+    with pytest.raises(vam.VamError):
+        g.back(y)                              # ... which is the dose accumulator
+    say("an attempt that fails")
+    vam.debug_fail_allocations(1)
+    assert torch.equal(g.forward(x), P0)
+    say("tried again")
+    vam.debug_fail_allocations(1)
+    assert torch.equal(g.forward(x), P0)       # this attempt fails again, so the hook is off now
+    assert torch.equal(g.forward(x), P0)       # and this one is made
+    say("given back")
+    for k in (1, 2):                           # with and without them in the handle
+        vam.debug_fail_allocations(1)
+        if k == 1:
+            assert torch.equal(g.back(y), D0)
+            vam.debug_fail_allocations(0)
+        else:
+            with pytest.raises(vam.VamError):
+                g.optimize_step(x, y.clone(), lr=0.1, want_loss=False)
+    assert torch.equal(g.forward(x), P0)
+    g.close()
+
+
+def test_forward_of_a_whole_turn_captured_before_its_volumes_exist():
+    """A graph captured after calls inside one quarter only: captured calls
+    allocate nothing, and every replay gives the eager bits, also with eager
+    calls in between that allocate the turned volumes, and after the handle
+    was short of memory."""
+    p = _p(24, n_angles=8)
+    x, y = _inputs(p, 54)
+    g = vam.Geometry(p)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        g.forward(x, angle_begin=0, angle_count=2)
+        out, out2 = torch.empty((8, 24, 24), device=DEV), torch.empty((8, 24, 24), device=DEV)
+        s.synchronize()
+        early, late = torch.cuda.CUDAGraph(), torch.cuda.CUDAGraph()
+        say("capture before the volumes exist")
+        with torch.cuda.graph(early, stream=s):
+            g.forward(x, out=out)
+        ref = g.forward(x)
+        say("capture after")
+        with torch.cuda.graph(late, stream=s):
+            g.forward(x, out=out2)
+        for i in range(4):
+            x.mul_(0.5).add_(0.1 * i)
+            early.replay()
+            late.replay()
+            ref = g.forward(x)
+            s.synchronize()
+            assert torch.equal(out, ref) and torch.equal(out2, ref), i
+            if i == 1:                         # a captured call uses the volumes: they stay
+                vam.debug_fail_allocations(1)
+                with pytest.raises(vam.VamError):
+                    g.back(y)
+                vam.debug_fail_allocations(0)
+            if i == 2:
+                g.back(y)
+        s.synchronize()
+    g.close()
