@@ -99,7 +99,11 @@ typedef struct vam_geometry* vam_geometry_t;
 /* Trace every ray of every pixel and pupil point through the optics and the
  * vial walls (Sec. 2.1; Fresnel factors of Sec. 2.5) in FP64 on the device
  * and keep the resin segments as the handle's ray table.  Allocates the ray
- * table and the padded working volumes (owned by the handle).  Synchronises
+ * table and the padded working volumes (owned by the handle).  The table holds
+ * 36 bytes for each run of a ray's samples in one box, once for the forward
+ * projection and once, cut where the ray climbs a voxel, for the deposit; where
+ * those would be 2^31 or more, or memory is short of them, the deposit keeps
+ * them uncut and is slower (same operator).  Synchronises
  * `stream` before returning.  Errors: VAM_ERR_INVALID_ARG for a descriptor
  * outside the ranges above or a NULL `out`; VAM_ERR_OUT_OF_MEMORY;
  * VAM_ERR_HIP. */

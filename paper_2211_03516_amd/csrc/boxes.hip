@@ -377,26 +377,32 @@ static bool sort_segments(std::vector<int4>& hs, const std::vector<int>& begin, 
 }
 
 // One table of segments, in the order `order` inside each box, packed into
-// compact records: the forward's runs of samples in a box, or (SPLIT) the
-// deposit's, which also end where the z cell changes (z does not turn, so
-// a segment then has one z cell at every angle).  ids: the boxes that hold
-// segments (the same for both); host: the sorted segments, for the caller.
-// Synchronises the stream.
+// compact records: the forward's or the deposit's runs of samples in a box, or
+// (SPLIT, deposit) runs that also end where the z cell changes (z does not turn,
+// so a segment then has one z cell at every angle).  ids: the boxes that hold
+// segments (the same for all); host: the sorted segments, for the caller.
+// Synchronises the stream.  Host memory that runs out is thrown.
 template <bool SPLIT>
-static vam_status build_table(vam_geometry* h, const BoxGrid& G, int order, SegTable& t, std::vector<int64_t>& ids,
+static vam_status build_table(vam_geometry* h, const BoxGrid& G, bool deposit, SegTable& t, std::vector<int64_t>& ids,
                               std::vector<int4>& host, hipStream_t s) {
   const vam_geometry_desc& D = h->desc;
   const int nb_all = G.nbx * G.nby * G.nbz;
-  int* ray_nseg = SPLIT ? nullptr : h->ray_nseg;
+  int* ray_nseg = deposit ? nullptr : h->ray_nseg;
   // staging: box counts, offsets and cursors, then the unsorted segments
-  int* count = nullptr;
-  int4* segs = nullptr;
-  auto release = [&]() {
-    if (count) (void)hipFree(count);
-    if (segs) (void)hipFree(segs);
-    count = nullptr;
-    segs = nullptr;
-  };
+  struct Staging {
+    int* count = nullptr;
+    int4* segs = nullptr;
+    void release() {
+      if (count) (void)hipFree(count);
+      if (segs) (void)hipFree(segs);
+      count = nullptr;
+      segs = nullptr;
+    }
+    ~Staging() { release(); }
+  } staging;
+  int*& count = staging.count;
+  int4*& segs = staging.segs;
+  auto release = [&]() { staging.release(); };
   hipError_t e = dev_alloc((void**)&count, 2 * (int64_t)nb_all * sizeof(int));
   if (e != hipSuccess) return hip_check(e, "allocating box counts");
   int* off = count + nb_all;
@@ -408,9 +414,9 @@ static vam_status build_table(vam_geometry* h, const BoxGrid& G, int order, SegT
                        count, ray_nseg);
     e = hipGetLastError();
   }
-  std::vector<int> hc(nb_all), ns(SPLIT ? 0 : h->n_rays);
+  std::vector<int> hc(nb_all), ns(deposit ? 0 : h->n_rays);
   if (e == hipSuccess) e = hipMemcpyAsync(hc.data(), count, nb_all * sizeof(int), hipMemcpyDeviceToHost, s);
-  if (e == hipSuccess && !SPLIT)
+  if (e == hipSuccess && !deposit)
     e = hipMemcpyAsync(ns.data(), ray_nseg, h->n_rays * sizeof(int), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) {
@@ -433,7 +439,7 @@ static vam_status build_table(vam_geometry* h, const BoxGrid& G, int order, SegT
     release();
     return fail(VAM_ERR_UNSUPPORTED, "more than 2^31 ray segments");
   }
-  if (!SPLIT) {
+  if (!deposit) {
     // forward partial-sum slots rank * n_rays + ray must be 32-bit offsets
     h->max_seg_per_ray = ns.empty() ? 0 : *std::max_element(ns.begin(), ns.end());
     if ((int64_t)h->max_seg_per_ray * h->n_rays >= 0x7fffffffLL) {
@@ -476,14 +482,14 @@ static vam_status build_table(vam_geometry* h, const BoxGrid& G, int order, SegT
   }
   // (the sort also makes the order independent of the scheduling of the fill
   // kernel)
-  if (!sort_segments(host, begin, order, D.n_u, D.n_v, D.n_pupil)) {
+  if (!sort_segments(host, begin, deposit ? h->seg_order : h->seg_order_fwd, D.n_u, D.n_v, D.n_pupil)) {
     release();
     return fail(VAM_ERR_OUT_OF_MEMORY, "sorting the box segments: out of host memory");
   }
   e = hipMemcpyAsync(segs, host.data(), total * sizeof(int4), hipMemcpyHostToDevice, s);
   if (e == hipSuccess && h->n_boxes > 0) {
     hipLaunchKernelGGL(k_seg_pack, dim3((unsigned)h->n_boxes), dim3(256), 0, s, G, h->box_id, t.box_begin, segs,
-                       h->ray64, (int)h->n_rays, D.step, D.alpha, D.n_u * D.n_v, SPLIT ? 0 : 1, t.pw, t.dn, t.idx);
+                       h->ray64, (int)h->n_rays, D.step, D.alpha, D.n_u * D.n_v, deposit ? 0 : 1, t.pw, t.dn, t.idx);
     e = hipGetLastError();
   }
   if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -511,7 +517,7 @@ static vam_status build_boxes_into(vam_geometry* h, hipStream_t s) {
   VAM_HIP_TRY(dev_alloc((void**)&h->ray_nseg, h->n_rays * sizeof(int)), "allocating segment counts");
   std::vector<int64_t> ids;
   std::vector<int4> hs;
-  vam_status st = build_table<false>(h, G, h->seg_order_fwd, h->seg_fwd, ids, hs, s);
+  vam_status st = build_table<false>(h, G, false, h->seg_fwd, ids, hs, s);
   if (st != VAM_OK) return st;
   h->n_segments = (int64_t)hs.size();
   {
@@ -522,7 +528,26 @@ static vam_status build_boxes_into(vam_geometry* h, hipStream_t s) {
     for (const int4& sg : hs) per[sg.x % npix] += sg.z;
     h->pix_samples_max = per.empty() ? 0 : *std::max_element(per.begin(), per.end());
   }
-  st = build_table<true>(h, G, h->seg_order, h->seg_dep, ids, hs, s);
+  // The deposit's segments cut at z cells are about twice as many where rays
+  // climb.  Where they are too many, or memory is short of them, the deposit takes
+  // whole runs, one angle at a time (see k_back_box).
+  auto deposit_table = [&](auto build) {
+    try {
+      return build();
+    } catch (const std::bad_alloc&) {
+      return fail(VAM_ERR_OUT_OF_MEMORY, "building the deposit's segments: out of host memory");
+    }
+  };
+  h->deposit_whole = 0;
+  st = deposit_table([&] { return build_table<true>(h, G, true, h->seg_dep, ids, hs, s); });
+  if (st == VAM_ERR_UNSUPPORTED || st == VAM_ERR_OUT_OF_MEMORY) {
+    (void)hipGetLastError();  // handled here
+    clear_error();
+    free_table(h->seg_dep);
+    std::vector<int4>().swap(hs);
+    h->deposit_whole = 1;
+    st = deposit_table([&] { return build_table<false>(h, G, true, h->seg_dep, ids, hs, s); });
+  }
   if (st != VAM_OK) return st;
   VAM_HIP_TRY(dev_alloc((void**)&h->box_supp, std::max(h->n_boxes, 1) * sizeof(int)), "allocating support bounds");
   st = support_bound(h, G, s);
@@ -535,7 +560,12 @@ static vam_status build_boxes_into(vam_geometry* h, hipStream_t s) {
 
 vam_status build_boxes(vam_geometry* h, hipStream_t s) {
   free_boxes(h);
-  const vam_status st = build_boxes_into(h, s);
+  vam_status st;
+  try {
+    st = build_boxes_into(h, s);
+  } catch (const std::bad_alloc&) {
+    st = fail(VAM_ERR_OUT_OF_MEMORY, "building the box decomposition: out of host memory");
+  }
   if (st != VAM_OK) {
     free_boxes(h);  // nothing half-built stays behind; boxes_ready stays 0
     return st;
@@ -1760,27 +1790,34 @@ __device__ inline void flush8(int* acc, unsigned cur, const float* w) {
   atomicAdd(p + SZ + SY + 1, round_to_int(w[7]));
 }
 
-// zc: the segment's z cell in the footprint (one for all its samples).
-template <int SY, int SZ, bool CLAMP>
-__device__ inline void march_deposit(int* acc, const SegPos& g, int zc, float e, float hx, float hy, float r_hi,
-                                     float r_lo) {
+// zc: the segment's z cell in the footprint, one for all its samples (WHOLE: each
+// sample has its own, and zc is 0).
+template <int SY, int SZ, bool CLAMP, bool WHOLE>
+__device__ inline void march_deposit(int* acc, const SegPos& g, int zc, float e, float hx, float hy, float hz,
+                                     float r_hi, float r_lo) {
   // at whole coordinates (see cell_number)
-  auto cell_bytes = [](float x, float y) { return (unsigned)fmaf(y, (float)(SY * 4), x * 4.0f); };
+  auto cell_bytes = [](float x, float y, float z) {
+    const float yx = fmaf(y, (float)(SY * 4), x * 4.0f);
+    return (unsigned)(WHOLE ? fmaf(z, (float)(SZ * 4), yx) : yx);
+  };
   acc += zc * SZ;
   const float pz = g.pz - (float)zc;
   float w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   // byte offset of the cell whose corners w holds, starting at the first
   // sample's (w is zero until its first add)
-  unsigned cur = cell_bytes(floorf(coord<CLAMP>(g.k0, g.dx, g.px, hx)), floorf(coord<CLAMP>(g.k0, g.dy, g.py, hy)));
+  unsigned cur = cell_bytes(floorf(coord<CLAMP>(g.k0, g.dx, g.px, hx)), floorf(coord<CLAMP>(g.k0, g.dy, g.py, hy)),
+                            WHOLE ? floorf(coord<CLAMP>(g.k0, g.dz, pz, hz)) : 0.0f);
   // exact: a segment has fewer than 2^24 samples
   for (float kf = g.k0; kf <= g.k1; kf += 1.0f) {
     const float x = coord<CLAMP>(kf, g.dx, g.px, hx);
     const float y = coord<CLAMP>(kf, g.dy, g.py, hy);
-    const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y), fz = unit(fmaf(kf, g.dz, pz));
+    const float z = coord<CLAMP && WHOLE>(kf, g.dz, pz, hz);
+    const float fx = __builtin_amdgcn_fractf(x), fy = __builtin_amdgcn_fractf(y);
+    const float fz = WHOLE ? __builtin_amdgcn_fractf(z) : unit(z);
     const float z1 = e * fz, z0 = e - z1;
     const float y01 = z0 * fy, y00 = z0 - y01;
     const float y11 = z1 * fy, y10 = z1 - y11;
-    const unsigned ob = cell_bytes(x - fx, y - fy);
+    const unsigned ob = cell_bytes(x - fx, y - fy, z - fz);
     const bool fl = ob != cur;
     if (fl) flush8<SY, SZ>(acc, cur, w);
     const float keep = fl ? 0.0f : 1.0f;
@@ -1801,7 +1838,10 @@ __device__ inline void march_deposit(int* acc, const SegPos& g, int zc, float e,
 // dep_coef), pmax the largest |projection value| of the call (FP32 bits;
 // a NaN or infinity among them leaves acc untouched: the dose copy then
 // writes NaN everywhere).
-template <int B, typename PT, int NT>
+// WHOLE: segments are not cut at z cells (see build_boxes_into), so samples form
+// theirs (256^3, 360 angles of a thin lens: 179 ms; k_back_planes, which needs
+// them cut, 104).
+template <int B, typename PT, int NT, bool WHOLE>
 __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, const PT* __restrict__ proj,
                                                  unsigned long long* __restrict__ acc64,
                                                  const unsigned* __restrict__ pmax, double dep_coef) {
@@ -1843,11 +1883,11 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
     const float4 pw = Bp.seg.pw[si], dn = Bp.seg.dn[si];
     const SegPos g = seg_pos(pw, dn, seg_count(dn), f, c, s, sc, ss, P.step);
     const float e = pw.w * pv * S;  // sample weights in the fixed-point units
-    const int zc = min(max(seg_z_cell(dn) + (int)f.zoff, 0), f.WZ - 2);
+    const int zc = WHOLE ? 0 : min(max(seg_z_cell(dn) + (int)f.zoff, 0), f.WZ - 2);
     if (seg_inside(g, hx, hy, hz))
-      march_deposit<SY, SZ, false>(acc, g, zc, e, hx, hy, P.r_hi, P.r_lo);
+      march_deposit<SY, SZ, false, WHOLE>(acc, g, zc, e, hx, hy, hz, P.r_hi, P.r_lo);
     else
-      march_deposit<SY, SZ, true>(acc, g, zc, e, hx, hy, P.r_hi, P.r_lo);
+      march_deposit<SY, SZ, true, WHOLE>(acc, g, zc, e, hx, hy, hz, P.r_hi, P.r_lo);
   }
   __syncthreads();
   unsigned long long* tile = acc64 + tile_base(Bp, f);
@@ -2172,10 +2212,12 @@ static void launch_back_box(vam_geometry* h, const MarchParams& P, const PT* pro
       hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, s, Pa, part, proj + a0 * Bp.npix, a64, pm, coef);
     });
   };
-  if (h->deposit_threads == 512)
-    launch(k_back_box<B, PT, 512>, 512);
+  if (h->deposit_whole)
+    launch(k_back_box<B, PT, 256, true>, 256);
+  else if (h->deposit_threads == 512)
+    launch(k_back_box<B, PT, 512, false>, 512);
   else
-    launch(k_back_box<B, PT, 256>, 256);
+    launch(k_back_box<B, PT, 256, false>, 256);
 }
 
 template <typename PT>
@@ -2191,7 +2233,7 @@ static void launch_back_box_t(vam_geometry* h, const MarchParams& P, const PT* p
   // a box) 4.39 / 4.36 ms, 2 points 4.96 / 5.12, 4 points (650) 5.05 / 5.27; on
   // dark-edged projections 2.98 / 2.72, 3.35 / 3.31, 3.90 / 3.63, with a thin
   // lens 1.93 / 1.90, 2.13 / 2.10, 2.48 / 2.65; 64^3, 1 point 0.64 / 0.60.
-  if (h->boxes.B == kBox && h->desc.step <= 0.99 && h->deposit_threads == 256 &&
+  if (h->boxes.B == kBox && h->desc.step <= 0.99 && h->deposit_threads == 256 && !h->deposit_whole &&
       h->seg_dep.n >= 500 * (int64_t)h->n_boxes && members_together(h, P.a0, na) == 4) {
     // two workgroups fit a CU's LDS: 24 waves at 77 registers (256^3: 512 lanes
     // 141 ms, 768 120; 1024 need 64 registers to fit twice, 170 in one)

@@ -120,6 +120,7 @@ struct vam_geometry {
   int seg_order;                 // deposit order of segments inside a box (see sort_segments)
   int seg_order_fwd;             // forward order of segments inside a box
   int deposit_threads;           // workgroup size of the box deposit (256 or 512)
+  int deposit_whole;             // the deposit's segments are not cut at z cells (see build_boxes_into)
   int xcd_forward, xcd_deposit;  // work order of the box kernels (see work_item; -1 = by kernel)
   vam::BoxGrid boxes;
   int boxes_ready;               // 1 once the decomposition is complete; 0 after a failed rebuild

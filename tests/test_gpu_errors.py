@@ -212,3 +212,50 @@ def test_forward_of_a_whole_turn_captured_before_its_volumes_exist():
                 g.back(y)
         s.synchronize()
     g.close()
+
+
+@pytest.mark.parametrize("edge", [8, 12, 16])
+def test_deposit_from_segments_not_cut_at_z_cells(edge):
+    """Where there is no room for the deposit's segments cut at z cells, it takes
+    whole runs of a box: the same operator against the oracle, with rays that
+    climb little, much and not at all, in every storage type and over any
+    angles; the forward keeps its bits."""
+    n, na = 30, 8
+    for what, kw in (("thin lens", {}), ("steep", {"projector": 0, "focus": 0.0, "pupil": 0.9, "step": 0.3}),
+                     ("long steps", {"projector": 0, "focus": 0.0, "pupil": 0.7, "step": 1.3}),
+                     ("along the lattice", {"projector": 0, "focus": 0.0, "pupil": 0.0})):
+        p = dict(_p(n, n_angles=na), nz=27, **kw)
+        og = oracle.Geometry(p)
+        rng = synth.SplitMix64(59)
+        x = torch.from_numpy(rng.uniform(27 * n * n).reshape(27, n, n).astype(np.float32)).to(DEV)
+        y = torch.from_numpy((rng.uniform(na * n * n).reshape(na, n, n) - 0.3).astype(np.float32))
+        g = vam.Geometry(p)
+        g.set_box_edge(edge)
+        P0, D0 = g.forward(x), g.back(y.to(DEV))
+        uncut = 0
+        for k in range(9, 40):             # the set-up's allocations after the forward's segments
+            vam.debug_fail_allocations(k)
+            try:
+                g.set_box_edge(edge)
+            except vam.VamError as e:
+                assert e.status == vam.VAM_ERR_OUT_OF_MEMORY
+                continue
+            finally:
+                vam.debug_fail_allocations(0)
+            D = g.back(y.to(DEV))
+            if torch.equal(D, D0):
+                break                      # the rebuild makes fewer than k allocations
+            uncut += 1
+            say("%s, edge %d, allocation %d" % (what, edge, k))
+            assert torch.equal(g.forward(x), P0)
+            if uncut > 1:
+                continue
+            for dt in (torch.float32, torch.bfloat16, torch.float16):
+                for a0, m in ((0, na), (3, 4)):
+                    yy = y[a0:a0 + m].to(dt)
+                    ref = oracle.adjoint(og, yy.double().numpy(), a0=a0, na=m)
+                    got = g.back(yy.to(DEV), angle_begin=a0).cpu().numpy()
+                    assert np.linalg.norm(got - ref) <= 1e-5 * np.linalg.norm(ref)
+                    assert np.abs(got - ref).max() <= 1e-5 * np.abs(ref).max()
+        assert uncut >= 1 or what == "along the lattice", what
+        g.close()
