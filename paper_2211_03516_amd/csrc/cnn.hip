@@ -216,12 +216,14 @@ __global__ __launch_bounds__(512) void k_conv(ConvArgs g) {
       for (int s = S0; s < S1; ++s) {
         const int lo = 16 * s, hi = lo + 8;
         const int o = col_offset<CP, PITCH>(lo);
-        // past the last tap (weights zero) the upper half rereads the lower's
+        // past the last tap (weights zero) the upper half rereads the lower's and
+        // takes zeros (an infinity there would make NaN)
         const bf16x8 ws = s < KR ? w[s < KR ? s : 0] : *(const bf16x8*)(wl + (((s - KR) * NB + nb) * 64 + lane) * 8);
         const int at = hi >= 9 * CP ? base : lo / CP == hi / CP ? at_chan : hi / CP % 3 != 0 ? at_tap : at_row;
 #pragma unroll
         for (int b = 0; b < MB; ++b) {
-          const bf16x8 a = *(const bf16x8*)(in + at + o + b * 2 * kTileP * PITCH);
+          bf16x8 a = *(const bf16x8*)(in + at + o + b * 2 * kTileP * PITCH);
+          if (hi >= 9 * CP && half != 0) a = bf16x8{};
           acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ws, a, acc[b], 0, 0, 0);
         }
       }

@@ -139,3 +139,51 @@ def test_cnn_learns_a_fixed_filter():
     say("fixed filter: loss %.3e -> %.3e" % (first, last))
     assert last < first / 20
     net.close()
+
+
+def _columns(a):
+    """[C, H, W] -> [9, C, H, W]: the nine neighbours of each pixel, zero outside."""
+    c, h, w = a.shape
+    p = np.zeros((c, h + 2, w + 2))
+    p[:, 1:-1, 1:-1] = a
+    return np.stack([p[:, dy:dy + h, dx:dx + w] for dy in range(3) for dx in range(3)])
+
+
+def _kind(a):
+    """0 finite, 1 and -1 infinities, 2 NaN."""
+    return np.where(np.isnan(a), 2, np.where(np.isinf(a), np.sign(a), 0))
+
+
+# Sizes with and without pixels of the last tiles outside the image; channel
+# counts whose nine taps fill the products' steps of 16 and leave half of one.
+@pytest.mark.parametrize("C,H,W", [(8, 17, 33), (24, 9, 17), (40, 16, 32), (64, 15, 31), (16, 8, 16), (32, 24, 40)])
+def test_cnn_of_infinite_inputs(C, H, W):
+    """An infinite input reaches the pixels whose neighbourhood holds it and no
+    others: outputs are infinite or NaN where the sum of products is."""
+    L, n, (s0, s1) = 2, 32, (0.05, 2.0)
+    rng = synth.SplitMix64(C)
+    net = vam.Cnn(L, C, H, W, max_batch=n, in_scale=(s0, s1))
+    p = synth.cnninit.he_init(L, C, seed=C, zero_last=False)
+    net.set_params(p)
+    (w1, b1), (w2, b2) = [(w.numpy(), b.numpy()) for w, b in ocnn.unpack(p, L, C)]
+    x = rng.uniform(n * 2 * H * W).reshape(n, 2, H, W)
+    for y0, x0 in ((H - 1, W - 1), (H - 1, W // 2), (0, 0), (H // 2, W - 1)):
+        for value in (np.inf, -np.inf):
+            xi = x.copy()
+            xi[1, 0, y0, x0] = value
+            xd = torch.from_numpy(xi).float().to(DEV)
+            got = net.forward(xd).cpu().numpy()
+            ref_y = np.zeros((n, H, W))
+            with np.errstate(invalid="ignore"):
+                for i in range(n):
+                    a0 = xi[i] * np.array([s0, s1])[:, None, None]
+                    c0 = _columns(a0)
+                    z1 = sum(w1[:, c, k // 3, k % 3][:, None, None] * c0[k, c] for k in range(9) for c in range(2))
+                    z1 = z1 + b1[:, None, None]
+                    a1 = np.where(z1 > 0, z1, 0.0)
+                    c1 = _columns(a1)
+                    z = sum(w2[0, c, k // 3, k % 3] * c1[k, c] for k in range(9) for c in range(C)) + b2[0]
+                    ref_y[i] = z / s1 + xi[i, 1]
+            say("infinite input at (%d, %d): %d outputs not finite" % (y0, x0, (~np.isfinite(ref_y)).sum()))
+            assert np.array_equal(_kind(got), _kind(ref_y))
+    net.close()
