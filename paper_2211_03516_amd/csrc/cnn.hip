@@ -388,6 +388,8 @@ __global__ __launch_bounds__(192 * CIB * COB) void k_wgrad(WgradArgs g) {
 #pragma unroll
   for (int dx = 0; dx < 3; ++dx)
     for (int i = 0; i < 16; ++i) acc[dx][i] = 0.0f;
+  __shared__ int again;
+  if (threadIdx.x == 0) again = 0;
   int t = blockIdx.x, cur = 0;
   if (t < g.tiles) {
     fetch(t);
@@ -421,6 +423,45 @@ __global__ __launch_bounds__(192 * CIB * COB) void k_wgrad(WgradArgs g) {
     __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
     if (more) stage(tile[cur ^ 1]);
     __syncthreads();
+  }
+  // Pixels of the last tiles outside the image have zero gradients, but a
+  // neighbour of theirs may be infinite, and 0 x Inf is NaN: sums that are not
+  // finite are formed again without those pixels.
+  if (g.H % TH != 0 || g.W % kTile != 0) {
+    float zero = 0.0f;
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) zero = fmaf(acc[dx][i], 0.0f, zero);
+    if (zero != 0.0f) again = 1;
+    __syncthreads();
+    if (again != 0) {
+#pragma unroll
+      for (int dx = 0; dx < 3; ++dx)
+        for (int i = 0; i < 16; ++i) acc[dx][i] = 0.0f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) bias[q] = 0.0f;
+      for (t = blockIdx.x; t < g.tiles; t += gridDim.x) {
+        fetch(t);
+        stage(tile[0]);
+        __syncthreads();
+        const int rest = t % (g.tiles_x * g.tiles_y), rows = min(TH, g.H - rest / g.tiles_x * TH);
+        const int columns = g.W - rest % g.tiles_x * kTile - 8 * (lane >> 5);  // of the lane's 8 pixels
+#pragma unroll 1
+        for (int y = 0; y < rows; ++y) {
+          const bf16x8 b = operand(tile[0] + at_g + y * kTile * PG, PG);
+#pragma unroll
+          for (int dx = 0; dx < 3; ++dx) {
+            bf16x8 a = operand(tile[0] + at_a + (y * kTileP + dx) * PA, PA);
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+              if (q >= columns) a[q] = (__bf16)0.0f;
+            acc[dx] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc[dx], 0, 0, 0);
+          }
+        }
+        __syncthreads();
+      }
+    }
   }
   float* part = g.part + (int64_t)blockIdx.x * g.stride;
 #pragma unroll

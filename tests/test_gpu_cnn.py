@@ -159,7 +159,9 @@ def _kind(a):
 @pytest.mark.parametrize("C,H,W", [(8, 17, 33), (24, 9, 17), (40, 16, 32), (64, 15, 31), (16, 8, 16), (32, 24, 40)])
 def test_cnn_of_infinite_inputs(C, H, W):
     """An infinite input reaches the pixels whose neighbourhood holds it and no
-    others: outputs are infinite or NaN where the sum of products is."""
+    others: outputs are infinite or NaN where the sum of products is, and
+    weight gradients are finite where no product of theirs has a factor that
+    is not."""
     L, n, (s0, s1) = 2, 32, (0.05, 2.0)
     rng = synth.SplitMix64(C)
     net = vam.Cnn(L, C, H, W, max_batch=n, in_scale=(s0, s1))
@@ -167,13 +169,16 @@ def test_cnn_of_infinite_inputs(C, H, W):
     net.set_params(p)
     (w1, b1), (w2, b2) = [(w.numpy(), b.numpy()) for w, b in ocnn.unpack(p, L, C)]
     x = rng.uniform(n * 2 * H * W).reshape(n, 2, H, W)
+    t = rng.uniform(n * H * W).reshape(n, H, W)
     for y0, x0 in ((H - 1, W - 1), (H - 1, W // 2), (0, 0), (H // 2, W - 1)):
         for value in (np.inf, -np.inf):
             xi = x.copy()
             xi[1, 0, y0, x0] = value
-            xd = torch.from_numpy(xi).float().to(DEV)
+            xd, td = torch.from_numpy(xi).float().to(DEV), torch.from_numpy(t).float().to(DEV)
             got = net.forward(xd).cpu().numpy()
-            ref_y = np.zeros((n, H, W))
+            net.loss_grad(xd, td)
+            grads = [g.numpy() for layer in ocnn.unpack(net.grads(), L, C) for g in layer]
+            ref_y, ref_g = np.zeros((n, H, W)), None
             with np.errstate(invalid="ignore"):
                 for i in range(n):
                     a0 = xi[i] * np.array([s0, s1])[:, None, None]
@@ -184,6 +189,18 @@ def test_cnn_of_infinite_inputs(C, H, W):
                     c1 = _columns(a1)
                     z = sum(w2[0, c, k // 3, k % 3] * c1[k, c] for k in range(9) for c in range(C)) + b2[0]
                     ref_y[i] = z / s1 + xi[i, 1]
-            say("infinite input at (%d, %d): %d outputs not finite" % (y0, x0, (~np.isfinite(ref_y)).sum()))
+                    g2 = 2.0 * (z + s1 * xi[i, 1] - s1 * t[i]) / (n * H * W)
+                    flipped = w2[0, :, ::-1, ::-1]
+                    cg = _columns(g2[None])[:, 0]
+                    g1 = sum(flipped[:, k // 3, k % 3][:, None, None] * cg[k] for k in range(9))
+                    g1 = np.where(a1 > 0, g1, 0.0)
+                    dw1 = np.stack([(c0[k][None] * g1[:, None]).sum(axis=(2, 3)) for k in range(9)], axis=-1)
+                    dw2 = np.stack([(c1[k] * g2).sum(axis=(1, 2)) for k in range(9)], axis=-1)
+                    gi = [dw1.reshape(C, 2, 3, 3), g1.sum(axis=(1, 2)), dw2.reshape(1, C, 3, 3), g2.sum().reshape(1)]
+                    ref_g = gi if ref_g is None else [u + v for u, v in zip(ref_g, gi)]
+            say("infinite input at (%d, %d): %d outputs not finite, %s gradients finite"
+                % (y0, x0, (~np.isfinite(ref_y)).sum(), [int(np.isfinite(g).sum()) for g in ref_g]))
             assert np.array_equal(_kind(got), _kind(ref_y))
+            for got_g, want in zip(grads, ref_g):
+                assert np.array_equal(np.isfinite(got_g), np.isfinite(want))
     net.close()
