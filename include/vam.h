@@ -306,10 +306,11 @@ vam_status vam_export_rays(vam_geometry_t h, double* out);
  *                   a voxel apart, so they often read the same LDS words);
  *                   3 = one lane that keeps the current cell's LDS words in
  *                   registers and reads LDS only when its cell changes
- *                   (the same bits as 1); 0 = default: 3 with FP32 cells of
- *                   a voxel and its x neighbour, and at the default box edge
+ *                   (the same bits as 1); 0 = default: at the default box
+ *                   edge 3 with FP32 cells of a voxel and its x neighbour, and
  *                   the angles of whole or half turns that lie whole quarter
- *                   turns apart together (the same bits as 1).
+ *                   turns apart together, at the others 3, or 1 for FP16
+ *                   volumes (the same bits as 1).
  * A failed rebuild (ops 2, 4, 7) leaves the handle without a box
  * decomposition: the box kernels then return VAM_ERR_INVALID_ARG until a
  * rebuild succeeds.  Errors: VAM_ERR_BAD_HANDLE, VAM_ERR_INVALID_ARG for an

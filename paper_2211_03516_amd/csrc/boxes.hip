@@ -1380,7 +1380,8 @@ template <int B, int FMT, bool FX>
 static void launch_forward_box_f(hipStream_t s, const MarchParams& P, const BoxParams& Bp, const uint32_t* vol,
                                  const FwdOut& o) {
   if constexpr (FX) {
-    if (o.mode == kMarchCells) return launch_forward_box_m<B, FMT, FX, kMarchCells>(s, P, Bp, vol, o);
+    if constexpr (B == kBox)
+      if (o.mode == kMarchCells) return launch_forward_box_m<B, FMT, FX, kMarchCells>(s, P, Bp, vol, o);
     if (o.mode == kMarchCached) return launch_forward_box_m<B, FMT, FX, kMarchCached>(s, P, Bp, vol, o);
     if (o.mode == kMarchPair) return launch_forward_box_m<B, FMT, FX, kMarchPair>(s, P, Bp, vol, o);
   }
@@ -1517,9 +1518,10 @@ static int members_together(const vam_geometry* h, int a0, int na) {
 // chosen: blocks of at most 16, and at least four blocks, so that the XCDs'
 // parts of a block's boxes are alike (45 of them in blocks of 16 / 12: 128^3 2.35
 // / 2.23 ms, one at a time in FP16 1.11 / 1.01, 256^3 telecentric 18.9 / 18.3; 90
-// in blocks of 16 / 12, 256^3: 64.3 / 67.0).
+// in blocks of 16 / 12, 256^3: 64.3 / 67.0).  Edges 8 and 16: blocks of 16 (30 of
+// 90 angles of 128^3 at edge 8 in blocks of 8 / 15: 2.34 / 2.13 ms).
 static int forward_order(const vam_geometry* h, int na) {
-  return h->xcd_forward >= 0 ? h->xcd_forward : std::max(2, std::min(16, (na + 3) / 4));
+  return h->xcd_forward >= 0 ? h->xcd_forward : h->boxes.B != kBox ? 16 : std::max(2, std::min(16, (na + 3) / 4));
 }
 
 // Segments a box from which the forward's cells take 16 bytes, so that two
@@ -1655,8 +1657,13 @@ static vam_status forward_box_fx(vam_geometry* h, const void* volume, PT* proj, 
       Bp.member0 = together ? m0 : m;
       // (128^3, 60 of 180 angles, FP32: one lane 1.75 ms, its words in
       // registers 1.47, FP32 cells 1.45; 64^3, 180 angles 0.51 and 0.48; FP16,
-      // 45 angles of 128^3: 1.16, 1.16, 1.14)
-      const int mode = h->forward_lanes ? h->forward_lanes : kMarchCells;
+      // 45 angles of 128^3: 1.16, 1.16, 1.14.  At edge 16 the wide cells leave one
+      // workgroup a CU: 90 angles of 128^3, FP32 / FP16 words in registers or one
+      // lane 5.8 / 4.6 ms, FP32 cells 7.6 / 7.3; edge 8 about alike.)
+      const int mode = h->forward_lanes          ? h->forward_lanes
+                       : h->boxes.B == kBox      ? kMarchCells
+                       : fmt == kVolF16Pairs     ? kMarchOne
+                                                 : kMarchCached;
       const FwdOut o{nullptr, 0, pfx + (first - a0) * npix, h->vol_absmax, coef, mode};
       launch_forward_box_edge<true>(h->boxes.B, s, march_params(h, first), Bp, fmt,
                                     together ? (const uint32_t*)vol : (const uint32_t*)h->vol_pad, o);
