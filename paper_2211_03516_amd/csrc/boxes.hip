@@ -302,8 +302,8 @@ static vam_status alloc_table(SegTable& t, int64_t n) {
 //     along a row, rows two apart);
 //  11, 12, 13: order 10, then the whole box (11) or each run of 512 (12) or
 //     2048 (13) consecutive segments by decreasing length (the plane-by-plane
-//     deposit at 256^3: runs of 512 / 1024 / 1536 / 4096 segments 129 / 118 /
-//     116 / 113 ms, the whole box 111);
+//     deposit at 256^3: runs of 512 / 2048 segments 118 / 107 ms, the whole box
+//     105);
 //  14, 15, 16: by ray, then each run of 256 (14) or 1024 (15) segments, or
 //     the whole box (16), by decreasing length in steps of two samples
 //     (ties keep the ray order).
@@ -986,7 +986,7 @@ constexpr int kMarchOne = 1, kMarchPair = 2, kMarchCached = 3, kMarchCells = 4;
 // S_even + r S_odd); their samples are half a voxel apart, so they often
 // read the same LDS words, which the LDS serves as one broadcast.
 // kMarchCached: one lane, the current cell's LDS words kept in registers.
-// kMarchCells (the default): the same with FP32 cells of a voxel and its x
+// kMarchCells (the default at the default box edge): the same with FP32 cells of a voxel and its x
 // neighbour, so a sample's corners are four 8-byte reads (7.7 clocks for 64
 // unrelated lanes, as much as one of 4 bytes) and 16-bit values are widened once
 // a cell.  Bound by vector issue and LDS reads, each about 70 % of the time.
@@ -1942,17 +1942,18 @@ __global__ __launch_bounds__(NT) void k_back_box(MarchParams P, BoxParams Bp, co
 //    integer hi 2^32 + lo of two members' 32-bit sums, whose bound is
 //    k_back_box's: a corner gets at most one add per sample of its support.
 //
-// 256^3, 360 angles: 104 ms against 181 corner by corner (when first built 110.9,
-// as the figures below are; 91.7 against
-// 118.0 on projections dark outside a part's shadow); 128^3, 180 angles, 8
-// pupil points 4.50 against 6.49; one pupil point 4.40 against 4.55 (there the
-// adds into the voxels bind, the same for both).  Without its LDS adds and
-// their conversions it takes 82 ms, without the adds into the voxels 105: the
-// adds and the vector work both bind, and neither hides the other fully.
-// Two members, or one, per workgroup measured (128^3: 90 angles in pairs 3.01
-// against 3.30 corner by corner, but 23.4 against 21.0 at 256^3 telecentric
-// on dark-edged projections, and one angle 2.30 against 1.79): per member the
-// vector work then grows past what the adds save, so those go corner by corner.
+// 256^3, 360 angles, 16 pupil points: 105 ms against 193 corner by corner with
+// every pixel lit, 87 against 127 on projections dark outside a part's shadow
+// (more sizes at launch_back_box_t).  With few segments a box the adds into the
+// voxels bind, the same for both.  In the kernel's first form, which took 111 ms,
+// the time without its LDS adds and their conversions was 82 ms, without the
+// adds into the voxels 105: the adds and the vector work both bind, and neither
+// hides the other fully.
+// Two members, or one, per workgroup were slower in that form (128^3: 90 angles
+// in pairs 3.01 ms against 3.30 corner by corner, but 23.4 against 21.0 at 256^3
+// telecentric on dark-edged projections, and one angle 2.30 against 1.79): per
+// member the vector work grows past what the adds save, so those go corner by
+// corner.
 
 // Largest value of the wave.
 __device__ inline float wave_max(float m) {
@@ -2199,10 +2200,11 @@ double deposit_coef(const vam_geometry* h, int na) {
 }
 
 // Work order of the deposit where none was chosen: angles (or representatives)
-// in blocks of 4.  Corner by corner, blocks of 4 / 8: 45 angles of 128^3 1.64 /
-// 1.74 ms, 128^3 with one pupil point 2.57 / 2.66, 64^3 0.348 / 0.365, 256^3
-// telecentric on dark-edged projections 19.2 / 19.4; plane by plane 128^3 3.92 /
-// 4.14, 256^3 103.5 / 104.1.
+// in blocks of 4.  Corner by corner, blocks of 4 / 8: 180 angles of 128^3,
+// telecentric with one pupil point 4.09 / 4.27 ms, on projections dark outside a
+// part's shadow 2.58 / 2.69, 90 angles of 256^3 with eight points on such 19.7 /
+// 20.0, 45 of 180 angles of 128^3 through a lens 1.89 / 1.89; plane by plane, 180
+// angles of 128^3 4.12 / 4.18, 360 of 256^3 105.3 / 105.0.
 static int deposit_order(const vam_geometry* h) { return h->xcd_deposit >= 0 ? h->xcd_deposit : 4; }
 
 template <int B, typename PT>
@@ -2236,10 +2238,11 @@ static void launch_back_box_t(vam_geometry* h, const MarchParams& P, const PT* p
   // plane by plane for whole turns of quarter-turn angles where no plane
   // between two samples is skipped and the boxes hold enough segments to fill
   // its workgroups (and at the default edge and workgroup size); else corner
-  // by corner.  128^3, 180 angles, planes / corners: 1 pupil point (150 segments
-  // a box) 4.39 / 4.36 ms, 2 points 4.96 / 5.12, 4 points (650) 5.05 / 5.27; on
-  // dark-edged projections 2.98 / 2.72, 3.35 / 3.31, 3.90 / 3.63, with a thin
-  // lens 1.93 / 1.90, 2.13 / 2.10, 2.48 / 2.65; 64^3, 1 point 0.64 / 0.60.
+  // by corner.  128^3, 180 angles, planes / corners, telecentric: 1 pupil point
+  // (150 segments a box) 4.16 / 4.13 ms, 2 points 4.65 / 4.75, 4 points (650) 4.84 /
+  // 5.02, 8 points 5.17 / 6.91; on projections dark outside a part's shadow 2.82 /
+  // 2.56, 3.19 / 3.05, 3.57 / 3.43, 4.36 / 5.08.  Thin lens, dark: 1.77 / 1.69, 1.95 /
+  // 1.91, 2.21 / 2.59, 3.37 / 4.45.  64^3, 180 angles, 1 point 0.60 / 0.58, dark 0.47 / 0.37.
   if (h->boxes.B == kBox && h->desc.step <= 0.99 && h->deposit_threads == 256 && !h->deposit_whole &&
       h->seg_dep.n >= 500 * (int64_t)h->n_boxes && members_together(h, P.a0, na) == 4) {
     // two workgroups fit a CU's LDS: 24 waves at 77 registers (256^3: 512 lanes

@@ -36,7 +36,7 @@ namespace vam {
 // taps, 660 us.  Here the FP32 matrix instructions multiply: a wave has 32 rows
 // x 64 columns (even and odd), and per 8 products of 32 x 32 x 2 it reads two
 // times four values and five weights a lane, a third of the LDS's time.
-// 85 us; 12000 rows of 1024 143 us.
+// 82 us; 12000 rows of 1024 133 us.
 //
 // Precision: the filter all but cancels the value itself and its neighbours,
 // so a sum over ascending b carries large partial sums through most of its
