@@ -428,12 +428,12 @@ __global__ __launch_bounds__(192 * CIB * COB) void k_wgrad(WgradArgs g) {
   // neighbour of theirs may be infinite, and 0 x Inf is NaN: sums that are not
   // finite are formed again without those pixels.
   if (g.H % TH != 0 || g.W % kTile != 0) {
-    float zero = 0.0f;
+    float zero[6] = {};  // six chains
 #pragma unroll
     for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) zero = fmaf(acc[dx][i], 0.0f, zero);
-    if (zero != 0.0f) again = 1;
+      for (int i = 0; i < 16; ++i) zero[2 * dx + (i & 1)] = fmaf(acc[dx][i], 0.0f, zero[2 * dx + (i & 1)]);
+    if (zero[0] + zero[1] + zero[2] + zero[3] + zero[4] + zero[5] != 0.0f) again = 1;
     __syncthreads();
     if (again != 0) {
 #pragma unroll

@@ -132,11 +132,12 @@ __global__ __launch_bounds__(64 * NB) void k_ramlak(const float* __restrict__ in
   }
   if (!any) return;
   const int u = 2 * (K * group + 32 * wave + col);
-  float not_finite = 0.0f;  // NaN if one of the sums is not finite
+  float not_finite[4] = {};  // NaN if one of the sums is not finite (four chains)
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
     const int r = 8 * (i >> 2) + 4 * half + (i & 3);
-    not_finite = fmaf(acc[0][i], 0.0f, fmaf(acc[1][i], 0.0f, not_finite));
+    not_finite[i & 1] = fmaf(acc[0][i], 0.0f, not_finite[i & 1]);
+    not_finite[2 + (i & 1)] = fmaf(acc[1][i], 0.0f, not_finite[2 + (i & 1)]);
     const float *e = x[0] + r * P + 4 + 32 * wave + col, *o = x[1] + r * P + 4 + 32 * wave + col;
     float v[2] = {0.25f * e[0], 0.25f * o[0]};
 #pragma unroll
@@ -156,7 +157,7 @@ __global__ __launch_bounds__(64 * NB) void k_ramlak(const float* __restrict__ in
     else if (u < nu)
       *to = v[0];
   }
-  if (not_finite == 0.0f) return;
+  if (not_finite[0] + not_finite[1] + not_finite[2] + not_finite[3] == 0.0f) return;
   unsigned again = 0u;
 #pragma unroll
   for (int i = 0; i < 32; ++i) again |= acc[i & 1][i >> 1] * 0.0f == 0.0f ? 0u : 1u << i;
