@@ -268,7 +268,8 @@ class Geometry:
         segment), 2 (two lanes, alternate samples), 3 (one lane keeping the
         cell's LDS words in registers; the same bits as 1) or 0 (the default:
         3 with FP32 cells of a voxel and its x neighbour, and angles whole
-        quarter turns apart together; the same bits as 1)."""
+        quarter turns apart together; at box edges 8 and 16 plain 3, or 1 for
+        FP16 volumes; the same bits as 1)."""
         _check(lib().vam_set_variant(self.handle, OP_FORWARD_LANES, int(lanes)))
 
     def set_angle_blocks(self, deposit=None, forward=None):

@@ -418,7 +418,7 @@ vam_status vam_setup_geometry(const vam_geometry_desc* desc, hipStream_t stream,
   h->deposit_threads = 256;
   h->xcd_deposit = -1;  // XCD-aware orders, block sizes by kernel and number of angles (deposit_order, forward_order)
   h->xcd_forward = -1;
-  h->forward_lanes = 0;  // FP32 cells kept in registers (fastest measured for every format)
+  h->forward_lanes = 0;  // FP32 cells kept in registers (fastest measured for every format at the default edge)
   h->angles.resize(desc->n_angles);
   for (int a = 0; a < desc->n_angles; ++a)
     h->angles[a] = desc->angles_rad ? desc->angles_rad[a] : 2.0 * M_PI * a / desc->n_angles;
